@@ -2343,10 +2343,11 @@ gsp_status take_rows(gsp_ctx *ctx, const float *x, const uint8_t *y, int64_t row
 
 // Device scratch of one training call, freed on return.
 struct TrainScratch {
-    float *params = nullptr, *m = nullptr, *v = nullptr, *part = nullptr, *grad = nullptr;
+    float *params = nullptr, *m = nullptr, *v = nullptr, *part = nullptr, *grad = nullptr, *acts = nullptr;
     double *ploss = nullptr, *loss = nullptr;
     ~TrainScratch() {
-        for (void *p : {(void *)params, (void *)m, (void *)v, (void *)part, (void *)grad, (void *)ploss, (void *)loss})
+        for (void *p : {(void *)params, (void *)m, (void *)v, (void *)part, (void *)grad, (void *)acts, (void *)ploss,
+                        (void *)loss})
             if (p) (void)hipFree(p);
     }
 };
@@ -2368,12 +2369,13 @@ gsp_status gsp_pruner_grad(gsp_ctx *ctx, const float *params, const float *x, co
     HIP_TRY(hipMalloc(&t.params, kGateParams * sizeof(float)));
     HIP_TRY(hipMalloc(&t.grad, kGateParams * sizeof(float)));
     HIP_TRY(hipMalloc(&t.part, (size_t)nb * kGateParams * sizeof(float)));
+    HIP_TRY(hipMalloc(&t.acts, mlp_act_floats(rows) * sizeof(float)));
     HIP_TRY(hipMalloc(&t.ploss, (size_t)nb * sizeof(double)));
     HIP_TRY(hipMalloc(&t.loss, sizeof(double)));
     HIP_TRY(hipMemcpyAsync(t.params, params, kGateParams * sizeof(float),
                            where == GSP_DEVICE ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s));
     launch_fill_f64(t.loss, 0.0, 1, s);
-    launch_mlp_grad(t.params, r.x, r.y, rows, pos_weight, 1.0f / (float)rows, t.part, t.ploss, s);
+    launch_mlp_grad(t.params, r.x, r.y, rows, pos_weight, 1.0f / (float)rows, t.acts, t.part, t.ploss, s);
     launch_mlp_reduce(t.part, t.ploss, nb, nullptr, nullptr, nullptr, false, 0.0f, 1.0f, 1.0f, t.grad, t.loss, s);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpyAsync(grad_out, t.grad, kGateParams * sizeof(float),
@@ -2404,6 +2406,7 @@ gsp_status gsp_pruner_train(gsp_ctx *ctx, const float *x, const uint8_t *y, int6
     HIP_TRY(hipMalloc(&t.m, kGateParams * sizeof(float)));
     HIP_TRY(hipMalloc(&t.v, kGateParams * sizeof(float)));
     HIP_TRY(hipMalloc(&t.part, (size_t)nbmax * kGateParams * sizeof(float)));
+    HIP_TRY(hipMalloc(&t.acts, mlp_act_floats(bmax) * sizeof(float)));
     HIP_TRY(hipMalloc(&t.ploss, (size_t)nbmax * sizeof(double)));
     HIP_TRY(hipMalloc(&t.loss, (size_t)(epochs > 0 ? epochs : 1) * sizeof(double)));
     HIP_TRY(hipMemcpyAsync(t.params, params_inout, kGateParams * sizeof(float), hipMemcpyHostToDevice, s));
@@ -2418,8 +2421,8 @@ gsp_status gsp_pruner_train(gsp_ctx *ctx, const float *x, const uint8_t *y, int6
             step++;
             float c1 = (float)(1.0 - std::pow(0.9, (double)step));
             float c2 = (float)(1.0 - std::pow(0.999, (double)step));
-            launch_mlp_grad(t.params, r.x + r0 * kGateFeatures, r.y + r0, len, pos_weight, 1.0f / (float)len, t.part,
-                            t.ploss, s);
+            launch_mlp_grad(t.params, r.x + r0 * kGateFeatures, r.y + r0, len, pos_weight, 1.0f / (float)len, t.acts,
+                            t.part, t.ploss, s);
             launch_mlp_reduce(t.part, t.ploss, nb, t.params, t.m, t.v, true, lr, c1, c2, nullptr, t.loss + ep, s);
         }
         HIP_TRY(hipGetLastError());

@@ -327,9 +327,14 @@ void launch_gate_eval(const GateNet &net, const float *x, int64_t rows, float *l
 // their sum in block order; with `adam` the sum is applied as one Adam step
 // (c1 = 1 - beta1^t, c2 = 1 - beta2^t), else written to grad.  The batch
 // loss (sum of the rows' losses * inv_batch) is added to *loss.
+// acts: mlp_act_floats(rows) floats of scratch (the rows' activations and
+// deltas; larger batches go in slabs of kMlpSlab rows).
 constexpr int kMlpRowsPerBlock = 64;
+constexpr int64_t kMlpSlab = 65536;
+static_assert(kMlpSlab % kMlpRowsPerBlock == 0, "slabs hold whole row blocks");
+size_t mlp_act_floats(int64_t rows);
 void launch_mlp_grad(const float *params, const float *x, const uint8_t *y, int64_t rows, float pos_weight,
-                     float inv_batch, float *part, double *part_loss, hipStream_t s);
+                     float inv_batch, float *acts, float *part, double *part_loss, hipStream_t s);
 void launch_mlp_reduce(const float *part, const double *part_loss, int nblocks, float *params, float *m, float *v,
                        bool adam, float lr, float c1, float c2, float *grad, double *loss, hipStream_t s);
 

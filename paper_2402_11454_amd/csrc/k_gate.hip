@@ -210,121 +210,284 @@ __global__ void __launch_bounds__(kBlock) k_gate_eval(GateNet net, const float *
 
 // ------------------------------------------------------------- training
 
-constexpr int kR = kMlpRowsPerBlock;  // rows per block, one thread per row
+constexpr int kR = kMlpRowsPerBlock;  // rows of one partial gradient
 constexpr int kH = kGateHidden;
 constexpr int kF = kGateFeatures;
-constexpr int kPad = kH + 1;         // row stride of the per-row LDS arrays
 
 __device__ __forceinline__ float softplus_f(float t) { return (t > 0.0f ? t : 0.0f) + log1pf(expf(-fabsf(t))); }
 __device__ __forceinline__ float sigmoid_f(float t) {
     return t >= 0.0f ? 1.0f / (1.0f + expf(-t)) : expf(t) / (1.0f + expf(t));
 }
 
-// One block = kR rows.  Phase A: thread r runs row r forward and backward to
-// the hidden layers' deltas (kept in LDS).  Phase B: thread t sums, over the
-// block's rows, the gradient entries of hidden unit t (column t of W2, row t
-// of W1, b1[t], b2[t], w3[t]; thread 0 also b3), and writes the block's
-// partial gradient in the parameter layout.
-__global__ void __launch_bounds__(kR) k_mlp_grad(const float *params, const float *x, const uint8_t *y,
-                                                 int64_t rows, float pw, float inv_b, float *part,
-                                                 double *part_loss) {
-    __shared__ float sW2[kH][kH];
-    __shared__ float sW1[kH][kF];
-    __shared__ float sb1[kH], sb2[kH], sw3[kH];
-    __shared__ float sx[kR][kF];
-    __shared__ float sh1[kR][kPad], sh2[kR][kPad], sd2[kR][kPad], sd1[kR][kPad];
-    __shared__ float sdz[kR], sloss[kR];
-    const int tid = threadIdx.x;
-    for (int k = tid; k < kH * kH; k += kR) sW2[k / kH][k % kH] = params[kPW2 + k];
-    for (int k = tid; k < kH * kF; k += kR) sW1[k / kF][k % kF] = params[kPW1 + k];
-    for (int k = tid; k < kH; k += kR) {
-        sb1[k] = params[kPB1 + k];
-        sb2[k] = params[kPB2 + k];
-        sw3[k] = params[kPW3 + k];
+// One training batch is three launches: k_mlp_rows (forward and backward of
+// every row to the hidden layers' deltas), k_mlp_part (each block of kR rows'
+// partial gradient) and k_mlp_reduce.  Every output is the same sequence of
+// fp32 products and sums whatever the thread layout: a hidden unit adds its
+// inputs in index order, a partial gradient its kR rows in row order, the
+// reduction its blocks in block order.
+//
+// What bounds it: latency.  A batch of the training recipe has 4096 rows, 64
+// row blocks; with a wavefront per row block (a thread per row, then a
+// thread per hidden unit) 64 of the 256 CUs ran one wavefront each through
+// some 12,000 multiply-adds in a row: 115 us per batch.  The rows go 16 to a
+// workgroup instead (256 workgroups, 16 threads per row with four hidden
+// units each: 10.1 us, of it two trips to memory for the parameters and the
+// rows) and each row block's partial gradient to kPartSlices workgroups
+// (5.5 us).  An epoch of 128 such batches: 17.4 -> 2.74 ms.
+constexpr int kRowTile = 16;         // rows per workgroup of k_mlp_rows
+constexpr int kRowThreads = 16;      // threads per row, kUnits hidden units each
+constexpr int kUnits = kH / kRowThreads;
+constexpr int kStride = kH + 4;      // row stride of its LDS arrays (16-byte rows)
+constexpr int kPartSlices = 6;       // per row block: four quarters of W2's rows, then the other parameters
+constexpr int kPartUnits = kH / (kPartSlices - 2);
+static_assert(kRowTile * kRowThreads == kBlock && kUnits == 4 && kPartUnits * kH == 4 * kBlock, "thread layout");
+
+// acts: five arrays of the slab's rows (padded to kR): h1, h2, d2, d1 with kH
+// values a row, then dz; loss with one.  Rows past `rows` (the padding) run
+// with x = 0 and dz = 0.
+struct MlpActs {
+    float *h1, *h2, *d2, *d1, *dz, *loss;
+};
+
+// acc[k] += sum over j, in order, of m[j][u0 + k] v[j].
+__device__ __forceinline__ void row_times(const float (*m)[kStride], const float *v, int u0, float *acc) {
+#pragma unroll 2
+    for (int j = 0; j < kH; j += 8) {
+        float4 w[8], x[2];
+#pragma unroll
+        for (int q = 0; q < 2; q++) x[q] = *reinterpret_cast<const float4 *>(v + j + 4 * q);
+#pragma unroll
+        for (int q = 0; q < 8; q++) w[q] = *reinterpret_cast<const float4 *>(&m[j + q][u0]);
+        const float xs[8] = {x[0].x, x[0].y, x[0].z, x[0].w, x[1].x, x[1].y, x[1].z, x[1].w};
+#pragma unroll
+        for (int q = 0; q < 8; q++) {
+            acc[0] += w[q].x * xs[q];
+            acc[1] += w[q].y * xs[q];
+            acc[2] += w[q].z * xs[q];
+            acc[3] += w[q].w * xs[q];
+        }
+    }
+}
+
+__global__ void __launch_bounds__(kBlock) k_mlp_rows(const float *params, const float *x, const uint8_t *y,
+                                                     int64_t rows, float pw, float inv_b, MlpActs act) {
+    __shared__ __align__(16) float sW2[kH][kStride], sW2t[kH][kStride];
+    __shared__ float sW1[kH][kF + 1];
+    __shared__ float sb1[kH], sb2[kH];
+    __shared__ __align__(16) float sw3[kH];
+    __shared__ float sx[kRowTile][kF];
+    __shared__ __align__(16) float sh[kRowTile][kStride], sd[kRowTile][kStride];
+    __shared__ float sdz[kRowTile];
+    const int tid = threadIdx.x, r = tid / kRowThreads, u0 = (tid % kRowThreads) * kUnits;
+    const int64_t row = (int64_t)blockIdx.x * kRowTile + r;
+    // the parameters were written by the previous launch (memory, not L2, for
+    // seven of the eight XCDs): all of a thread's loads in one trip
+    float w2[kH * kH / kBlock], w1[kH * kF / kBlock];
+#pragma unroll
+    for (int q = 0; q < kH * kH / kBlock; q++) w2[q] = params[kPW2 + q * kBlock + tid];
+#pragma unroll
+    for (int q = 0; q < kH * kF / kBlock; q++) w1[q] = params[kPW1 + q * kBlock + tid];
+#pragma unroll
+    for (int q = 0; q < kH * kH / kBlock; q++) {
+        const int k = q * kBlock + tid;
+        sW2[k / kH][k % kH] = w2[q];
+        sW2t[k % kH][k / kH] = w2[q];
+    }
+#pragma unroll
+    for (int q = 0; q < kH * kF / kBlock; q++) {
+        const int k = q * kBlock + tid;
+        sW1[k / kF][k % kF] = w1[q];
+    }
+    if (tid < kH) {
+        sb1[tid] = params[kPB1 + tid];
+        sb2[tid] = params[kPB2 + tid];
+        sw3[tid] = params[kPW3 + tid];
     }
     const float b3 = params[kPB3];
-    const int64_t row = (int64_t)blockIdx.x * kR + tid;
-    const bool valid = row < rows;
-#pragma unroll
-    for (int f = 0; f < kF; f++) sx[tid][f] = valid ? x[row * kF + f] : 0.0f;
-    __syncthreads();
-    // ---- phase A
-    for (int h = 0; h < kH; h++) {
-        float s = 0.0f;
-#pragma unroll
-        for (int f = 0; f < kF; f++) s += sW1[h][f] * sx[tid][f];
-        float a1 = s + sb1[h];
-        sh1[tid][h] = a1 > 0.0f ? a1 : 0.0f;
-    }
-    float z = 0.0f;
-    for (int o = 0; o < kH; o++) {
-        float s = 0.0f;
-        for (int h = 0; h < kH; h++) s += sW2[o][h] * sh1[tid][h];
-        float a2 = s + sb2[o];
-        float h2 = a2 > 0.0f ? a2 : 0.0f;
-        sh2[tid][o] = h2;
-        z += sw3[o] * h2;
-    }
-    z += b3;
-    float yr = valid && y[row] ? 1.0f : 0.0f;
-    float dz = 0.0f, loss = 0.0f;
-    if (valid) {
-        loss = pw * yr * softplus_f(-z) + (1.0f - yr) * softplus_f(z);
-        dz = (sigmoid_f(z) * (pw * yr + 1.0f - yr) - pw * yr) * inv_b;
-    }
-    sdz[tid] = dz;
-    sloss[tid] = loss;
-    for (int o = 0; o < kH; o++) sd2[tid][o] = sh2[tid][o] > 0.0f ? dz * sw3[o] : 0.0f;
-    for (int h = 0; h < kH; h++) {
-        float s = 0.0f;
-        for (int o = 0; o < kH; o++) s += sW2[o][h] * sd2[tid][o];
-        sd1[tid][h] = sh1[tid][h] > 0.0f ? s : 0.0f;
+    if (tid < kRowTile * kF) {
+        const int64_t xr = (int64_t)blockIdx.x * kRowTile + tid / kF;
+        sx[tid / kF][tid % kF] = xr < rows ? x[xr * kF + tid % kF] : 0.0f;
     }
     __syncthreads();
-    // ---- phase B: hidden unit t = tid
-    const int t = tid;
+    float h1[kUnits], h2[kUnits], acc[kUnits];
+#pragma unroll
+    for (int k = 0; k < kUnits; k++) {
+        float s = 0.0f;
+#pragma unroll
+        for (int f = 0; f < kF; f++) s += sW1[u0 + k][f] * sx[r][f];
+        const float a1 = s + sb1[u0 + k];
+        h1[k] = a1 > 0.0f ? a1 : 0.0f;
+        sh[r][u0 + k] = h1[k];
+        acc[k] = 0.0f;
+    }
+    __syncthreads();
+    row_times(sW2t, sh[r], u0, acc);
+#pragma unroll
+    for (int k = 0; k < kUnits; k++) {
+        const float a2 = acc[k] + sb2[u0 + k];
+        h2[k] = a2 > 0.0f ? a2 : 0.0f;
+        sd[r][u0 + k] = h2[k];
+    }
+    __syncthreads();
+    if (tid < kRowTile) {   // the output unit and the loss, a thread per row
+        const int64_t orow = (int64_t)blockIdx.x * kRowTile + tid;
+        const bool ok = orow < rows;
+        float z = 0.0f;
+#pragma unroll
+        for (int o = 0; o < kH; o += 4) {
+            const float4 h = *reinterpret_cast<const float4 *>(&sd[tid][o]);
+            const float4 w = *reinterpret_cast<const float4 *>(&sw3[o]);
+            z += w.x * h.x;
+            z += w.y * h.y;
+            z += w.z * h.z;
+            z += w.w * h.w;
+        }
+        z += b3;
+        const float yr = ok && y[orow] ? 1.0f : 0.0f;
+        float dz = 0.0f, loss = 0.0f;
+        if (ok) {
+            loss = pw * yr * softplus_f(-z) + (1.0f - yr) * softplus_f(z);
+            dz = (sigmoid_f(z) * (pw * yr + 1.0f - yr) - pw * yr) * inv_b;
+        }
+        sdz[tid] = dz;
+        act.dz[orow] = dz;
+        act.loss[orow] = loss;
+    }
+    __syncthreads();
+    float d2[kUnits];
+    const float dz = sdz[r];
+#pragma unroll
+    for (int k = 0; k < kUnits; k++) {
+        d2[k] = h2[k] > 0.0f ? dz * sw3[u0 + k] : 0.0f;
+        sd[r][u0 + k] = d2[k];
+        acc[k] = 0.0f;
+    }
+    __syncthreads();
+    row_times(sW2, sd[r], u0, acc);
+    const int64_t at = row * kH + u0;
+    *reinterpret_cast<float4 *>(act.h1 + at) = make_float4(h1[0], h1[1], h1[2], h1[3]);
+    *reinterpret_cast<float4 *>(act.h2 + at) = make_float4(h2[0], h2[1], h2[2], h2[3]);
+    *reinterpret_cast<float4 *>(act.d2 + at) = make_float4(d2[0], d2[1], d2[2], d2[3]);
+    *reinterpret_cast<float4 *>(act.d1 + at) =
+        make_float4(h1[0] > 0.0f ? acc[0] : 0.0f, h1[1] > 0.0f ? acc[1] : 0.0f, h1[2] > 0.0f ? acc[2] : 0.0f,
+                    h1[3] > 0.0f ? acc[3] : 0.0f);
+}
+
+// Partial gradient of row block blockIdx.x (kR rows, summed in row order) in
+// the parameter layout.  Slice blockIdx.y < 4: rows [16 y, 16 y + 16) of dW2,
+// thread t = hidden unit (column), group = four of those rows.  Slice 4: dW1
+// and b1; slice 5: b2, w3, b3 and the block's loss, a wavefront each.
+__global__ void __launch_bounds__(kBlock) k_mlp_part(const float *x, int64_t rows, float inv_b, MlpActs act,
+                                                     float *part, double *part_loss) {
+    __shared__ __align__(16) float sa[kR][kStride];
+    __shared__ __align__(16) float sb[kR][kStride];
+    __shared__ float sx[kR][kF];
+    __shared__ float sz[kR], sl[kR];
+    const int tid = threadIdx.x, t = tid % kH, grp = tid / kH;
+    const int64_t r0 = (int64_t)blockIdx.x * kR;
     float *pp = part + (int64_t)blockIdx.x * kGateParams;
-    float acc[kH];
+    if (blockIdx.y < kPartSlices - 2) {
+        const int o0 = blockIdx.y * kPartUnits;
+        for (int k = tid; k < kR * kH / 4; k += kBlock) {
+            const int rr = k / (kH / 4), c = (k % (kH / 4)) * 4;
+            *reinterpret_cast<float4 *>(&sa[rr][c]) = *reinterpret_cast<const float4 *>(act.h1 + (r0 + rr) * kH + c);
+        }
+        {
+            const int rr = tid / (kPartUnits / 4), c = (tid % (kPartUnits / 4)) * 4;
+            *reinterpret_cast<float4 *>(&sb[rr][c]) =
+                *reinterpret_cast<const float4 *>(act.d2 + (r0 + rr) * kH + o0 + c);
+        }
+        __syncthreads();
+        float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 16
+        for (int r = 0; r < kR; r++) {
+            const float hv = sa[r][t];
+            const float4 d = *reinterpret_cast<const float4 *>(&sb[r][grp * 4]);
+            acc[0] += d.x * hv;
+            acc[1] += d.y * hv;
+            acc[2] += d.z * hv;
+            acc[3] += d.w * hv;
+        }
 #pragma unroll
-    for (int o = 0; o < kH; o++) acc[o] = 0.0f;
-    float g1[kF] = {0, 0, 0, 0, 0, 0, 0, 0};
-    float db1 = 0.0f, db2 = 0.0f, dw3 = 0.0f, db3 = 0.0f;
-    for (int r = 0; r < kR; r++) {
-        float hv = sh1[r][t];
-#pragma unroll
-        for (int o = 0; o < kH; o++) acc[o] += sd2[r][o] * hv;   // dW2[o][t]
-        float d1 = sd1[r][t];
-#pragma unroll
-        for (int f = 0; f < kF; f++) g1[f] += d1 * sx[r][f];      // dW1[t][f]
-        db1 += d1;
-        db2 += sd2[r][t];
-        dw3 += sdz[r] * sh2[r][t];
-        db3 += sdz[r];
+        for (int k = 0; k < 4; k++) pp[kPW2 + (o0 + grp * 4 + k) * kH + t] = acc[k];
+        return;
     }
-#pragma unroll
-    for (int o = 0; o < kH; o++) pp[kPW2 + o * kH + t] = acc[o];
-#pragma unroll
-    for (int f = 0; f < kF; f++) pp[kPW1 + t * kF + f] = g1[f];
-    pp[kPB1 + t] = db1;
-    pp[kPB2 + t] = db2;
-    pp[kPW3 + t] = dw3;
-    if (t == 0) {
+    const bool first = blockIdx.y == kPartSlices - 2;
+    const float *ga = first ? act.d1 : act.d2;
+    for (int k = tid; k < kR * kH / 4; k += kBlock) {
+        const int rr = k / (kH / 4), c = (k % (kH / 4)) * 4;
+        *reinterpret_cast<float4 *>(&sa[rr][c]) = *reinterpret_cast<const float4 *>(ga + (r0 + rr) * kH + c);
+        if (!first)
+            *reinterpret_cast<float4 *>(&sb[rr][c]) = *reinterpret_cast<const float4 *>(act.h2 + (r0 + rr) * kH + c);
+    }
+    if (first) {
+        for (int k = tid; k < kR * kF; k += kBlock) {
+            const int64_t row = r0 + k / kF;
+            sx[k / kF][k % kF] = row < rows ? x[row * kF + k % kF] : 0.0f;
+        }
+    } else if (tid < kR) {
+        sz[tid] = act.dz[r0 + tid];
+        sl[tid] = act.loss[r0 + tid];
+    }
+    __syncthreads();
+    if (first) {
+        float g[2] = {0.0f, 0.0f}, db1 = 0.0f;
+#pragma unroll 16
+        for (int r = 0; r < kR; r++) {
+            const float d1 = sa[r][t];
+            g[0] += d1 * sx[r][2 * grp];   // dW1[t][2 grp], dW1[t][2 grp + 1]
+            g[1] += d1 * sx[r][2 * grp + 1];
+            db1 += d1;
+        }
+        pp[kPW1 + t * kF + 2 * grp] = g[0];
+        pp[kPW1 + t * kF + 2 * grp + 1] = g[1];
+        if (grp == 0) pp[kPB1 + t] = db1;
+    } else if (grp == 0) {
+        float db2 = 0.0f;
+#pragma unroll 16
+        for (int r = 0; r < kR; r++) db2 += sa[r][t];
+        pp[kPB2 + t] = db2;
+    } else if (grp == 1) {
+        float dw3 = 0.0f;
+#pragma unroll 16
+        for (int r = 0; r < kR; r++) dw3 += sz[r] * sb[r][t];
+        pp[kPW3 + t] = dw3;
+    } else if (grp == 2 && t == 0) {
+        float db3 = 0.0f;
+#pragma unroll 16
+        for (int r = 0; r < kR; r++) db3 += sz[r];
         pp[kPB3] = db3;
+    } else if (grp == 3 && t == 0) {
         double L = 0.0;
-        for (int r = 0; r < kR; r++) L += (double)sloss[r];
+#pragma unroll 16
+        for (int r = 0; r < kR; r++) L += (double)sl[r];
         part_loss[blockIdx.x] = L * (double)inv_b;
     }
 }
 
 // Sum of the blocks' partial gradients (in block order), then one Adam step
-// (beta1 0.9, beta2 0.999, eps 1e-8) or the gradient itself.
-__global__ void __launch_bounds__(kBlock) k_mlp_reduce(const float *part, const double *part_loss, int nblocks,
+// (beta1 0.9, beta2 0.999, eps 1e-8) or the gradient itself.  A thread per
+// parameter, kReduceAhead partials in flight at once: the sum is a serial
+// chain, its loads need not be (4096-row batches, 64 partials: 19 us with the
+// loads in the chain, 4.9 us with them ahead and the losses' own chain in a
+// workgroup of its own).
+constexpr int kReduceThreads = kWave, kReduceAhead = 64;
+
+__global__ void __launch_bounds__(kReduceThreads) k_mlp_reduce(const float *part, const double *part_loss, int nblocks,
                                                        float *params, float *m, float *v, int adam, float lr,
                                                        float c1, float c2, float *grad, double *loss) {
-    int k = blockIdx.x * kBlock + threadIdx.x;
+    int k = blockIdx.x * kReduceThreads + threadIdx.x;
     if (k < kGateParams) {
         float g = 0.0f;
-        for (int b = 0; b < nblocks; b++) g += part[(int64_t)b * kGateParams + k];
+        for (int b = 0; b < nblocks; b += kReduceAhead) {
+            float p[kReduceAhead];
+#pragma unroll
+            for (int q = 0; q < kReduceAhead; q++)
+                p[q] = b + q < nblocks ? part[(int64_t)(b + q) * kGateParams + k] : 0.0f;
+#pragma unroll
+            for (int q = 0; q < kReduceAhead; q++)
+                if (b + q < nblocks) g += p[q];
+        }
         if (adam) {
             float mk = 0.9f * m[k] + 0.1f * g;
             float vk = 0.999f * v[k] + 0.001f * (g * g);
@@ -336,10 +499,14 @@ __global__ void __launch_bounds__(kBlock) k_mlp_reduce(const float *part, const 
             grad[k] = g;
         }
     }
-    if (k == 0 && loss) {
+    if (blockIdx.x == gridDim.x - 1 && loss) {   // a workgroup of its own: the blocks' losses, in order
         double L = 0.0;
-        for (int b = 0; b < nblocks; b++) L += part_loss[b];
-        *loss += L;
+        for (int b = 0; b < nblocks; b += kReduceThreads) {
+            const int m = nblocks - b < kReduceThreads ? nblocks - b : kReduceThreads;
+            const double v = (int)threadIdx.x < m ? part_loss[b + threadIdx.x] : 0.0;
+            for (int q = 0; q < m; q++) L += __shfl(v, q);
+        }
+        if (threadIdx.x == 0) *loss += L;
     }
 }
 
@@ -365,16 +532,33 @@ void launch_gate_eval(const GateNet &net, const float *x, int64_t rows, float *l
     k_gate_eval<<<grid_cap((rows + kBlock - 1) / kBlock, 4096), kBlock, 0, s>>>(net, x, rows, logit);
 }
 
+size_t mlp_act_floats(int64_t rows) {
+    if (rows > kMlpSlab) rows = kMlpSlab;
+    return (size_t)((rows + kR - 1) / kR) * kR * (4 * kH + 2);
+}
+
 void launch_mlp_grad(const float *params, const float *x, const uint8_t *y, int64_t rows, float pos_weight,
-                     float inv_batch, float *part, double *part_loss, hipStream_t s) {
-    if (rows == 0) return;
-    unsigned nb = (unsigned)((rows + kR - 1) / kR);
-    k_mlp_grad<<<nb, kR, 0, s>>>(params, x, y, rows, pos_weight, inv_batch, part, part_loss);
+                     float inv_batch, float *acts, float *part, double *part_loss, hipStream_t s) {
+    for (int64_t r0 = 0; r0 < rows; r0 += kMlpSlab) {
+        const int64_t len = rows - r0 < kMlpSlab ? rows - r0 : kMlpSlab, nb = (len + kR - 1) / kR, pad = nb * kR;
+        MlpActs a;
+        a.h1 = acts;
+        a.h2 = a.h1 + pad * kH;
+        a.d2 = a.h2 + pad * kH;
+        a.d1 = a.d2 + pad * kH;
+        a.dz = a.d1 + pad * kH;
+        a.loss = a.dz + pad;
+        k_mlp_rows<<<(unsigned)(pad / kRowTile), kBlock, 0, s>>>(params, x + r0 * kF, y + r0, len, pos_weight,
+                                                                 inv_batch, a);
+        k_mlp_part<<<dim3((unsigned)nb, kPartSlices), kBlock, 0, s>>>(x + r0 * kF, len, inv_batch, a,
+                                                                      part + (r0 / kR) * kGateParams,
+                                                                      part_loss + r0 / kR);
+    }
 }
 
 void launch_mlp_reduce(const float *part, const double *part_loss, int nblocks, float *params, float *m, float *v,
                        bool adam, float lr, float c1, float c2, float *grad, double *loss, hipStream_t s) {
-    k_mlp_reduce<<<(kGateParams + kBlock - 1) / kBlock, kBlock, 0, s>>>(part, part_loss, nblocks, params, m, v,
+    k_mlp_reduce<<<(kGateParams + kReduceThreads - 1) / kReduceThreads + 1, kReduceThreads, 0, s>>>(part, part_loss, nblocks, params, m, v,
                                                                         adam ? 1 : 0, lr, c1, c2, grad, loss);
 }
 

@@ -123,6 +123,19 @@ def test_gradient_matches_oracle(ctx, rows):
         assert np.linalg.norm(g.astype(np.float64) - g64) <= 1e-4 * np.linalg.norm(g64)
 
 
+@pytest.mark.parametrize("rows", [15, 16, 17, 63, 65, 4096, 65535, 65537])
+def test_gradient_at_the_tiles_edges(ctx, rows):
+    """Row tiles of 16, row blocks of 64 and slabs of 65536 rows: one more,
+    one less and exactly full.  Tolerance: fp32 sums of `rows` terms, as for
+    the gradients above."""
+    x, y = _rows(60 + rows, rows)
+    p = _params(61)
+    loss, g = ctx.pruner_grad(p, x, y, 1.7)
+    l64, g64 = oracle.mlp_loss_grad(p, x, y, 1.7)
+    assert math.isclose(loss, l64, rel_tol=1e-5)
+    assert np.linalg.norm(g.astype(np.float64) - g64) <= 1e-4 * np.linalg.norm(g64)
+
+
 def test_adam_step_matches_oracle(ctx):
     x, y = _rows(40, 512)
     p = _params(41)
