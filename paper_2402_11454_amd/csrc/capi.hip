@@ -1217,7 +1217,14 @@ gsp_status modularity_of(gsp_ctx *ctx, const int32_t *m, double *out) {
     launch_fill_f64(ctx->sc.f64, 0.0, 1, s);
     launch_fill_u64(ctx->sc.u64, 0, 1, s);
     launch_community_totals(ctx->K0, m, ctx->n, ctx->sig, nullptr, s);
-    launch_modularity_parts(level0(ctx), m, ctx->K0, ctx->sig, ctx->sc.f64, s);
+    if (ctx->ordered) {
+        // the copy in degree order is there: its columns repeat the hot
+        // vertices' lines, so the gathers of the labels hit the caches more
+        launch_gather_i32(m, ctx->ord.orig, ctx->n, ctx->dec, s);
+        launch_inside_weight(level_ordered(ctx), ctx->dec, ctx->sc.f64, s);
+    } else {
+        launch_inside_weight(level0(ctx), m, ctx->sc.f64, s);
+    }
     launch_sum_squares(ctx->sig, ctx->n, ctx->M2, ctx->sc.u64, s);
     HIP_TRY(hipMemcpyAsync(ctx->f64_h, ctx->sc.f64, sizeof(double), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipMemcpyAsync(ctx->i64_h, ctx->sc.u64, sizeof(int64_t), hipMemcpyDeviceToHost, s));

@@ -219,22 +219,7 @@ __device__ __forceinline__ long long group_sum_ll(long long x) {
 // Wave-aggregated atomics keyed by an index: lanes of one wavefront that hit
 // the same element are combined into one atomic (a popular community would
 // otherwise serialise thousands of same-address atomics).  Lanes are taken
-// one distinct key at a time; at most 64 rounds.
-__device__ __forceinline__ void wave_add_i32_by_key(int *base, int key, int val, bool pred) {
-    unsigned long long pending = __ballot(pred);
-    while (pending) {
-        int leader = __ffsll((long long)pending) - 1;
-        int lk = __shfl(key, leader);
-        bool mine = pred && key == lk && ((pending >> lane_id()) & 1ull);
-        unsigned long long m = __ballot(mine);
-        int sum = mine ? val : 0;
-#pragma unroll
-        for (int off = kWave / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
-        if (lane_id() == leader) atomicAdd(&base[lk], sum);
-        pending &= ~m;
-    }
-}
-
+// one distinct key at a time; at most 64 rounds, so for few distinct keys.
 __device__ __forceinline__ void wave_add_u64_by_key(unsigned long long *base, int key, unsigned long long val,
                                                     bool pred) {
     unsigned long long pending = __ballot(pred);

@@ -238,11 +238,11 @@ void launch_labels_min_orig(int32_t *lab, const int32_t *orig, int64_t n, int32_
 void launch_labels_orig(const int32_t *lab, const int32_t *orig, int64_t n, int32_t *out, hipStream_t s);
 // out[orig[v]] <- in[v].
 void launch_scatter_by_orig(const int32_t *in, const int32_t *orig, int64_t n, int32_t *out, hipStream_t s);
-// Modularity parts: *sigma_in += sum of entries inside communities,
-// sig[c] += K_i; then q = sigma_in/M2 - sum_c (sig[c]/M2)^2, the second sum
-// in units of 2^-62 (*out of launch_sum_squares), exact in any order.
-void launch_modularity_parts(const Level &g, const int32_t *memb, const double *K, double *sig, double *sigma_in,
-                             hipStream_t s);
+// *out += entry weight inside the communities of memb (a batch: out[k] +=
+// that of graph k); g an input graph (dense rows).  Modularity is then
+// *out / M2 - sum_c (sig[c] / M2)^2, the second sum in units of 2^-62 (*out
+// of launch_sum_squares), exact in any order.
+void launch_inside_weight(const Level &g, const int32_t *memb, double *out, hipStream_t s);
 void launch_sum_squares(const double *sig, int64_t n, double M2, unsigned long long *out, hipStream_t s);
 void launch_check_labels(const int32_t *memb, int64_t n, int *err, hipStream_t s);
 // Weight grid (exact sums): every weight becomes the nearest multiple of
@@ -374,6 +374,8 @@ int launch_split_lp(const Level &g, const int32_t *cm, int32_t *labels, uint8_t 
 void launch_renumber(const int32_t *labels, int64_t n, int32_t *out, int32_t *flag, int32_t *rank, int64_t *count,
                      void *tmp, hipStream_t s);
 void launch_lookup(int32_t *top, int64_t n, const int32_t *cm, hipStream_t s);
+// out[v] = tab[idx[v]].
+void launch_gather_i32(const int32_t *tab, const int32_t *idx, int64_t n, int32_t *out, hipStream_t s);
 // Counts communities (of memb) with more than one component (labels).
 void launch_count_disconnected(const int32_t *labels, const int32_t *memb, int64_t n, int32_t *roots_per_comm,
                                unsigned long long *out, hipStream_t s);

@@ -52,34 +52,6 @@ __global__ void __launch_bounds__(kBlock) k_batch_cfirst(const int32_t *rank, co
         cfirst[g] = g < G ? (int64_t)rank[vbase[g]] : *count;
 }
 
-// Intra-community entry weight per graph: a wavefront takes 64 consecutive
-// rows and flushes its running sum whenever the graph changes.
-template <int WT>
-__global__ void __launch_bounds__(kBlock) k_batch_qin(Level g, const int32_t *memb, double *qin) {
-    const int lane = lane_id();
-    const int64_t wid = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
-    const int64_t nw = (int64_t)gridDim.x * (kBlock / kWave);
-    for (int64_t r0 = wid * kWave; r0 < g.n; r0 += nw * kWave) {
-        int64_t r1 = r0 + kWave < g.n ? r0 + kWave : g.n;
-        int cur = g.gid[r0];
-        double run = 0.0;
-        for (int64_t i = r0; i < r1; i++) {
-            int gi = g.gid[i];
-            if (gi != cur) {
-                if (lane == 0 && run != 0.0) unsafeAtomicAdd(&qin[cur], run);
-                run = 0.0;
-                cur = gi;
-            }
-            int32_t c = memb[i];
-            double s = 0.0;
-            for (int64_t k = g.off[i] + lane; k < g.off[i] + g.deg[i]; k += kWave)
-                if (memb[g.col[k]] == c) s += edge_weight<WT>(g.w, k);
-            run += group_sum<kWave>(s);
-        }
-        if (lane == 0 && run != 0.0) unsafeAtomicAdd(&qin[cur], run);
-    }
-}
-
 // One block per graph: Q_g = qin_g / 2m_g - sum over g's communities of
 // (Sigma_c / 2m_g)^2 (0 for 2m_g = 0).
 __global__ void __launch_bounds__(kBlock) k_batch_q(const double *sig, const int64_t *cfirst, int64_t G,
@@ -139,15 +111,7 @@ void launch_batch_cfirst(const int32_t *rank, const int64_t *vbase, int64_t G, c
 void launch_batch_modularity(const Level &g, const int32_t *memb, const double *sig, const int64_t *cfirst,
                              double *qin, double *q, hipStream_t s) {
     launch_fill_f64(qin, 0.0, g.graphs, s);
-    if (g.n > 0) {
-        unsigned gr = grid_of(g.n, (int64_t)kWave * (kBlock / kWave), 4096);
-        if (g.wt == W_UNIT)
-            k_batch_qin<W_UNIT><<<gr, kBlock, 0, s>>>(g, memb, qin);
-        else if (g.wt == W_F32)
-            k_batch_qin<W_F32><<<gr, kBlock, 0, s>>>(g, memb, qin);
-        else
-            k_batch_qin<W_F64><<<gr, kBlock, 0, s>>>(g, memb, qin);
-    }
+    launch_inside_weight(g, memb, qin, s);
     k_batch_q<<<grid_of(g.graphs, 1, 4096), kBlock, 0, s>>>(sig, cfirst, g.graphs, g.M2g, qin, q);
 }
 

@@ -1236,15 +1236,56 @@ __global__ void __launch_bounds__(kBlock) k_move_apply(MoveArgs a, int nq) {
     }
 }
 
+// sig[c] += K_i and csize[c] += 1 over the vertices i of community c.  A
+// tile of kTotalsTile vertices is summed per community in LDS first, so a
+// popular community costs one atomic per tile and distinct communities one
+// each.  (Combining the lanes of a wavefront key by key instead takes 64
+// rounds of shuffles when they all differ: R-MAT 24, 16.8 M vertices in 7.9 M
+// communities, 1.03 ms against 12.5.)
+constexpr int kTotalsTile = 4 * kBlock;
+constexpr int kTotalsTable = 2 * kTotalsTile;
+
+template <bool SIZES>
 __global__ void __launch_bounds__(kBlock) k_community_totals(const double *K, const int32_t *cm, int64_t n,
                                                             double *sig, int32_t *csize) {
-    for (int64_t i0 = blockIdx.x * (int64_t)kBlock; i0 < n; i0 += (int64_t)gridDim.x * kBlock) {
-        int64_t i = i0 + threadIdx.x;
-        bool ok = i < n;
-        int c = ok ? cm[i] : 0;
-        double k = ok ? K[i] : 0.0;
-        wave_add_f64_by_key(sig, c, k, ok && k != 0.0);
-        if (csize) wave_add_i32_by_key(csize, c, 1, ok);
+    __shared__ int tk[kTotalsTable];
+    __shared__ double tv[kTotalsTable];
+    __shared__ int tc[SIZES ? kTotalsTable : 1];
+    for (int q = threadIdx.x; q < kTotalsTable; q += kBlock) {
+        tk[q] = kEmpty;
+        tv[q] = 0.0;
+        if (SIZES) tc[q] = 0;
+    }
+    __syncthreads();
+    for (int64_t i0 = blockIdx.x * (int64_t)kTotalsTile; i0 < n; i0 += (int64_t)gridDim.x * kTotalsTile) {
+        int c[4];
+        double k[4];
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int64_t i = i0 + r * kBlock + threadIdx.x;
+            c[r] = i < n ? cm[i] : kEmpty;
+            k[r] = i < n ? K[i] : 0.0;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            if (c[r] == kEmpty) continue;
+            const int q = lds_table_slot(tk, kTotalsTable - 1, c[r]);
+            if (k[r] != 0.0) atomicAdd(&tv[q], k[r]);
+            if (SIZES) atomicAdd(&tc[q], 1);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kTotalsTable / kBlock; r++) {
+            const int q = r * kBlock + threadIdx.x;
+            const int key = tk[q];
+            if (key == kEmpty) continue;
+            if (tv[q] != 0.0) unsafeAtomicAdd(&sig[key], tv[q]);
+            if (SIZES) atomicAdd(&csize[key], tc[q]);
+            tk[q] = kEmpty;
+            tv[q] = 0.0;
+            if (SIZES) tc[q] = 0;
+        }
+        __syncthreads();
     }
 }
 
@@ -1260,7 +1301,12 @@ inline int64_t sched_cap(const MoveArgs &a, int64_t cap) { return a.grid_cap > 0
 
 void launch_community_totals(const double *K, const int32_t *cm, int64_t n, double *sig, int32_t *csize,
                              hipStream_t s) {
-    if (n > 0) k_community_totals<<<cap_grid((n + kBlock - 1) / kBlock, 8192), kBlock, 0, s>>>(K, cm, n, sig, csize);
+    if (n == 0) return;
+    const unsigned gr = cap_grid((n + kTotalsTile - 1) / kTotalsTile, 8192);
+    if (csize)
+        k_community_totals<true><<<gr, kBlock, 0, s>>>(K, cm, n, sig, csize);
+    else
+        k_community_totals<false><<<gr, kBlock, 0, s>>>(K, cm, n, sig, nullptr);
 }
 
 void launch_move_compact(const MoveArgs &a, const WorkLists &wl, hipStream_t s) {

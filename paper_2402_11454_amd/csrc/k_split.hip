@@ -268,8 +268,28 @@ __global__ void __launch_bounds__(kBlock) k_lookup(int32_t *top, int64_t n, cons
 
 __global__ void __launch_bounds__(kBlock) k_roots_per_comm(const int32_t *labels, const int32_t *memb, int64_t n,
                                                           int32_t *cnt) {
-    for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock)
-        if (labels[i] == (int32_t)i) atomicAdd(&cnt[memb[i]], 1);
+    // the roots of a tile are counted per community in LDS first: with many
+    // roots per community (labels from elsewhere) an atomic per root piles
+    // up on a few addresses (R-MAT 22, 4.2 M vertices, power-law labels:
+    // 687 -> 235 us)
+    __shared__ int tk[kVoteTable];
+    __shared__ int tv[kVoteTable];
+    for (int q = threadIdx.x; q < kVoteTable; q += kBlock) {
+        tk[q] = kEmpty;
+        tv[q] = 0;
+    }
+    __syncthreads();
+    for (int64_t i0 = blockIdx.x * (int64_t)kVoteTile; i0 < n; i0 += (int64_t)gridDim.x * kVoteTile) {
+        for (int64_t i = i0 + threadIdx.x; i < i0 + kVoteTile && i < n; i += kBlock)
+            if (labels[i] == (int32_t)i) atomicAdd(&tv[lds_table_slot(tk, kVoteTable - 1, memb[i])], 1);
+        __syncthreads();
+        for (int q = threadIdx.x; q < kVoteTable; q += kBlock) {
+            if (tk[q] != kEmpty) atomicAdd(&cnt[tk[q]], tv[q]);
+            tk[q] = kEmpty;
+            tv[q] = 0;
+        }
+        __syncthreads();
+    }
 }
 
 __global__ void __launch_bounds__(kBlock) k_count_gt1(const int32_t *cnt, int64_t n, unsigned long long *out) {
@@ -490,10 +510,15 @@ void launch_lookup(int32_t *top, int64_t n, const int32_t *cm, hipStream_t s) {
     if (n > 0) k_lookup<<<grid1(n), kBlock, 0, s>>>(top, n, cm);
 }
 
+void launch_gather_i32(const int32_t *tab, const int32_t *idx, int64_t n, int32_t *out, hipStream_t s) {
+    if (n > 0) k_gather<<<grid1(n), kBlock, 0, s>>>(tab, idx, n, out);
+}
+
 void launch_count_disconnected(const int32_t *labels, const int32_t *memb, int64_t n, int32_t *roots_per_comm,
                                unsigned long long *out, hipStream_t s) {
     launch_fill_i32(roots_per_comm, 0, n, s);
-    k_roots_per_comm<<<grid1(n), kBlock, 0, s>>>(labels, memb, n, roots_per_comm);
+    k_roots_per_comm<<<(unsigned)std::min<int64_t>((n + kVoteTile - 1) / kVoteTile, 4096), kBlock, 0, s>>>(
+        labels, memb, n, roots_per_comm);
     k_count_gt1<<<grid1(n), kBlock, 0, s>>>(roots_per_comm, n, out);
 }
 

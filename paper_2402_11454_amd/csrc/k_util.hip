@@ -268,30 +268,142 @@ __global__ void __launch_bounds__(kBlock) k_vertex_weights_rows(Level g, double 
     }
 }
 
-// One wavefront per row: *sigma_in += entries of row i whose column shares
-// i's community (the community totals come from launch_community_totals).
-template <int WT>
-__global__ void __launch_bounds__(kBlock) k_modularity_parts(Level g, const int32_t *memb, const double *K,
-                                                            double *sig, double *sigma_in) {
+// Entry weight inside communities: out += w_ij over the entries (i, j) with
+// memb[i] = memb[j], or out[gid[i]] += of a batch.  Rows are dense (an input
+// graph, loaded or in degree order).
+//
+// What bounds it: the random gathers of memb[j].  A wavefront per row kept
+// one gather per lane in flight and left most lanes idle on short rows; here
+// a workgroup takes tiles of kInTile consecutive entries, whatever rows they
+// belong to, sixteen entries per thread with all their gathers in flight.
+// The row of each entry comes from the tile's row starts, marked in LDS (the
+// first row is found by a 64-way search of the offsets) and filled in by a
+// running maximum.  A workgroup walks consecutive tiles and flushes its sum
+// at their end (batch: where the graph changes), as thousands of atomics on
+// one address take longer than the tiles.  Measured: R-MAT 24 (520 M entries,
+// fp32 weights, degree order) 13.3 -> 6.3 ms, R-MAT 22 in the loaded order
+// 2.29 -> 1.34 ms, a road-like graph of 31 M entries 3.07 -> 0.63 ms.
+constexpr int kInPer = 16;
+constexpr int kInTile = kBlock * kInPer;
+
+// Largest r in [0, n) with off[r] <= e (off[0] = 0 <= e); by a whole wavefront.
+__device__ __forceinline__ int64_t wave_row_of(const int64_t *off, int64_t n, int64_t e) {
+    int64_t lo = 0, len = n;
+    while (len > 1) {
+        const int64_t step = (len + kWave - 1) / kWave, at = lane_id() * step;
+        const bool ok = at < len && off[lo + at] <= e;
+        const int64_t k = __popcll(__ballot(ok)) - 1;
+        lo += k * step;
+        len = step < len - k * step ? step : len - k * step;
+    }
+    return lo;
+}
+
+template <int WT, bool BATCH>
+__global__ void __launch_bounds__(kBlock) k_inside_weight(Level g, const int32_t *memb, int64_t tiles, double *out) {
+    __shared__ __align__(16) int srow[kInTile];
+    __shared__ int64_t sr[2];
+    __shared__ int wmax[kBlock / kWave];
     __shared__ double part[kBlock / kWave];
-    int lane = lane_id(), w = threadIdx.x / kWave;
-    double blk = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * (kBlock / kWave) + w; i < g.n; i += (int64_t)gridDim.x * (kBlock / kWave)) {
-        int64_t b = g.off[i], e = b + g.deg[i];   // rows may be gapped
-        int32_t c = memb[i];
-        double s = 0.0;
-        for (int64_t k = b + lane; k < e; k += kWave)
-            if (memb[g.col[k]] == c) s += edge_weight<WT>(g.w, k);
-        s = group_sum<kWave>(s);
-        if (lane == 0) blk += s;
+    const int tid = threadIdx.x, lane = lane_id(), w = tid / kWave;
+    const int64_t t0 = tiles * blockIdx.x / gridDim.x, t1 = tiles * (blockIdx.x + 1) / gridDim.x;
+    double s = 0.0;
+    int cur = -1;   // batch: the graph s belongs to
+    auto flush = [&](double *to) {
+        const double v = group_sum<kWave>(s);
+        s = 0.0;
+        if (lane == 0) part[w] = v;
+        __syncthreads();
+        if (tid == 0) {
+            double t = 0.0;
+            for (int k = 0; k < kBlock / kWave; k++) t += part[k];
+            if (t != 0.0) unsafeAtomicAdd(to, t);
+        }
+        __syncthreads();
+    };
+    for (int64_t t = t0; t < t1; t++) {
+        const int64_t e0 = t * kInTile, e1 = e0 + kInTile < g.nnz ? e0 + kInTile : g.nnz;
+        int j[kInPer];
+#pragma unroll
+        for (int k = 0; k < kInPer; k++) {
+            const int64_t e = e0 + k * kBlock + tid;
+            j[k] = e < e1 ? load_col(g.col, e) : -1;
+        }
+        if (w < 2) {
+            const int64_t r = wave_row_of(g.off, g.n, w == 0 ? e0 : e1 - 1);
+            if (lane == 0) sr[w] = r;
+        }
+#pragma unroll
+        for (int k = 0; k < kInPer; k++) srow[k * kBlock + tid] = 0;
+        __syncthreads();
+        const int64_t r0 = sr[0], r1 = sr[1];
+        for (int64_t r = r0 + 1 + tid; r <= r1; r += kBlock) atomicMax(&srow[g.off[r] - e0], (int)(r - r0));
+        int cj[kInPer];
+#pragma unroll
+        for (int k = 0; k < kInPer; k++) cj[k] = j[k] >= 0 ? memb[j[k]] : -1;
+        __syncthreads();
+        // running maximum: a thread's sixteen consecutive entries, then the
+        // wavefront's lanes, then the wavefronts
+        int m[kInPer];
+        int run = 0;
+#pragma unroll
+        for (int q = 0; q < kInPer / 4; q++) {
+            const int4 v = *reinterpret_cast<const int4 *>(&srow[tid * kInPer + 4 * q]);
+            m[4 * q] = run = max(run, v.x);
+            m[4 * q + 1] = run = max(run, v.y);
+            m[4 * q + 2] = run = max(run, v.z);
+            m[4 * q + 3] = run = max(run, v.w);
+        }
+        int inc = run;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int y = __shfl_up(inc, o);
+            if (lane >= o) inc = max(inc, y);
+        }
+        int before = __shfl_up(inc, 1);
+        if (lane == 0) before = 0;
+        if (lane == kWave - 1) wmax[w] = inc;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kBlock / kWave - 1; q++)
+            if (q < w) before = max(before, wmax[q]);
+#pragma unroll
+        for (int q = 0; q < kInPer / 4; q++)
+            *reinterpret_cast<int4 *>(&srow[tid * kInPer + 4 * q]) =
+                make_int4(max(before, m[4 * q]), max(before, m[4 * q + 1]), max(before, m[4 * q + 2]),
+                          max(before, m[4 * q + 3]));
+        __syncthreads();
+        if constexpr (BATCH) {
+            const int ga = g.gid[r0], gb = g.gid[r1];
+            if (ga != gb) {   // several graphs in the tile: each wavefront adds graph by graph
+                if (cur >= 0) flush(&out[cur]);
+                cur = -1;
+#pragma unroll
+                for (int k = 0; k < kInPer; k++) {
+                    const int64_t r = r0 + srow[k * kBlock + tid];
+                    const bool in = j[k] >= 0 && memb[r] == cj[k];
+                    const double v = in ? edge_weight<WT>(g.w, e0 + k * kBlock + tid) : 0.0;
+                    wave_add_f64_by_key(out, g.gid[r], v, in);
+                }
+                __syncthreads();   // srow is rewritten by the next tile
+                continue;
+            }
+            if (ga != cur) {
+                if (cur >= 0) flush(&out[cur]);
+                cur = ga;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kInPer; k++) {
+            const bool in = j[k] >= 0 && memb[r0 + srow[k * kBlock + tid]] == cj[k];
+            if (in) s += edge_weight<WT>(g.w, e0 + k * kBlock + tid);
+        }
+        __syncthreads();   // srow is rewritten by the next tile
     }
-    if (lane == 0) part[w] = blk;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int k = 0; k < kBlock / kWave; k++) t += part[k];
-        unsafeAtomicAdd(sigma_in, t);
-    }
+    if (!BATCH)
+        flush(out);
+    else if (cur >= 0)
+        flush(&out[cur]);
 }
 
 // *out += sum_c (Sigma_c / M2)^2 in fixed point: each term rounded to the
@@ -453,16 +565,17 @@ void launch_vertex_weights(const Level &g, double *K, double *M2, hipStream_t s)
         k_vertex_weights<W_F64><<<gr, kBlock, 0, s>>>(g, K, M2);
 }
 
-void launch_modularity_parts(const Level &g, const int32_t *memb, const double *K, double *sig, double *sigma_in,
-                             hipStream_t s) {
-    if (g.n == 0) return;
-    unsigned gr = grid_for(g.n, kBlock / kWave, 65536);
-    if (g.wt == W_UNIT)
-        k_modularity_parts<W_UNIT><<<gr, kBlock, 0, s>>>(g, memb, K, sig, sigma_in);
-    else if (g.wt == W_F32)
-        k_modularity_parts<W_F32><<<gr, kBlock, 0, s>>>(g, memb, K, sig, sigma_in);
+void launch_inside_weight(const Level &g, const int32_t *memb, double *out, hipStream_t s) {
+    if (g.n == 0 || g.nnz == 0) return;
+    const int64_t tiles = (g.nnz + kInTile - 1) / kInTile;
+    const unsigned gr = grid_for(tiles, 1, 2048);   // eight workgroups per CU
+    auto go = [&](auto kernel) { kernel<<<gr, kBlock, 0, s>>>(g, memb, tiles, out); };
+    if (g.gid)
+        g.wt == W_UNIT ? go(k_inside_weight<W_UNIT, true>)
+                       : g.wt == W_F32 ? go(k_inside_weight<W_F32, true>) : go(k_inside_weight<W_F64, true>);
     else
-        k_modularity_parts<W_F64><<<gr, kBlock, 0, s>>>(g, memb, K, sig, sigma_in);
+        g.wt == W_UNIT ? go(k_inside_weight<W_UNIT, false>)
+                       : g.wt == W_F32 ? go(k_inside_weight<W_F32, false>) : go(k_inside_weight<W_F64, false>);
 }
 
 void launch_sum_squares(const double *sig, int64_t n, double M2, unsigned long long *out, hipStream_t s) {

@@ -1,0 +1,106 @@
+"""Kernels that cut a level into tiles, at the sizes where a tile can go
+wrong (GPU, through the C ABI): graphs of exactly a tile of entries, one
+less and one more, rows longer than a tile, runs of empty rows, many graphs
+in one tile; against numpy or the oracle.  All sums here are exact (unit or
+dyadic weights), so the tolerance on modularity is that of its last two
+divisions and the fixed-point sum: 1e-12.
+"""
+import numpy as np
+import pytest
+
+import gsp_inputs as gi
+import oracle
+import paper_2402_11454_amd as gsp
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    try:
+        import torch
+        count = torch.cuda.device_count()
+    except Exception:
+        count = 0
+    if count == 0:
+        pytest.skip("no GPU")
+    c = gsp.Context(0)
+    yield c
+    c.close()
+
+
+def _csr(n, u, v, weighted, seed):
+    """Symmetric CSR of the pairs (u, v), u != v, with dyadic weights."""
+    key = np.unique(np.concatenate([u * n + v, v * n + u]))
+    row, col = key // n, key % n
+    off = np.searchsorted(row, np.arange(n + 1)).astype(np.int64)
+    w = None
+    if weighted:
+        a = np.minimum(row, col) * 7919 + np.maximum(row, col) * 104729 + seed
+        w = (1.0 + (a % 31) / 8.0).astype(np.float32)
+    return gi.Graph(n=n, offsets=off, cols=col.astype(np.int32), weights=w)
+
+
+def _path(entries, n, weighted, seed=1):
+    """A path with `entries` directed entries (even), its vertices spread
+    over n ids so that runs of empty rows lie between them."""
+    k = entries // 2 + 1
+    at = np.sort(np.random.default_rng(seed).choice(n, k, replace=False)).astype(np.int64)
+    return _csr(n, at[:-1], at[1:], weighted, seed)
+
+
+def _star(leaves, n, weighted, hub=3):
+    v = np.setdiff1d(np.arange(leaves + 1, dtype=np.int64) + (n - leaves - 1), [hub])
+    return _csr(n, np.full(v.shape, hub, np.int64), v, weighted, 5)
+
+
+def _modularity(g, memb):
+    w = g.weights_f64()
+    row = np.repeat(np.arange(g.n), np.diff(g.offsets))
+    m2 = w.sum()
+    if m2 == 0:
+        return 0.0
+    tot = np.bincount(memb[row], weights=w, minlength=g.n)
+    return float(w[memb[row] == memb[g.cols]].sum() / m2 - ((tot / m2) ** 2).sum())
+
+
+TILE = 4096
+CASES = {
+    "tile-2": lambda w: _path(TILE - 2, 60000, w),
+    "tile": lambda w: _path(TILE, 60000, w),
+    "tile+2": lambda w: _path(TILE + 2, 60000, w),
+    "two": lambda w: _path(2, 70000, w),
+    "dense-path": lambda w: _path(3 * TILE, 3 * TILE // 2 + 1, w),
+    "star": lambda w: _star(3 * TILE + 7, 90000, w),
+    "rmat13": lambda w: gi.rmat_small(13, 5, weights=(1.0, 4.0) if w else None),
+}
+
+
+@pytest.mark.parametrize("order", [gsp.ORDER_LOADED, gsp.ORDER_DEGREE])
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("name", list(CASES))
+def test_modularity_at_the_tiles_edges(ctx, name, weighted, order):
+    g = CASES[name](weighted)
+    ctx.load_graph(g)
+    if order == gsp.ORDER_DEGREE:
+        ctx.run(1e-2, 1, vertex_order=order)   # builds the copy the evaluation then reads
+    for ncomm in (1, 2, 37, g.n):
+        m = gi.random_membership(g.n, ncomm, 11 + ncomm)
+        assert abs(ctx.modularity(m) - _modularity(g, m)) <= 1e-12
+        assert ctx.count_disconnected(m) == oracle.disconnected(g, m)[0]
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+def test_batch_modularity_with_many_graphs_in_a_tile(ctx, weighted):
+    """Graphs of 2 to 4,098 entries side by side: several per tile, a tile
+    that ends with a graph, a graph that spans tiles, graphs without entries."""
+    gs = []
+    for k, entries in enumerate([2, 40, 0, 4054, 4096, 0, 0, 6, 4098, 100, 8200, 2]):
+        gs.append(_path(entries, 4200 + 13 * k, weighted, seed=k) if entries else
+                  gi.Graph(n=5, offsets=np.zeros(6, np.int64), cols=np.zeros(0, np.int32),
+                           weights=np.zeros(0, np.float32) if weighted else None))
+    ctx.load_batch(gs)
+    ctx.run_batch(1e-2, 10)
+    q = ctx.batch_modularity()
+    for k, g in enumerate(gs):
+        assert abs(q[k] - _modularity(g, ctx.batch_membership(k))) <= 1e-12
