@@ -571,6 +571,9 @@ gsp_status move_phase(gsp_ctx *ctx, const Level &g, const double *K, const WorkL
             launch_fill_u64(ctx->ggain, 0, G, cs);
             launch_fill_u64(ctx->gmoved, 0, G, cs);
         }
+        // the sub-rounds with vertices
+        std::vector<MoveArgs> subs;
+        bool hubs = false;
         for (int p = 0; p < P; p++) {
             MoveArgs a;
             a.g = g;
@@ -642,29 +645,43 @@ gsp_status move_phase(gsp_ctx *ctx, const Level &g, const double *K, const WorkL
                 }
             }
             if (cap == 0) continue;
+            hubs = hubs || a.qcap[BIN_HUB] > 0;
+            subs.push_back(a);
+        }
+        // apply of one sub-round and compaction of the next in one launch
+        // (see launch_move_apply_compact)
+        const bool fuse = !hubs && !cfg.single_only && !cfg.timing_k;
+        for (size_t k = 0; k < subs.size(); k++) {
+            const MoveArgs &a = subs[k];
+            const int p = a.round;
+            int64_t cap = 0;
+            for (int b = 0; b < kNumBins; b++) cap += a.qcap[b];
             const bool tk = cfg.timing_k && cs == s;
             int t;
             t = tk ? ctx->timer.begin(100 + GSP_K_FRONTIER, cs) : -1;
-            launch_move_compact(a, wl, cs);
+            if (!fuse || k == 0) launch_move_compact(a, wl, cs);
             ctx->timer.end(t);
             if (mode == GATED) {
                 t = tk ? ctx->timer.begin(100 + GSP_K_GATE, cs) : -1;
                 launch_gate(a, net, cfg.theta_logit, cap, cs);
                 ctx->timer.end(t);
             }
-            // the four scans read the same state and write disjoint
-            // decisions: the wave-bin, workgroup-bin and hub scans fork onto
-            // side streams and join before the moves are applied.  Timed
-            // sweeps stay on one stream (timing = 2), so that an event pair
-            // around a kernel holds that kernel alone, or keep the side
-            // streams (timing = 3): each pair is then on its kernel's own
-            // stream and times it as it runs beside the others.
-            const bool fork = !cfg.timing_k || cfg.timing_side;
+            // the scans read the same state and write disjoint decisions.
+            // The small, wave and workgroup bins go in one launch; the hubs'
+            // chain runs beside it on a side stream and joins before the
+            // moves are applied.  Timed sweeps launch every scan by itself:
+            // on one stream (timing = 2), so that an event pair around a
+            // kernel holds that kernel alone, or on four (timing = 3), each
+            // pair on its kernel's own stream, which times it as it runs
+            // beside the others.
+            const bool merged = !cfg.timing_k;
+            const bool fork = merged ? a.qcap[BIN_HUB] > 0 : cfg.timing_side;
             hipStream_t sw = fork ? ctx->side[0] : cs, sb = fork ? ctx->side[1] : cs, sh = fork ? ctx->side[2] : cs;
+            const int q0 = merged ? 2 : 0;   // the first side stream in use
             if (fork) {
                 hipEvent_t fe = ctx->fork_ev[p];
                 (void)hipEventRecord(fe, cs);
-                for (hipStream_t q : ctx->side) (void)hipStreamWaitEvent(q, fe, 0);
+                for (int q = q0; q < 3; q++) (void)hipStreamWaitEvent(ctx->side[q], fe, 0);
             }
             // hubs first: their chain of three kernels is the longest path of
             // the sub-round, and enqueued first it gets the compute units
@@ -683,22 +700,29 @@ gsp_status move_phase(gsp_ctx *ctx, const Level &g, const double *K, const WorkL
             t = tk && a.qcap[BIN_HUB] ? ctx->timer.begin(100 + GSP_K_MOVE_HUB_FINISH, sh) : -1;
             if (a.hub_parts) launch_move_hub_decide(a, sh); else launch_move_hub_finish(a, sh);
             ctx->timer.end(t);
-            t = tk ? ctx->timer.begin(100 + GSP_K_MOVE_SMALL, cs) : -1;
-            launch_move_small(a, wl, cs);
-            ctx->timer.end(t);
-            t = tk && a.qcap[BIN_WAVE] ? ctx->timer.begin(100 + GSP_K_MOVE_WAVE, sw) : -1;
-            launch_move_wave(a, sw);
-            ctx->timer.end(t);
-            t = tk && a.qcap[BIN_BLOCK] ? ctx->timer.begin(100 + GSP_K_MOVE_BLOCK, sb) : -1;
-            launch_move_block(a, sb);
-            ctx->timer.end(t);
-            for (int q = 0; fork && q < 3; q++) {
+            if (merged) {
+                launch_move_scan(a, cs);
+            } else {
+                t = tk ? ctx->timer.begin(100 + GSP_K_MOVE_SMALL, cs) : -1;
+                launch_move_small(a, wl, cs);
+                ctx->timer.end(t);
+                t = tk && a.qcap[BIN_WAVE] ? ctx->timer.begin(100 + GSP_K_MOVE_WAVE, sw) : -1;
+                launch_move_wave(a, sw);
+                ctx->timer.end(t);
+                t = tk && a.qcap[BIN_BLOCK] ? ctx->timer.begin(100 + GSP_K_MOVE_BLOCK, sb) : -1;
+                launch_move_block(a, sb);
+                ctx->timer.end(t);
+            }
+            for (int q = q0; fork && q < 3; q++) {
                 hipEvent_t je = ctx->join_ev[3 * p + q];
                 (void)hipEventRecord(je, ctx->side[q]);
                 (void)hipStreamWaitEvent(cs, je, 0);
             }
             t = tk ? ctx->timer.begin(100 + GSP_K_MOVE_APPLY, cs) : -1;
-            launch_move_apply(a, cap, cs);
+            if (fuse && k + 1 < subs.size())
+                launch_move_apply_compact(a, subs[k + 1], wl, cs);
+            else
+                launch_move_apply(a, cap, cs);
             ctx->timer.end(t);
             if (tk) {
                 launches[GSP_K_FRONTIER]++;

@@ -281,6 +281,8 @@ void launch_move_compact(const MoveArgs &a, const WorkLists &wl, hipStream_t s);
 void launch_move_small(const MoveArgs &a, const WorkLists &wl, hipStream_t s);
 void launch_move_wave(const MoveArgs &a, hipStream_t s);
 void launch_move_block(const MoveArgs &a, hipStream_t s);
+// The small, wave and workgroup scans in one launch.
+void launch_move_scan(const MoveArgs &a, hipStream_t s);
 void launch_move_hub_scan(const MoveArgs &a, hipStream_t s);
 void launch_move_hub_finish(const MoveArgs &a, hipStream_t s);
 // Hubs by hash partitions: chunk -> LDS reduction -> pairs sorted by
@@ -294,6 +296,9 @@ void launch_move_hub_parts(const MoveArgs &a, hipStream_t s);    // phase 1: chu
 void launch_move_hub_gather(const MoveArgs &a, hipStream_t s);   // phase 2: partitions merged and scored
 void launch_move_hub_decide(const MoveArgs &a, hipStream_t s);   // phase 3: a workgroup per hub decides
 void launch_move_apply(const MoveArgs &a, int64_t cap, hipStream_t s);
+// Apply of sub-round a and compaction of sub-round next (both with vertices;
+// levels without hubs, not with single_only: it reads sizes apply changes).
+void launch_move_apply_compact(const MoveArgs &a, const MoveArgs &next, const WorkLists &wl, hipStream_t s);
 
 // ---- k_leiden.hip ----
 // The same-bound subgraph of a level for GSP-Leiden's refinement: row i

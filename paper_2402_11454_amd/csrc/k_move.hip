@@ -269,18 +269,21 @@ __device__ __forceinline__ void fold_table(const MoveArgs &a, double m2, int *ke
 constexpr int kCompactSpan = 4096;   // entries of the buckets per compaction workgroup, at most
 
 // Unprocessed vertices of the sub-round's buckets -> per-bin queues (or,
-// in a gated sweep, per-bin candidate lists for the gate).  Workgroup k
-// takes the contiguous range [k span, (k + 1) span) of the buckets (span <=
+// in a gated sweep, per-bin candidate lists for the gate).  A workgroup
+// takes the contiguous range [part span, (part + 1) span) of the buckets (span <=
 // kCompactSpan), stages its active vertices in LDS with their rank in their
 // bin, reserves their queue slots with one atomic per bin, then writes them.
 // The queue counters are shared by every workgroup, so their atomics, not
 // the reads, bound this kernel on large levels: one per bin per workgroup
 // (not per 256 entries) keeps them few.
-__global__ void __launch_bounds__(kBlock) k_move_compact(MoveArgs a, const int32_t *bl, int64_t span) {
+struct CompactLds {
+    int32_t sv[kCompactSpan];     // staged vertex
+    uint32_t sbr[kCompactSpan];   // its bin (top 4 bits) and rank in the bin
+};
+
+__device__ void compact_range(const MoveArgs &a, const int32_t *bl, int64_t span, int64_t part, CompactLds &l) {
     __shared__ int lcnt[kNumBins];
     __shared__ int lbase[kNumBins];
-    __shared__ int32_t sv[kCompactSpan];      // staged vertex
-    __shared__ uint32_t sbr[kCompactSpan];    // its bin (top 4 bits) and rank in the bin
     int64_t pre[kNumBins + 1];
     pre[0] = 0;
 #pragma unroll
@@ -289,7 +292,7 @@ __global__ void __launch_bounds__(kBlock) k_move_compact(MoveArgs a, const int32
     const bool gated = a.cand != nullptr;   // the gate fills the queue from the candidates
     int *qcnt = gated ? a.ctr->ccnt[a.round] : a.ctr->qcnt[a.round];
     int32_t *qout = gated ? a.cand : a.queue;
-    const int64_t lo = blockIdx.x * span;
+    const int64_t lo = part * span;
     const int64_t hi = lo + span < total ? lo + span : total;
     if (threadIdx.x < kNumBins) lcnt[threadIdx.x] = 0;
     __shared__ int nst;
@@ -310,8 +313,8 @@ __global__ void __launch_bounds__(kBlock) k_move_compact(MoveArgs a, const int32
             if (a.dmoved) a.dsnap[i] = a.dmoved[i];   // the features' D_i
             const int rank = atomicAdd(&lcnt[b], 1);
             const int slot = atomicAdd(&nst, 1);
-            sv[slot] = i;
-            sbr[slot] = ((uint32_t)b << 28) | (uint32_t)rank;
+            l.sv[slot] = i;
+            l.sbr[slot] = ((uint32_t)b << 28) | (uint32_t)rank;
         }
     }
     __syncthreads();
@@ -319,10 +322,15 @@ __global__ void __launch_bounds__(kBlock) k_move_compact(MoveArgs a, const int32
         lbase[threadIdx.x] = atomicAdd(&qcnt[threadIdx.x], lcnt[threadIdx.x]);
     __syncthreads();
     for (int k = threadIdx.x; k < nst; k += kBlock) {
-        const uint32_t br = sbr[k];
+        const uint32_t br = l.sbr[k];
         const int b = (int)(br >> 28);
-        qout[a.qbase[b] + lbase[b] + (int64_t)(br & 0x0FFFFFFFu)] = sv[k];
+        qout[a.qbase[b] + lbase[b] + (int64_t)(br & 0x0FFFFFFFu)] = l.sv[k];
     }
+}
+
+__global__ void __launch_bounds__(kBlock) k_move_compact(MoveArgs a, const int32_t *bl, int64_t span) {
+    __shared__ CompactLds l;
+    compact_range(a, bl, span, blockIdx.x, l);
 }
 
 // ---------------------------------------------------------------- small
@@ -443,11 +451,17 @@ __device__ void small_unit(const MoveArgs &a, int bin, int G, int64_t unit, int 
 // vertices of small bin b per wavefront
 __host__ __device__ inline int small_vpw(int b) { return kWave / small_lanes(4 << b); }
 
+constexpr int kWaveSlots = 2 * kWave * kSmallE;   // (64 / L) vertices x 2G slots, at most
+struct SmallLds {
+    double vals[kWaveSlots * (kBlock / kWave)];
+    int keys[kWaveSlots * (kBlock / kWave)];
+};
+
+// The small bins' share of workgroup `part` of `parts`.
 template <int WT>
-__global__ void __launch_bounds__(kBlock, WT == W_UNIT ? 5 : 4) k_move_small(MoveArgs a) {
-    constexpr int kWaveSlots = 2 * kWave * kSmallE;   // (64 / L) vertices x 2G slots, at most
-    __shared__ int tkeys[kWaveSlots * (kBlock / kWave)];
-    __shared__ double tvals[kWaveSlots * (kBlock / kWave)];
+__device__ __forceinline__ void scan_small(const MoveArgs &a, SmallLds &lds, int part, int parts) {
+    int *tkeys = lds.keys;
+    double *tvals = lds.vals;
     const int w = threadIdx.x / kWave;
     int *wkeys = tkeys + w * kWaveSlots;
     double *wvals = tvals + w * kWaveSlots;
@@ -466,13 +480,19 @@ __global__ void __launch_bounds__(kBlock, WT == W_UNIT ? 5 : 4) k_move_small(Mov
         pre[b + 1] = pre[b] + (cnt[b] + vpw - 1) / vpw;
     }
     Acc acc;
-    const int64_t nw = (int64_t)gridDim.x * (kBlock / kWave);
-    for (int64_t u = (int64_t)blockIdx.x * (kBlock / kWave) + w; u < pre[kNumSmallBins]; u += nw) {
+    const int64_t nw = (int64_t)parts * (kBlock / kWave);
+    for (int64_t u = (int64_t)part * (kBlock / kWave) + w; u < pre[kNumSmallBins]; u += nw) {
         int b = 0;
         while (u >= pre[b + 1]) b++;
         small_unit<WT>(a, b, 4 << b, u - pre[b], cnt[b], wkeys, wvals, acc);
     }
     flush_acc(acc, a.ctr, 0);
+}
+
+template <int WT>
+__global__ void __launch_bounds__(kBlock, WT == W_UNIT ? 5 : 4) k_move_small(MoveArgs a) {
+    __shared__ SmallLds lds;
+    scan_small<WT>(a, lds, blockIdx.x, gridDim.x);
 }
 
 // ---------------------------------------------------------------- large
@@ -548,25 +568,35 @@ __device__ __forceinline__ void scan_put(int *keys, V *vals, int T, int key, dou
         block_put(keys, vals, (uint32_t)T, key, w);
 }
 
-// One wavefront per vertex of 65..512 entries, table in its LDS.
+template <int WT> struct WaveLds {
+    static constexpr int S = ScanSlots<WT>::wave;
+    typename TabVal<WT>::T vals[kBlock / kWave * S];
+    int keys[kBlock / kWave * S];
+};
+template <int WT> struct BlockLds {
+    static constexpr int S = ScanSlots<WT>::block;
+    typename TabVal<WT>::T vals[S];
+    int keys[S];
+};
+
+// One wavefront per vertex of 65..512 entries, table in its LDS: workgroup
+// `part` of `parts`.
 template <int WT>
-__global__ void __launch_bounds__(kBlock, 4) k_move_wave(MoveArgs a) {
+__device__ __forceinline__ void scan_wave(const MoveArgs &a, WaveLds<WT> &lds, int part, int parts) {
     using V = typename TabVal<WT>::T;
-    constexpr int S = ScanSlots<WT>::wave;
-    __shared__ int tkeys[kBlock / kWave * S];
-    __shared__ V tvals[kBlock / kWave * S];
+    constexpr int S = WaveLds<WT>::S;
     const int w = threadIdx.x / kWave, lane = lane_id();
-    int *keys = tkeys + w * S;
-    V *vals = tvals + w * S;
+    int *keys = lds.keys + w * S;
+    V *vals = lds.vals + w * S;
     for (int k = lane; k < S; k += kWave) {
         keys[k] = kEmpty;
         vals[k] = 0;
     }
     wave_lds_sync();
     const int cnt = a.ctr->qcnt[a.round][BIN_WAVE];
-    const int64_t nw = (int64_t)gridDim.x * (kBlock / kWave);
+    const int64_t nw = (int64_t)parts * (kBlock / kWave);
     Acc acc;
-    for (int64_t qi = (int64_t)blockIdx.x * (kBlock / kWave) + w; qi < cnt; qi += nw) {
+    for (int64_t qi = (int64_t)part * (kBlock / kWave) + w; qi < cnt; qi += nw) {
         int i = a.queue[a.qbase[BIN_WAVE] + qi];
         const double m2 = m2_of(a, i);
         int di = a.g.deg[i];
@@ -623,13 +653,20 @@ __global__ void __launch_bounds__(kBlock, 4) k_move_wave(MoveArgs a) {
     flush_acc(acc, a.ctr, 1);
 }
 
-// One workgroup per vertex of 513..2048 entries, table in LDS.
 template <int WT>
-__global__ void __launch_bounds__(kBlock, 4) k_move_block(MoveArgs a) {
+__global__ void __launch_bounds__(kBlock, 4) k_move_wave(MoveArgs a) {
+    __shared__ WaveLds<WT> lds;
+    scan_wave<WT>(a, lds, blockIdx.x, gridDim.x);
+}
+
+// One workgroup per vertex of 513..2048 entries, table in LDS: workgroup
+// `part` of `parts`.
+template <int WT>
+__device__ __forceinline__ void scan_block(const MoveArgs &a, BlockLds<WT> &lds, int part, int parts) {
     using V = typename TabVal<WT>::T;
-    constexpr int S = ScanSlots<WT>::block;
-    __shared__ int keys[S];
-    __shared__ V vals[S];
+    constexpr int S = BlockLds<WT>::S;
+    int *keys = lds.keys;
+    V *vals = lds.vals;
     const int tid = threadIdx.x;
     for (int k = tid; k < S; k += kBlock) {
         keys[k] = kEmpty;
@@ -638,7 +675,7 @@ __global__ void __launch_bounds__(kBlock, 4) k_move_block(MoveArgs a) {
     __syncthreads();
     const int cnt = a.ctr->qcnt[a.round][BIN_BLOCK];
     Acc acc;
-    for (int64_t qi = blockIdx.x; qi < cnt; qi += gridDim.x) {
+    for (int64_t qi = part; qi < cnt; qi += parts) {
         int i = a.queue[a.qbase[BIN_BLOCK] + qi];
         const double m2 = m2_of(a, i);
         int di = a.g.deg[i];
@@ -690,6 +727,37 @@ __global__ void __launch_bounds__(kBlock, 4) k_move_block(MoveArgs a) {
         __syncthreads();
     }
     flush_acc(acc, a.ctr, 2);
+}
+
+template <int WT>
+__global__ void __launch_bounds__(kBlock, 4) k_move_block(MoveArgs a) {
+    __shared__ BlockLds<WT> lds;
+    scan_block<WT>(a, lds, blockIdx.x, gridDim.x);
+}
+
+// The three scans above in one launch: workgroups [0, nb) take the workgroup
+// bin, [nb, nb + nw) the wave bin, the others the small bins.  One launch
+// after the compaction instead of three on forked streams: a fork and its
+// join cost two dependency points of about 10 us, and the three scans of a
+// level without hubs then follow the compaction with no gap (batch of 64
+// graphs, levels of 12k-177k super-vertices: 52 -> 22 us per sub-round
+// together with the fused apply and compaction below).
+template <int WT> union ScanLds {
+    SmallLds small;
+    WaveLds<WT> wave;
+    BlockLds<WT> block;
+};
+
+template <int WT>
+__global__ void __launch_bounds__(kBlock, 4) k_move_scan(MoveArgs a, int nb, int nw) {
+    __shared__ ScanLds<WT> lds;
+    const int k = blockIdx.x;
+    if (k < nb)
+        scan_block<WT>(a, lds.block, k, nb);
+    else if (k < nb + nw)
+        scan_wave<WT>(a, lds.wave, k - nb, nw);
+    else
+        scan_small<WT>(a, lds.small, k - nb - nw, gridDim.x - nb - nw);
 }
 
 // ---------------------------------------------------------------- hubs
@@ -1164,13 +1232,16 @@ __global__ void __launch_bounds__(kBlock) k_move_hub_final(MoveArgs a) {
 // take the sub-round's hub chunks and mark the chunk's neighbours of a hub
 // that moved.
 constexpr int kApplyTable = 4 * kBlock;
+struct ApplyLds {
+    double tv[kApplyTable];
+    int tk[kApplyTable], tc[kApplyTable];
+};
 
-__global__ void __launch_bounds__(kBlock) k_move_apply(MoveArgs a, int nq) {
-    __shared__ int tk[kApplyTable];
-    __shared__ double tv[kApplyTable];
-    __shared__ int tc[kApplyTable];
+__device__ __forceinline__ void apply_moves(const MoveArgs &a, int nq, int nh, ApplyLds &lds) {
+    int *tk = lds.tk, *tc = lds.tc;
+    double *tv = lds.tv;
     if ((int)blockIdx.x >= nq) {
-        for (int64_t k = a.ch_first + (blockIdx.x - nq); k < a.ch_first + a.ch_count; k += gridDim.x - nq) {
+        for (int64_t k = a.ch_first + (blockIdx.x - nq); k < a.ch_first + a.ch_count; k += nh) {
             int i = a.ch_vert[k];
             if (a.hub_act[i] != 2) continue;
             int64_t beg = a.ch_beg[k];
@@ -1234,6 +1305,29 @@ __global__ void __launch_bounds__(kBlock) k_move_apply(MoveArgs a, int nq) {
         }
         __syncthreads();
     }
+}
+
+__global__ void __launch_bounds__(kBlock) k_move_apply(MoveArgs a, int nq) {
+    __shared__ ApplyLds lds;
+    apply_moves(a, nq, gridDim.x - nq, lds);
+}
+
+// Apply of one sub-round and, in workgroups [nq, ...), the compaction of the
+// next (`next`): on a level without hubs every mover's neighbours are marked
+// by the scans, so the next sub-round's frontier is final when they end, and
+// neither half reads what the other writes (apply: memberships, Sigma,
+// sizes; compaction: flags, queues).  One dependent launch fewer per
+// sub-round.
+__global__ void __launch_bounds__(kBlock) k_move_apply_compact(MoveArgs a, int nq, MoveArgs next, const int32_t *bl,
+                                                              int64_t span) {
+    __shared__ union {
+        ApplyLds apply;
+        CompactLds compact;
+    } lds;
+    if ((int)blockIdx.x < nq)
+        apply_moves(a, nq, 0, lds.apply);
+    else
+        compact_range(next, bl, span, blockIdx.x - nq, lds.compact);
 }
 
 // sig[c] += K_i and csize[c] += 1 over the vertices i of community c.  A
@@ -1309,28 +1403,44 @@ void launch_community_totals(const double *K, const int32_t *cm, int64_t n, doub
         k_community_totals<false><<<gr, kBlock, 0, s>>>(K, cm, n, sig, nullptr);
 }
 
-void launch_move_compact(const MoveArgs &a, const WorkLists &wl, hipStream_t s) {
-    int64_t total = 0;
-    for (int b = 0; b < kNumBins; b++) total += a.qcap[b];
-    if (total == 0) return;
-    // one pass of 256 entries per workgroup while that gives at most 1024
-    // workgroups, then longer ranges (at most kCompactSpan entries)
+// Workgroups of a compaction of `total` bucket entries and the entries each
+// takes: one pass of 256 per workgroup while that gives at most 1024
+// workgroups, then longer ranges (at most kCompactSpan entries).
+static int64_t compact_blocks(int64_t total, int64_t *span) {
     int64_t blocks = (total + kBlock - 1) / kBlock;
     if (blocks > 1024) blocks = 1024;
     if (blocks < (total + kCompactSpan - 1) / kCompactSpan) blocks = (total + kCompactSpan - 1) / kCompactSpan;
-    int64_t span = (total + blocks - 1) / blocks;
-    span = (span + kBlock - 1) / kBlock * kBlock;
-    blocks = (total + span - 1) / span;
+    *span = ((total + blocks - 1) / blocks + kBlock - 1) / kBlock * kBlock;
+    return (total + *span - 1) / *span;
+}
+
+static int64_t bucket_total(const MoveArgs &a) {
+    int64_t total = 0;
+    for (int b = 0; b < kNumBins; b++) total += a.qcap[b];
+    return total;
+}
+
+void launch_move_compact(const MoveArgs &a, const WorkLists &wl, hipStream_t s) {
+    const int64_t total = bucket_total(a);
+    if (total == 0) return;
+    int64_t span = 0;
+    const int64_t blocks = compact_blocks(total, &span);
     k_move_compact<<<(unsigned)blocks, kBlock, 0, s>>>(a, wl.bl, span);
 }
 
-void launch_move_small(const MoveArgs &a, const WorkLists &wl, hipStream_t s) {
-    (void)wl;
-    int64_t units = 0;   // wave units
+// wave units of the small bins, at most
+static int64_t small_units(const MoveArgs &a) {
+    int64_t units = 0;
     for (int b = 0; b < kNumSmallBins; b++) {
         int vpw = small_vpw(b);
         units += (a.qcap[b] + vpw - 1) / vpw;
     }
+    return units;
+}
+
+void launch_move_small(const MoveArgs &a, const WorkLists &wl, hipStream_t s) {
+    (void)wl;
+    const int64_t units = small_units(a);
     if (units == 0) return;
     unsigned gr = cap_grid((units + 3) / 4, sched_cap(a, 8192));
     if (a.g.wt == W_UNIT)
@@ -1361,6 +1471,21 @@ void launch_move_block(const MoveArgs &a, hipStream_t s) {
         k_move_block<W_F32><<<gr, kBlock, 0, s>>>(a);
     else
         k_move_block<W_F64><<<gr, kBlock, 0, s>>>(a);
+}
+
+void launch_move_scan(const MoveArgs &a, hipStream_t s) {
+    const int nb = a.qcap[BIN_BLOCK] ? (int)cap_grid(a.qcap[BIN_BLOCK], sched_cap(a, 2048)) : 0;
+    const int nw = a.qcap[BIN_WAVE] ? (int)cap_grid((a.qcap[BIN_WAVE] + 3) / 4, sched_cap(a, 4096)) : 0;
+    const int64_t units = small_units(a);
+    const int ns = units ? (int)cap_grid((units + 3) / 4, sched_cap(a, 8192)) : 0;
+    const int gr = nb + nw + ns;
+    if (gr == 0) return;
+    if (a.g.wt == W_UNIT)
+        k_move_scan<W_UNIT><<<gr, kBlock, 0, s>>>(a, nb, nw);
+    else if (a.g.wt == W_F32)
+        k_move_scan<W_F32><<<gr, kBlock, 0, s>>>(a, nb, nw);
+    else
+        k_move_scan<W_F64><<<gr, kBlock, 0, s>>>(a, nb, nw);
 }
 
 void launch_move_hub_scan(const MoveArgs &a, hipStream_t s) {
@@ -1416,6 +1541,13 @@ void launch_move_apply(const MoveArgs &a, int64_t cap, hipStream_t s) {
     int nq = (int)cap_grid((cap + kBlock - 1) / kBlock, sched_cap(a, 2048));
     int nh = a.qcap[BIN_HUB] ? (int)cap_grid(a.ch_count, sched_cap(a, 2048)) : 0;
     k_move_apply<<<nq + nh, kBlock, 0, s>>>(a, nq);
+}
+
+void launch_move_apply_compact(const MoveArgs &a, const MoveArgs &next, const WorkLists &wl, hipStream_t s) {
+    const int nq = (int)cap_grid((bucket_total(a) + kBlock - 1) / kBlock, sched_cap(a, 2048));
+    int64_t span = 0;
+    const int64_t blocks = compact_blocks(bucket_total(next), &span);
+    k_move_apply_compact<<<(unsigned)(nq + blocks), kBlock, 0, s>>>(a, nq, next, wl.bl, span);
 }
 
 }  // namespace gsp

@@ -104,3 +104,42 @@ def test_batch_modularity_with_many_graphs_in_a_tile(ctx, weighted):
     q = ctx.batch_modularity()
     for k, g in enumerate(gs):
         assert abs(q[k] - _modularity(g, ctx.batch_membership(k))) <= 1e-12
+
+
+def _same_run(ctx, g, **kw):
+    """A whole run equal to the oracle's: membership, passes, iterations,
+    communities."""
+    opt = dict(kw)
+    rounds, returns = opt.get("sub_rounds", 8), bool(opt.get("return_moves", 0))
+    ref = oracle.louvain(g, 1e-2, 10, sync=True, rounds=rounds, return_moves=returns)
+    res = ctx.louvain(1e-2, 10, **opt)
+    assert np.array_equal(res.membership, ref.membership)
+    assert res.stats["passes"] == ref.passes
+    assert res.stats["iterations"] == list(ref.iterations)
+    assert res.stats["communities"] == list(ref.communities)
+    assert res.stats["vertices"] == list(ref.vertices)
+    # the counters, and the launch-by-launch run they are compared with
+    slow = ctx.louvain(1e-2, 10, timing=2, **opt)
+    assert np.array_equal(slow.membership, ref.membership)
+    for key in ("moves", "scanned_entries", "scanned_vertices", "sweeps"):
+        assert res.stats[key] == slow.stats[key]
+    for kernel in ("move_small", "move_wave", "move_block"):
+        assert res.stats["kernels"][kernel]["items"] == slow.stats["kernels"][kernel]["items"]
+    assert abs(res.modularity - ref.modularity) <= 1e-9
+
+
+@pytest.mark.parametrize("use_graphs", [0, 1])
+@pytest.mark.parametrize("sub_rounds", [1, 2, 8, 64])
+@pytest.mark.parametrize("n", [2, 3, 9, 300, 5000])
+def test_sub_rounds_without_hubs(ctx, n, sub_rounds, use_graphs):
+    """Levels without hubs apply one sub-round and compact the next in one
+    launch: sub-rounds with no vertex between others, one sub-round only,
+    more sub-rounds than vertices (the return-move option keeps the level's
+    launches whatever its size)."""
+    r = np.random.default_rng(n)
+    m = 4 * n
+    u, v = r.integers(0, n, m), r.integers(0, n, m)
+    g = _csr(n, u[u != v], v[u != v], True, n)
+    ctx.load_graph(g)
+    for rm in (0, 1):
+        _same_run(ctx, g, sub_rounds=sub_rounds, use_graphs=use_graphs, return_moves=rm)
