@@ -149,6 +149,7 @@ struct gsp_ctx {
     IterCounters *ctr = nullptr;      // device, 2 slots
     IterCounters *ctr_h = nullptr;    // pinned host mirror
     int64_t *i64_h = nullptr;         // pinned host scalars
+    RestOut *rest_h = nullptr;        // pinned: the record of run_rest
     double *f64_h = nullptr;
 
     // learned gate: per-vertex history of the current pass and the gated
@@ -1342,6 +1343,7 @@ gsp_status gsp_create(int device, void *hip_stream, gsp_ctx **out) {
     }
     if (hipHostMalloc((void **)&ctx->ctr_h, sizeof(IterCounters), hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void **)&ctx->i64_h, 16 * sizeof(int64_t), hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc((void **)&ctx->rest_h, sizeof(RestOut), hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void **)&ctx->f64_h, 8 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
         gsp_destroy(ctx);
         return GSP_ENOMEM;
@@ -1360,6 +1362,7 @@ gsp_status gsp_destroy(gsp_ctx *ctx) {
     ctx->persist.clear();
     if (ctx->ctr_h) (void)hipHostFree(ctx->ctr_h);
     if (ctx->i64_h) (void)hipHostFree(ctx->i64_h);
+    if (ctx->rest_h) (void)hipHostFree(ctx->rest_h);
     if (ctx->f64_h) (void)hipHostFree(ctx->f64_h);
     if (ctx->own_stream && ctx->stream) (void)hipStreamDestroy(ctx->stream);
     ctx->drop_sweep_graphs();
@@ -1417,6 +1420,51 @@ gsp_status run_split(gsp_ctx *ctx, const Level &g, const WorkLists &wl, const in
     }
     launch_split(g, wl, cm, labels, ctx->sc.i32c, reinterpret_cast<uint32_t *>(ctx->sc.i32a),
                  reinterpret_cast<unsigned long long *>(ctx->sc.i64a), s);
+    return GSP_OK;
+}
+
+// The rest of a run of at most `left` passes from level g (pass lp, tolerance
+// tau) in one launch; *done = false, and nothing changed, if g does not fit.
+gsp_status run_rest(gsp_ctx *ctx, const Level &g, const double *K, const gsp_options &opt, double tau, int lp,
+                    int left, int next, bool *done) {
+    hipStream_t s = ctx->stream;
+    static_assert(sizeof(RestOut) <= kScratchU64 * sizeof(unsigned long long), "the record fits the counters");
+    RestArgs a;
+    a.g = g;
+    a.K = K;
+    a.M2 = ctx->M2;
+    a.tau = tau;
+    a.tol_drop = opt.tolerance_drop;
+    a.agg_tol = opt.aggregation_tolerance;
+    a.max_iter = opt.max_iterations;
+    for (a.shift = 0; (1 << a.shift) < opt.sub_rounds;) a.shift++;
+    a.passes = left;
+    a.col[0] = ctx->colL[next];
+    a.w[0] = ctx->wL[next];
+    a.col[1] = ctx->gap_col;
+    a.w[1] = ctx->gap_w;
+    a.label = ctx->cm;
+    a.out = reinterpret_cast<RestOut *>(ctx->sc.u64);
+    launch_rest_of_run(a, 1, s);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipMemcpyAsync(ctx->rest_h, a.out, sizeof(RestOut), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    const RestOut &r = *ctx->rest_h;
+    *done = r.status == 0;
+    if (!*done) return GSP_OK;
+    for (int k = 0; k < r.passes && lp + k < GSP_MAX_PASSES_STATS; k++) {
+        ctx->stats.iterations[lp + k] = r.iterations[k];
+        ctx->stats.vertices[lp + k] = r.vertices[k];
+        ctx->stats.communities[lp + k] = r.communities[k];
+    }
+    ctx->stats.moves += (int64_t)r.moved;
+    ctx->stats.scanned_vertices += (int64_t)r.verts;
+    ctx->stats.sweeps += r.sweeps;
+    for (int c = 0; c < 3; c++) {
+        ctx->stats.scanned_entries += (int64_t)r.scanned[c];
+        ctx->stats.kernels[kClassKernel[c]].items += (int64_t)r.scanned[c];
+    }
+    launch_lookup(ctx->top, ctx->n, ctx->cm, s);
     return GSP_OK;
 }
 
@@ -1492,7 +1540,22 @@ gsp_status run_passes(gsp_ctx *ctx, double tolerance, int32_t max_passes, const 
     double tau = tolerance;
     int next = 0;
     int passes = 0;
+    // small levels: the rest of the run in one launch (k_rest.hip), for plain
+    // runs with the default split that ask for no timing and no hub switch.
+    // 2^32 entries: its row starts are 32-bit offsets
+    const bool rest = !batch && !leiden && !tphase && !ctx->tracing && opt.prune_mode == GSP_PRUNE_PLAIN &&
+                      !opt.return_moves && opt.split_mode == GSP_SPLIT_PASS && opt.split_algo == GSP_SPLIT_UF &&
+                      opt.hub_global == 0 && opt.hub_max_parts == 0 && ctx->nnz < (int64_t(1) << 32);
     for (int lp = 0; lp < max_passes; lp++) {
+        if (rest && !g.orig && g.n <= kRestVertices && g.nnz <= kRestEntries) {
+            bool done = false;
+            st = run_rest(ctx, g, K, opt, tau, lp, max_passes - lp, next, &done);
+            if (st != GSP_OK) return st;
+            if (done) {
+                passes = lp + ctx->rest_h->passes;
+                break;
+            }
+        }
         passes = lp + 1;
         int t = tphase ? ctx->timer.begin(PH_OTHER) : -1;
         WorkLists wl = make_lists(ctx);

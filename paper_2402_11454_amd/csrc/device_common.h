@@ -216,6 +216,69 @@ __device__ __forceinline__ long long group_sum_ll(long long x) {
     return x;
 }
 
+// Maximum / minimum over the W lanes of an aligned lane group, every lane
+// gets it; the group's lanes must all be active.  Within a row of 16 lanes
+// the partners come by data-parallel primitives (the neighbour, the other
+// pair, the mirrored half row, the mirrored row: each combines groups that
+// already agree), across rows by the row and half swaps of gfx950: vector
+// instructions throughout, where a shuffle goes through the LDS (an
+// argmax with its sum over 64 lanes: 1230 cycles of shuffles).
+template <int CTRL>
+__device__ __forceinline__ int dpp_i32(int x) {
+    return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xF, 0xF, false);
+}
+constexpr int kDppPair = 0xB1, kDppQuad = 0x4E, kDppHalfRow = 0x141, kDppRow = 0x140;
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double x) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = (uint32_t)dpp_i32<CTRL>((int)(uint32_t)u), hi = (uint32_t)dpp_i32<CTRL>((int)(u >> 32));
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+// x of the other row of a pair (HALF: of the other half of the wavefront)
+// beside x, in some order.
+template <bool HALF>
+__device__ __forceinline__ void swap_rows(uint32_t x, uint32_t &a, uint32_t &b) {
+    const auto r = HALF ? __builtin_amdgcn_permlane32_swap(x, x, false, false)
+                        : __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    a = r[0];
+    b = r[1];
+}
+template <bool HALF>
+__device__ __forceinline__ double max_rows(double x) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    uint32_t la, lb, ha, hb;
+    swap_rows<HALF>((uint32_t)u, la, lb);
+    swap_rows<HALF>((uint32_t)(u >> 32), ha, hb);
+    return fmax(__builtin_bit_cast(double, ((uint64_t)ha << 32) | la),
+                __builtin_bit_cast(double, ((uint64_t)hb << 32) | lb));
+}
+template <bool HALF>
+__device__ __forceinline__ int min_rows(int x) {
+    uint32_t a, b;
+    swap_rows<HALF>((uint32_t)x, a, b);
+    return min((int)a, (int)b);
+}
+template <int W>
+__device__ __forceinline__ double group_max(double x) {
+    if constexpr (W >= 2) x = fmax(x, dpp_f64<kDppPair>(x));
+    if constexpr (W >= 4) x = fmax(x, dpp_f64<kDppQuad>(x));
+    if constexpr (W >= 8) x = fmax(x, dpp_f64<kDppHalfRow>(x));
+    if constexpr (W >= 16) x = fmax(x, dpp_f64<kDppRow>(x));
+    if constexpr (W >= 32) x = max_rows<false>(x);
+    if constexpr (W >= 64) x = max_rows<true>(x);
+    return x;
+}
+template <int W>
+__device__ __forceinline__ int group_min(int x) {
+    if constexpr (W >= 2) x = min(x, dpp_i32<kDppPair>(x));
+    if constexpr (W >= 4) x = min(x, dpp_i32<kDppQuad>(x));
+    if constexpr (W >= 8) x = min(x, dpp_i32<kDppHalfRow>(x));
+    if constexpr (W >= 16) x = min(x, dpp_i32<kDppRow>(x));
+    if constexpr (W >= 32) x = min_rows<false>(x);
+    if constexpr (W >= 64) x = min_rows<true>(x);
+    return x;
+}
+
 // Wave-aggregated atomics keyed by an index: lanes of one wavefront that hit
 // the same element are combined into one atomic (a popular community would
 // otherwise serialise thousands of same-address atomics).  Lanes are taken

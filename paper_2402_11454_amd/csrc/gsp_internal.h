@@ -300,6 +300,36 @@ void launch_move_apply(const MoveArgs &a, int64_t cap, hipStream_t s);
 // levels without hubs, not with single_only: it reads sizes apply changes).
 void launch_move_apply_compact(const MoveArgs &a, const MoveArgs &next, const WorkLists &wl, hipStream_t s);
 
+// ---- k_rest.hip ----
+// The rest of a run on a small level, a workgroup per graph: every remaining
+// pass of the level (or, of a batch, of graphs which[0..graphs)) with plain
+// pruning, the split in every pass and no options beyond those below.
+// label[v] <- the number of v's final community (from 0 within its graph,
+// in ascending order of the smallest vertex).  status 1: the graph does not
+// fit (vertices, entries, a row beyond kBlockMaxDeg entries) or takes
+// more than kRestPasses passes; nothing of the graph has changed then.
+constexpr int kRestVertices = 1536;
+constexpr int kRestEntries = 65535;
+constexpr int kRestPasses = 64;
+struct RestOut {
+    int status, passes, ncomm, sweeps;
+    unsigned long long moved, verts, scanned[3];   // movers; vertices scanned; entries by the scans' classes
+    int iterations[kRestPasses], vertices[kRestPasses], communities[kRestPasses];
+};
+struct RestArgs {
+    Level g;
+    const double *K = nullptr;
+    double M2 = 0.0;
+    const int32_t *which = nullptr;   // batch: the graphs to run
+    double tau = 0.0, tol_drop = 10.0, agg_tol = 0.8;
+    int max_iter = 20, shift = 3, passes = 1;   // passes left, at least 1
+    int32_t *col[2] = {nullptr, nullptr};       // two buffers for the levels to come, indexed
+    double *w[2] = {nullptr, nullptr};          // like g's entries
+    int32_t *label = nullptr;
+    RestOut *out = nullptr;                     // one per graph
+};
+void launch_rest_of_run(const RestArgs &a, int graphs, hipStream_t s);
+
 // ---- k_leiden.hip ----
 // The same-bound subgraph of a level for GSP-Leiden's refinement: row i
 // keeps the entries (i, j) with bound[j] == bound[i], in order.  Writes its

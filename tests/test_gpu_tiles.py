@@ -143,3 +143,81 @@ def test_sub_rounds_without_hubs(ctx, n, sub_rounds, use_graphs):
     ctx.load_graph(g)
     for rm in (0, 1):
         _same_run(ctx, g, sub_rounds=sub_rounds, use_graphs=use_graphs, return_moves=rm)
+
+
+def _dense(n, p, weighted, seed, loops=False):
+    """A random graph with mean degree p n; weights dyadic."""
+    r = np.random.default_rng(seed)
+    m = int(p * n * n / 2)
+    u, v = r.integers(0, n, m), r.integers(0, n, m)
+    g = _csr(n, u[u != v], v[u != v], weighted, seed)
+    return gi.with_self_loops(g, {0: 2.0, n - 1: 1.5, n // 2: 0.25}) if loops else g
+
+
+SMALL = {
+    # the last size that one workgroup takes, and the first that it leaves
+    "n1536": lambda: _dense(1536, 8 / 1536, True, 1),
+    "n1537": lambda: _dense(1537, 8 / 1537, True, 2),
+    "entries": lambda: _dense(1500, 42 / 1500, False, 3),
+    "over": lambda: _dense(1500, 46 / 1500, False, 4),
+    # rows around the classes' ends: 64 / 65, 341 / 342 entries, a star
+    "rows64": lambda: _dense(900, 64 / 900, True, 5, loops=True),
+    "rows341": lambda: gi.sbm(180, 2, 0.97, 0.9, 3, weights=(1.0, 4.0)),
+    "clique": lambda: _dense(255, 3.0, True, 7),
+    "star": lambda: _star(1500, 1530, True),
+    "cliques": lambda: _csr(1400, *[np.array(x) for x in zip(*[(7 * c + i, 7 * c + j) for c in range(200)
+                                                               for i in range(7) for j in range(i)])], True, 8),
+    "path": lambda: _path(2000, 1300, True),
+    "sbm1k": lambda: gi.sbm(1013, 10, 0.09, 0.004, 4),
+    "sbm10k": lambda: gi.planted_sbm_10k(3),
+    "road": lambda: gi.road_small(40, 3),
+    "edgeless": lambda: gi.Graph(n=7, offsets=np.zeros(8, np.int64), cols=np.zeros(0, np.int32)),
+    "loop": lambda: gi.Graph(n=1, offsets=np.array([0, 1]), cols=np.zeros(1, np.int32),
+                             weights=np.array([2.0], np.float32)),
+    "zero-weights": lambda: gi.Graph(n=4, offsets=np.array([0, 2, 4, 6, 8]),
+                                     cols=np.array([1, 2, 0, 3, 0, 3, 1, 2], np.int32),
+                                     weights=np.array([0, 1, 0, 0, 1, 0, 0, 0], np.float32)),
+}
+
+
+@pytest.mark.parametrize("sub_rounds", [1, 8, 64])
+@pytest.mark.parametrize("name", list(SMALL))
+def test_small_levels_in_one_launch(ctx, name, sub_rounds):
+    """Levels that one workgroup takes through the rest of the run: the same
+    run as the oracle's and, with the same counters, as the level-wide
+    kernels'."""
+    g = SMALL[name]()
+    ctx.load_graph(g)
+    _same_run(ctx, g, sub_rounds=sub_rounds)
+
+
+@pytest.mark.parametrize("kw", [dict(max_iterations=0), dict(max_iterations=1), dict(aggregation_tolerance=0.3),
+                                dict(aggregation_tolerance=1.0), dict(tolerance_drop=2.0)])
+@pytest.mark.parametrize("max_passes", [1, 2, 10])
+def test_small_levels_options(ctx, kw, max_passes):
+    g = SMALL["sbm1k"]()
+    ctx.load_graph(g)
+    ref = oracle.louvain(g, 1e-2, max_passes, sync=True, rounds=8, **kw)
+    res = ctx.louvain(1e-2, max_passes, **kw)
+    assert np.array_equal(res.membership, ref.membership)
+    assert res.stats["iterations"] == list(ref.iterations)
+    assert res.stats["communities"] == list(ref.communities)
+
+
+def test_small_graph_with_duplicates_and_fp64_weights(ctx):
+    """Rows that hold a column twice, fp64 weights that need the grid."""
+    r = np.random.default_rng(9)
+    n, m = 400, 3000
+    u, v = r.integers(0, n, m), r.integers(0, n, m)
+    w = r.uniform(0.1, 3.0, m)
+    row, col, ww = np.concatenate([u, v]), np.concatenate([v, u]), np.concatenate([w, w])
+    keep = row != col
+    order = np.argsort(row[keep], kind="stable")
+    row, col, ww = row[keep][order], col[keep][order].astype(np.int32), ww[keep][order]
+    off = np.searchsorted(row, np.arange(n + 1)).astype(np.int64)
+    ctx.load(off, col, ww)
+    wg = ww.copy()
+    assert oracle.weight_grid(wg)[0] == ctx.weight_grid()[0]
+    g = oracle.CSR(n, off, col, wg)
+    ref = oracle.louvain(g, 1e-2, 10, sync=True, rounds=8)
+    assert np.array_equal(ctx.louvain(1e-2, 10).membership, ref.membership)
