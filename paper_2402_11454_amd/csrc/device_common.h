@@ -86,27 +86,79 @@ __device__ __forceinline__ uint32_t key_hash(int32_t k) {
     return h ^ (h >> 15);
 }
 
+// Probing.  Every table probes by double hashing: a key's step is 1, 7, 13,
+// ... or 43, coprime to the table sizes 2^k and 3 2^k, from hash bits that
+// its first slot does not depend on (a mask takes the low bits, a
+// multiply-shift reduction the high ones).  With linear probing the keys
+// pile up in runs, and 64 lanes wait for the longest: at two thirds full
+// (R-MAT 24, the hub chunks' tables) 1.43 -> 1.28 ms per launch.
+__device__ __forceinline__ int step_mask(uint32_t h) { return 1 + 6 * (int)(h >> 29); }
+__device__ __forceinline__ int step_shift(uint32_t h) { return 1 + 6 * (int)(h & 7u); }
+
 // Adds w to the value of `key` in an LDS table of mask+1 slots.
 __device__ __forceinline__ void lds_table_add(int *keys, double *vals, uint32_t mask, int key, double w) {
-    uint32_t s = key_hash(key) & mask;
+    const uint32_t h = key_hash(key);
+    uint32_t s = h & mask;
     while (true) {
         int prev = atomicCAS(&keys[s], kEmpty, key);
         if (prev == kEmpty || prev == key) {
             atomicAdd(&vals[s], w);
             return;
         }
-        s = (s + 1) & mask;
+        s = (s + step_mask(h)) & mask;
     }
 }
 
 // Slot of `key` in an LDS table of mask+1 slots (claimed if absent).
 __device__ __forceinline__ int lds_table_slot(int *keys, uint32_t mask, int key) {
-    uint32_t s = key_hash(key) & mask;
+    const uint32_t h = key_hash(key);
+    uint32_t s = h & mask;
     while (true) {
         int prev = atomicCAS(&keys[s], kEmpty, key);
         if (prev == kEmpty || prev == key) return (int)s;
-        s = (s + 1) & mask;
+        s = (s + step_mask(h)) & mask;
     }
+}
+
+// Puts a thread's entries (c[r], x[r]), r < R with c[r] != kEmpty, into a table
+// in LDS (the threads of a wavefront or a workgroup together): `first` and
+// `after` give a key's first slot and the one probed next.  The first
+// compare-and-swaps of all R entries are issued together, then those that
+// met another community probe on together.  Leaves the entries' slots in q
+// and returns the mask of the entries that claimed theirs: their thread
+// scores the community and clears the slot later (take_owned), so that nothing
+// reads the empty slots.  (Scoring by a pass over the table's slots instead
+// kept the LDS busy with them: a wavefront's table has 768 slots for 65 to
+// 512 entries.)
+template <int R, typename V, typename First, typename After>
+__device__ __forceinline__ unsigned table_put_all(int *keys, V *vals, const int (&c)[R], const double (&x)[R],
+                                                  int (&q)[R], First first, After after) {
+    int prev[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        q[r] = first(c[r]);
+        prev[r] = c[r];
+        if (c[r] != kEmpty) prev[r] = atomicCAS(&keys[q[r]], kEmpty, c[r]);
+    }
+    bool more = true;
+    while (more) {
+        more = false;
+#pragma unroll
+        for (int r = 0; r < R; r++)
+            if (prev[r] != kEmpty && prev[r] != c[r]) {
+                q[r] = after(q[r], c[r]);
+                prev[r] = atomicCAS(&keys[q[r]], kEmpty, c[r]);
+                more = true;
+            }
+    }
+    unsigned own = 0;
+#pragma unroll
+    for (int r = 0; r < R; r++)
+        if (c[r] != kEmpty) {
+            if (prev[r] == kEmpty) own |= 1u << r;
+            atomicAdd(&vals[q[r]], (V)x[r]);
+        }
+    return own;
 }
 
 // Same on a table in global memory (device-scope atomics).
@@ -188,20 +240,6 @@ __device__ __forceinline__ bool better(double g, int c, double g2, int c2, const
     return orig[c] < orig[c2];
 }
 
-// Argmax over the W lanes of an aligned lane group (W power of two <= 64).
-template <int W>
-__device__ __forceinline__ void group_argmax(double &g, int &c, const int32_t *orig) {
-#pragma unroll
-    for (int off = W / 2; off > 0; off >>= 1) {
-        double og = __shfl_xor(g, off, W);
-        int oc = __shfl_xor(c, off, W);
-        if (better(og, oc, g, c, orig)) {
-            g = og;
-            c = oc;
-        }
-    }
-}
-
 template <int W>
 __device__ __forceinline__ double group_sum(double x) {
 #pragma unroll
@@ -277,6 +315,61 @@ __device__ __forceinline__ int group_min(int x) {
     if constexpr (W >= 32) x = min_rows<false>(x);
     if constexpr (W >= 64) x = min_rows<true>(x);
     return x;
+}
+
+// Argmax over the W lanes of an aligned lane group (W power of two <= 64):
+// every lane gets the largest g and, of the communities that reach it, the
+// first in the order of `better`.
+template <int W>
+__device__ __forceinline__ void group_argmax(double &g, int &c, const int32_t *orig) {
+    const double top = group_max<W>(g);
+    const bool at = g == top && c != kIntMax;
+    g = top;
+    if (orig) {
+        // on a level in degree order ties go by the caller's ids, read only
+        // where some group has a tie
+        unsigned long long m = __ballot(at);
+        if (W < kWave) m = (m >> (lane_id() & ~(W - 1))) & ((1ull << (W & 63)) - 1ull);
+        if (__any(__popcll(m) > 1)) {
+            const int o = at ? orig[c] : kIntMax;
+            const int first = group_min<W>(o);   // every lane takes part
+            c = group_min<W>(at && o == first ? c : kIntMax);
+            return;
+        }
+    }
+    c = group_min<W>(at ? c : kIntMax);
+}
+
+// The same over groups of G lanes, G a runtime power of two, at most 16 and
+// the same in the whole wavefront.
+__device__ __forceinline__ double group_max_rt(double x, int G) {
+    if (G >= 2) x = fmax(x, dpp_f64<kDppPair>(x));
+    if (G >= 4) x = fmax(x, dpp_f64<kDppQuad>(x));
+    if (G >= 8) x = fmax(x, dpp_f64<kDppHalfRow>(x));
+    if (G >= 16) x = fmax(x, dpp_f64<kDppRow>(x));
+    return x;
+}
+__device__ __forceinline__ int group_min_rt(int x, int G) {
+    if (G >= 2) x = min(x, dpp_i32<kDppPair>(x));
+    if (G >= 4) x = min(x, dpp_i32<kDppQuad>(x));
+    if (G >= 8) x = min(x, dpp_i32<kDppHalfRow>(x));
+    if (G >= 16) x = min(x, dpp_i32<kDppRow>(x));
+    return x;
+}
+__device__ __forceinline__ void group_argmax_rt(double &g, int &c, int G, const int32_t *orig) {
+    const double top = group_max_rt(g, G);
+    const bool at = g == top && c != kIntMax;
+    g = top;
+    if (orig) {
+        const unsigned long long m = (__ballot(at) >> (lane_id() & ~(G - 1))) & ((1ull << G) - 1ull);
+        if (__any(__popcll(m) > 1)) {
+            const int o = at ? orig[c] : kIntMax;
+            const int first = group_min_rt(o, G);
+            c = group_min_rt(at && o == first ? c : kIntMax, G);
+            return;
+        }
+    }
+    c = group_min_rt(at ? c : kIntMax, G);
 }
 
 // Wave-aggregated atomics keyed by an index: lanes of one wavefront that hit

@@ -184,45 +184,6 @@ __device__ __forceinline__ void fold_key(const MoveArgs &a, double m2, int key, 
 template <int WT> struct TabVal { using T = double; };
 template <> struct TabVal<W_UNIT> { using T = int; };
 
-__device__ __forceinline__ void lds_count_add(int *keys, int *vals, uint32_t mask, int key) {
-    uint32_t s = key_hash(key) & mask;
-    while (true) {
-        int prev = atomicCAS(&keys[s], kEmpty, key);
-        if (prev == kEmpty || prev == key) {
-            atomicAdd(&vals[s], 1);
-            return;
-        }
-        s = (s + 1) & mask;
-    }
-}
-__device__ __forceinline__ void lds_table_put(int *keys, int *vals, uint32_t mask, int key, double) {
-    lds_count_add(keys, vals, mask, key);
-}
-__device__ __forceinline__ void lds_table_put(int *keys, double *vals, uint32_t mask, int key, double w) {
-    lds_table_add(keys, vals, mask, key, w);
-}
-
-// Reads one table slot, resets it and folds it into (bg, bc, kid).
-template <typename V>
-__device__ __forceinline__ void take_slot(const MoveArgs &a, double m2, int *keys, V *vals, int64_t s, int d,
-                                          double ki, double &bg, int &bc, double &kid, unsigned long long &nkeys) {
-    int key = keys[s];
-    if (key == kEmpty) return;
-    double v = (double)vals[s];
-    keys[s] = kEmpty;
-    vals[s] = 0;
-    nkeys++;
-    if (key == d) {
-        kid = v;
-    } else {
-        double g = m2 * v - ki * a.sig[key];
-        if (better(g, key, bg, bc, a.g.orig)) {
-            bg = g;
-            bc = key;
-        }
-    }
-}
-
 // Scores a whole table of T slots with NT threads (t = this thread's
 // index), resetting it: each thread reads CH slots, then the Sigma of their
 // communities together, then folds them.  The argmax does not depend on the
@@ -259,6 +220,38 @@ __device__ __forceinline__ void fold_table(const MoveArgs &a, double m2, int *ke
                     bg = g;
                     bc = key[u];
                 }
+            }
+        }
+    }
+}
+
+// Reads and clears the slots the thread owns and folds their communities
+// into (bg, bc, kid).
+template <int R, typename V>
+__device__ __forceinline__ void take_owned(const MoveArgs &a, double m2, int *keys, V *vals, const int (&c)[R],
+                                           const int (&q)[R], unsigned own, int d, double ki, double &bg, int &bc,
+                                           double &kid) {
+    double v[R], sg[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        v[r] = sg[r] = 0.0;
+        if ((own >> r) & 1u) {
+            if (c[r] != d) sg[r] = a.sig[c[r]];
+            v[r] = (double)vals[q[r]];
+            keys[q[r]] = kEmpty;
+            vals[q[r]] = 0;
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        if (!((own >> r) & 1u)) continue;
+        if (c[r] == d) {
+            kid = v[r];
+        } else {
+            const double g = m2 * v[r] - ki * sg[r];
+            if (better(g, c[r], bg, bc, a.g.orig)) {
+                bg = g;
+                bc = c[r];
             }
         }
     }
@@ -343,23 +336,6 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// Argmax / sum over aligned groups of G lanes, G a runtime power of two.
-__device__ __forceinline__ void group_argmax_rt(double &g, int &c, int G, const int32_t *orig) {
-    for (int off = G >> 1; off > 0; off >>= 1) {
-        double og = __shfl_xor(g, off);
-        int oc = __shfl_xor(c, off);
-        if (better(og, oc, g, c, orig)) {
-            g = og;
-            c = oc;
-        }
-    }
-}
-
-__device__ __forceinline__ double group_sum_rt(double x, int G) {
-    for (int off = G >> 1; off > 0; off >>= 1) x += __shfl_xor(x, off);
-    return x;
-}
-
 // Small bins (degree <= G = 4, 8, ..., 64): a group of L = max(G /
 // kSmallE, 1) lanes per vertex, up to kSmallE entries per lane (loaded
 // together), a table of 2G slots per vertex in the wave's LDS; a wavefront
@@ -379,12 +355,15 @@ __device__ void small_unit(const MoveArgs &a, int bin, int G, int64_t unit, int 
     int *keys = wkeys + grp * kSlots;
     double *vals = wvals + grp * kSlots;
     int i = -1, di = 0, d = -1, csd = 0;
-    int j[kSmallE];
+    int j[kSmallE], c[kSmallE], q[kSmallE];
     double w[kSmallE];
     double ki = 0.0, m2 = a.M2, sgd = 0.0;
+    unsigned own = 0;
 #pragma unroll
     for (int r = 0; r < kSmallE; r++) {
         j[r] = -1;
+        c[r] = kEmpty;
+        q[r] = 0;
         w[r] = 0.0;
     }
     if (valid) {
@@ -404,23 +383,19 @@ __device__ void small_unit(const MoveArgs &a, int bin, int G, int64_t unit, int 
                 w[r] = edge_weight<WT>(a.g.w, b0 + e);
             }
         }
-        int c[kSmallE];
 #pragma unroll
         for (int r = 0; r < kSmallE; r++) c[r] = (j[r] >= 0 && j[r] != i) ? a.cm[j[r]] : kEmpty;
-#pragma unroll
-        for (int r = 0; r < kSmallE; r++)
-            if (c[r] != kEmpty) lds_table_add(keys, vals, kSlots - 1, c[r], w[r]);
+        own = table_put_all(
+            keys, vals, c, w, q, [&](int key) { return (int)(key_hash(key) & (uint32_t)(kSlots - 1)); },
+            [&](int at, int key) { return (at + step_mask(key_hash(key))) & (kSlots - 1); });
     }
     wave_lds_sync();
     double bg = -INFINITY, kid = 0.0;
     int bc = kIntMax;
-    if (valid) {
-#pragma unroll
-        for (int q = 0; q < 2 * kSmallE; q++)
-            if (gl + q * L < kSlots) take_slot(a, m2, keys, vals, gl + q * L, d, ki, bg, bc, kid, acc.keys);
-    }
+    if (valid) take_owned(a, m2, keys, vals, c, q, own, d, ki, bg, bc, kid);
+    acc.keys += __popc(own);
     group_argmax_rt(bg, bc, L, a.g.orig);
-    kid = group_sum_rt(kid, L);
+    kid = group_max_rt(kid, L);   // one lane's, 0 elsewhere; weights are >= 0
     double gain = 0.0;
     bool mv = valid && decide(m2, d, ki, kid, bg, bc, sgd, csd, best_single(a, d, csd, bc), &gain);
     if (mv)
@@ -497,12 +472,13 @@ __global__ void __launch_bounds__(kBlock, WT == W_UNIT ? 5 : 4) k_move_small(Mov
 
 // ---------------------------------------------------------------- large
 
-// Block-wide argmax / sum through LDS; every thread gets the result.
-__device__ void block_argmax_sum(double &bg, int &bc, double &x, const int32_t *orig) {
+// Block-wide argmax, and the one non-zero x (K_{i->d}, >= 0), through LDS;
+// every thread gets the result.
+__device__ void block_argmax_kid(double &bg, int &bc, double &x, const int32_t *orig) {
     __shared__ double sg[kBlock / kWave], sx[kBlock / kWave];
     __shared__ int sc[kBlock / kWave];
     group_argmax<kWave>(bg, bc, orig);
-    x = group_sum<kWave>(x);
+    x = group_max<kWave>(x);
     int w = threadIdx.x / kWave;
     if (lane_id() == 0) { sg[w] = bg; sc[w] = bc; sx[w] = x; }
     __syncthreads();
@@ -512,7 +488,7 @@ __device__ void block_argmax_sum(double &bg, int &bc, double &x, const int32_t *
 #pragma unroll
     for (int q = 1; q < kBlock / kWave; q++) {
         if (better(sg[q], sc[q], bg, bc, orig)) { bg = sg[q]; bc = sc[q]; }
-        x += sx[q];
+        x = fmax(x, sx[q]);
     }
     __syncthreads();
 }
@@ -522,50 +498,30 @@ __device__ void block_argmax_sum(double &bg, int &bc, double &x, const int32_t *
 // 512 and 2048 entries: 36 KB per workgroup of four wave tables or one
 // workgroup table, so four workgroups share a CU's LDS where half-full
 // tables let three (R-MAT 26: 3 % less time per run).  A key's first slot is
-// then the multiply-shift reduction of its hash onto the T slots in use, and
-// probing is linear with wrap-around.  On unit weights (int values) the
+// then the multiply-shift reduction of its hash onto the slots.  On unit weights (int values) the
 // half-full power-of-two tables already fit four workgroups, and the
 // fuller ones only lengthened the probes (R-MAT 20: 2.6 % more time), so
-// they stay.
+// they stay.  Only claimed slots are read back, so a short row costs the
+// same in the whole table as in a part of it.
 template <int WT> struct ScanSlots {
     static constexpr int wave = WT == W_UNIT ? kWaveTable : 3 * kWaveMaxDeg / 2;
     static constexpr int block = WT == W_UNIT ? kBlockTable : 3 * kBlockMaxDeg / 2;
-    // slots a vertex of d entries uses in a table of `cap` slots
-    __device__ static int of(int d, int cap) {
-        return WT == W_UNIT || d <= cap / 3 ? (int)hub_table_size(d) : cap;
-    }
 };
-__device__ __forceinline__ uint32_t block_slot(int key, uint32_t T) {
-    return (uint32_t)(((uint64_t)key_hash(key) * T) >> 32);
-}
-__device__ __forceinline__ void block_put(int *keys, int *vals, uint32_t T, int key, double) {
-    uint32_t s = block_slot(key, T);
-    while (true) {
-        const int prev = atomicCAS(&keys[s], kEmpty, key);
-        if (prev == kEmpty || prev == key) {
-            atomicAdd(&vals[s], 1);
-            return;
-        }
-        s = s + 1 == T ? 0 : s + 1;
-    }
-}
-__device__ __forceinline__ void block_put(int *keys, double *vals, uint32_t T, int key, double w) {
-    uint32_t s = block_slot(key, T);
-    while (true) {
-        const int prev = atomicCAS(&keys[s], kEmpty, key);
-        if (prev == kEmpty || prev == key) {
-            atomicAdd(&vals[s], w);
-            return;
-        }
-        s = s + 1 == T ? 0 : s + 1;
-    }
-}
-template <int WT, typename V>
-__device__ __forceinline__ void scan_put(int *keys, V *vals, int T, int key, double w) {
-    if constexpr (WT == W_UNIT)
-        lds_table_put(keys, vals, (uint32_t)T - 1, key, w);   // T a power of two
-    else
-        block_put(keys, vals, (uint32_t)T, key, w);
+// Puts a thread's R entries into a table of T slots (table_put_all).
+template <int T, int R, typename V>
+__device__ __forceinline__ unsigned scan_put_all(int *keys, V *vals, const int (&c)[R], const double (&x)[R],
+                                                 int (&q)[R]) {
+    return table_put_all(
+        keys, vals, c, x, q,
+        [](int key) {
+            const uint32_t h = key_hash(key);
+            return (T & (T - 1)) == 0 ? (int)(h & (uint32_t)(T - 1)) : (int)(((uint64_t)h * (uint32_t)T) >> 32);
+        },
+        [](int at, int key) {
+            const uint32_t h = key_hash(key);
+            const int to = at + ((T & (T - 1)) == 0 ? step_mask(h) : step_shift(h));
+            return to >= T ? to - T : to;
+        });
 }
 
 template <int WT> struct WaveLds {
@@ -605,7 +561,6 @@ __device__ __forceinline__ void scan_wave(const MoveArgs &a, WaveLds<WT> &lds, i
         double ki = a.K[i];
         const double sgd = a.sig[d];
         const int csd = a.csize[d];
-        const int T = ScanSlots<WT>::of(di, S);
         // the lane's entries (at most R) are loaded together, then their
         // memberships: two round trips to memory instead of 2R
         constexpr int R = kWaveMaxDeg / kWave;
@@ -620,15 +575,15 @@ __device__ __forceinline__ void scan_wave(const MoveArgs &a, WaveLds<WT> &lds, i
         int cj[R];
 #pragma unroll
         for (int r = 0; r < R; r++) cj[r] = jj[r] != i ? a.cm[jj[r]] : kEmpty;
-#pragma unroll
-        for (int r = 0; r < R; r++)
-            if (cj[r] != kEmpty) scan_put<WT>(keys, vals, T, cj[r], ww[r]);
+        int sl[R];
+        const unsigned own = scan_put_all<S>(keys, vals, cj, ww, sl);
         wave_lds_sync();
         double bg = -INFINITY, kid = 0.0;
         int bc = kIntMax;
-        fold_table<kWave, 4>(a, m2, keys, vals, T, lane, d, ki, bg, bc, kid, acc.keys);
+        take_owned(a, m2, keys, vals, cj, sl, own, d, ki, bg, bc, kid);
+        acc.keys += __popc(own);
         group_argmax<kWave>(bg, bc, a.g.orig);
-        kid = group_sum<kWave>(kid);
+        kid = group_max<kWave>(kid);   // one lane's, 0 elsewhere; weights are >= 0
         double gain = 0.0;
         bool mv = decide(m2, d, ki, kid, bg, bc, sgd, csd, best_single(a, d, csd, bc), &gain);
         if (mv)   // the lane's columns are still in registers (weights reloaded)
@@ -684,7 +639,6 @@ __device__ __forceinline__ void scan_block(const MoveArgs &a, BlockLds<WT> &lds,
         double ki = a.K[i];
         const double sgd = a.sig[d];
         const int csd = a.csize[d];
-        const int T = ScanSlots<WT>::of(di, S);
         constexpr int R = kBlockMaxDeg / kBlock;   // entries per thread, loaded together
         int jj[R];
         double ww[R];
@@ -697,14 +651,14 @@ __device__ __forceinline__ void scan_block(const MoveArgs &a, BlockLds<WT> &lds,
         int cj[R];
 #pragma unroll
         for (int r = 0; r < R; r++) cj[r] = jj[r] != i ? a.cm[jj[r]] : kEmpty;
-#pragma unroll
-        for (int r = 0; r < R; r++)
-            if (cj[r] != kEmpty) scan_put<WT>(keys, vals, T, cj[r], ww[r]);
+        int sl[R];
+        const unsigned own = scan_put_all<S>(keys, vals, cj, ww, sl);
         __syncthreads();
         double bg = -INFINITY, kid = 0.0;
         int bc = kIntMax;
-        fold_table<kBlock, 4>(a, m2, keys, vals, T, tid, d, ki, bg, bc, kid, acc.keys);
-        block_argmax_sum(bg, bc, kid, a.g.orig);
+        take_owned(a, m2, keys, vals, cj, sl, own, d, ki, bg, bc, kid);
+        acc.keys += __popc(own);
+        block_argmax_kid(bg, bc, kid, a.g.orig);
         double gain = 0.0;
         bool mv = decide(m2, d, ki, kid, bg, bc, sgd, csd, best_single(a, d, csd, bc), &gain);
         if (mv)   // the thread's columns are still in registers (weights reloaded)
@@ -867,43 +821,39 @@ __global__ void __launch_bounds__(kBlock) k_hub_bucket(MoveArgs a) {
         int64_t end = a.g.off[i] + di;
         if (end > beg + kHubChunk) end = beg + kHubChunk;
         int s = (int)((beg - a.g.off[i]) / kHubChunk);
-        {
-            constexpr int R = kHubChunk / kBlock;   // entries per thread, loaded together
-            int jj[R];
-            double ww[R];
+        constexpr int R = kHubChunk / kBlock;   // entries per thread, loaded together
+        int jj[R];
+        double ww[R];
 #pragma unroll
-            for (int r = 0; r < R; r++) {
-                const int64_t e = beg + tid + r * kBlock;
-                jj[r] = e < end ? load_col(a.g.col, e) : i;
-                ww[r] = e < end ? edge_weight<WT>(a.g.w, e) : 0.0;
-            }
-            int cj[R];
-#pragma unroll
-            for (int r = 0; r < R; r++) cj[r] = jj[r] != i ? a.cm[jj[r]] : kEmpty;
-#pragma unroll
-            for (int r = 0; r < R; r++)
-                if (cj[r] != kEmpty) scan_put<WT>(tkeys, tvals, S, cj[r], ww[r]);
+        for (int r = 0; r < R; r++) {
+            const int64_t e = beg + tid + r * kBlock;
+            jj[r] = e < end ? load_col(a.g.col, e) : i;
+            ww[r] = e < end ? edge_weight<WT>(a.g.w, e) : 0.0;
         }
+        int cj[R], sl[R];
+#pragma unroll
+        for (int r = 0; r < R; r++) cj[r] = jj[r] != i ? a.cm[jj[r]] : kEmpty;
+        const unsigned own = scan_put_all<S>(tkeys, tvals, cj, ww, sl);
         for (int b = tid; b <= P; b += kBlock) pcnt[b] = 0;
         __syncthreads();
-        for (int sl = tid; sl < S; sl += kBlock) {
-            int key = tkeys[sl];
-            if (key != kEmpty) atomicAdd(&pcnt[part_of(key, P)], 1);
-        }
+        // a thread counts, then stages, the communities whose slots it claimed
+#pragma unroll
+        for (int r = 0; r < R; r++)
+            if ((own >> r) & 1u) atomicAdd(&pcnt[part_of(cj[r], P)], 1);
         __syncthreads();
         block_scan_excl(pcnt, P);
         uint32_t *words = a.hbuck + a.hub_b0[i] + (int64_t)s * P;
         for (int b = tid; b < P; b += kBlock) words[b] = ((uint32_t)pcnt[b] << 16) | (uint32_t)(pcnt[b + 1] - pcnt[b]);
         if (tid == 0) acc.aux += (unsigned long long)P;
         __syncthreads();
-        for (int sl = tid; sl < S; sl += kBlock) {
-            int key = tkeys[sl];
-            if (key == kEmpty) continue;
-            double v = (double)tvals[sl];
-            tkeys[sl] = kEmpty;
-            tvals[sl] = 0;
-            int pos = atomicAdd(&pcnt[part_of(key, P)], 1);
-            a.skey[beg + pos] = key;
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            if (!((own >> r) & 1u)) continue;
+            const double v = (double)tvals[sl[r]];
+            tkeys[sl[r]] = kEmpty;
+            tvals[sl[r]] = 0;
+            const int pos = atomicAdd(&pcnt[part_of(cj[r], P)], 1);
+            a.skey[beg + pos] = cj[r];
             a.sval[beg + pos] = v;
             acc.ginserts++;
         }
@@ -984,7 +934,7 @@ __device__ void hub_finish_block(const MoveArgs &a, int i, int P, Acc &acc) {
             kid += a.part_kid[c0 + q];
         }
     }
-    block_argmax_sum(bg, bc, kid, a.g.orig);
+    block_argmax_kid(bg, bc, kid, a.g.orig);
     hub_decide(a, i, bg, bc, kid, P, acc);
     __syncthreads();
 }
@@ -1108,7 +1058,7 @@ __global__ void __launch_bounds__(kBlock) k_hub_gather(MoveArgs a) {
             double bg = -INFINITY, kid = 0.0;
             int bc = kIntMax;
             fold_table<kBlock, 8>(a, m2, tkeys, tvals, S, tid, d, ki, bg, bc, kid, acc.keys);
-            block_argmax_sum(bg, bc, kid, a.g.orig);
+            block_argmax_kid(bg, bc, kid, a.g.orig);
             if (tid == 0) {
                 a.part_g[k] = bg;
                 a.part_c[k] = bc;
@@ -1167,7 +1117,7 @@ __global__ void __launch_bounds__(kBlock) k_move_hub_part(MoveArgs a) {
             for (int u = 0; u < 4; u++)
                 if (key[u] != kEmpty) fold_key(a, m2, key[u], v[u], d, ki, bg, bc, kid);
         }
-        block_argmax_sum(bg, bc, kid, a.g.orig);
+        block_argmax_kid(bg, bc, kid, a.g.orig);
         if (threadIdx.x == 0) {
             a.part_g[k] = bg;
             a.part_c[k] = bc;
@@ -1201,7 +1151,7 @@ __global__ void __launch_bounds__(kBlock) k_move_hub_final(MoveArgs a) {
             kid += a.part_kid[c0 + q];
         }
         group_argmax<kWave>(bg, bc, a.g.orig);
-        kid = group_sum<kWave>(kid);
+        kid = group_max<kWave>(kid);   // one chunk's, 0 elsewhere
         double gain = 0.0;
         const int csd = a.csize[d];
         bool mv = decide(m2, d, ki, kid, bg, bc, a.sig[d], csd, best_single(a, d, csd, bc), &gain);

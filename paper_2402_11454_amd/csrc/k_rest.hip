@@ -141,28 +141,10 @@ __device__ __noinline__ void scan_rows(const int32_t *col, const double *w, int 
     const double ki = s.K[i], sgd = s.sig[d];
 #pragma unroll
     for (int r = 0; r < R; r++) c[r] = j[r] != i ? s.cm[j[r]] : kEmpty;
-    uint32_t q[R];
-    int prev[R];
-#pragma unroll
-    for (int r = 0; r < R; r++) {
-        q[r] = key_hash(c[r]) >> (32 - __builtin_ctz(S));
-        prev[r] = c[r] != kEmpty ? atomicCAS(&keys[q[r]], kEmpty, c[r]) : c[r];
-    }
-    // the entries whose slot held another community probe on together
-    bool more = true;
-    while (more) {
-        more = false;
-#pragma unroll
-        for (int r = 0; r < R; r++)
-            if (prev[r] != kEmpty && prev[r] != c[r]) {
-                q[r] = (q[r] + 1) & (S - 1);
-                prev[r] = atomicCAS(&keys[q[r]], kEmpty, c[r]);
-                more = true;
-            }
-    }
-#pragma unroll
-    for (int r = 0; r < R; r++)
-        if (c[r] != kEmpty) atomicAdd(&vals[q[r]], x[r]);
+    int q[R];
+    const unsigned owned = table_put_all(
+        keys, vals, c, x, q, [](int key) { return (int)(key_hash(key) >> (32 - __builtin_ctz(S))); },
+        [](int at, int key) { return (at + step_shift(key_hash(key))) & (int)(S - 1); });
     __builtin_amdgcn_wave_barrier();
     // the lane that claimed a slot scores its community and clears the slot:
     // nothing reads the empty slots
@@ -171,7 +153,7 @@ __device__ __noinline__ void scan_rows(const int32_t *col, const double *w, int 
 #pragma unroll
     for (int r = 0; r < R; r++) {
         v[r] = sg[r] = 0.0;
-        own[r] = c[r] != kEmpty && prev[r] == kEmpty;
+        own[r] = (owned >> r) & 1u;
         if (own[r]) {
             v[r] = vals[q[r]];
             sg[r] = s.sig[c[r]];
