@@ -230,6 +230,59 @@ __device__ __forceinline__ int last_le(const int *v, int n, int t) {
     return lo;
 }
 
+// Merges staged (key, value) pairs t = 0 .. total - 1 into a table of S slots
+// in LDS, a workgroup together: pair t of the window lies at at(s, t), s the
+// source with pst[s] <= t < pst[s + 1], s < nw.  *nkeys counts the distinct
+// keys; past CAP of them *ovf is set and the workgroup stops (fewer than kBlock
+// inserts are in flight then: CAP + kBlock < S keeps the table open).
+// A thread takes four pairs at a time: their sources by one binary search in
+// step, then their loads together, then the inserts (a pair at a time left
+// one trip to memory per 256 pairs on the workgroup's path).
+template <int S, int CAP, typename V, typename At>
+__device__ __forceinline__ void merge_pairs(const int *pst, int nw, int total, const int32_t *skey,
+                                            const double *sval, int *tkeys, V *tvals, int *nkeys, int *ovf, At at) {
+    static_assert(CAP + kBlock < S, "the merge table never fills");
+    constexpr int R = 4;
+    int top = 1;
+    while (2 * top < nw) top <<= 1;
+    for (int t0 = threadIdx.x; t0 < total; t0 += R * kBlock) {
+        int src[R], key[R];
+        double v[R];
+#pragma unroll
+        for (int r = 0; r < R; r++) src[r] = 0;
+        for (int step = top; step > 0; step >>= 1)
+#pragma unroll
+            for (int r = 0; r < R; r++)
+                if (src[r] + step < nw && pst[src[r] + step] <= t0 + r * kBlock) src[r] += step;
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const int t = t0 + r * kBlock;
+            key[r] = kEmpty;
+            v[r] = 0.0;
+            if (t < total) {
+                const int64_t idx = at(src[r], t);
+                key[r] = skey[idx];
+                v[r] = sval[idx];
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            if (key[r] == kEmpty || *(volatile int *)ovf) continue;
+            const uint32_t h = key_hash(key[r]);
+            constexpr bool kMask = (S & (S - 1)) == 0;
+            int q = kMask ? (int)(h & (uint32_t)(S - 1)) : (int)(((uint64_t)h * (uint32_t)S) >> 32);
+            const int step = kMask ? step_mask(h) : step_shift(h);
+            while (true) {
+                const int prev = atomicCAS(&tkeys[q], kEmpty, key[r]);
+                if (prev == kEmpty && atomicAdd(nkeys, 1) >= CAP) *(volatile int *)ovf = 1;
+                if (prev == kEmpty || prev == key[r]) break;
+                q = q + step >= S ? q + step - S : q + step;
+            }
+            atomicAdd(&tvals[q], (V)v[r]);
+        }
+    }
+}
+
 // (g, c) beats (g2, c2): larger score, ties to the lower community id.
 // Community ids are vertex ids of the level; on a level stored in degree
 // order (orig != nullptr) they are compared as the caller's vertex ids,

@@ -241,20 +241,6 @@ __device__ __forceinline__ int group_search(int incl, int x) {
 
 // Inserts the entries of a chunk of at most W members (positions
 // [m0, m1) of c's member list) into the table; uniform across the group.
-// Adds w to `key` in an LDS table of T slots (any T): first slot by the
-// multiply-shift reduction of the hash, linear probing with wrap-around.
-__device__ __forceinline__ void lds_table_add_mod(int *keys, double *vals, uint32_t T, int key, double w) {
-    uint32_t s = (uint32_t)(((uint64_t)key_hash(key) * T) >> 32);
-    while (true) {
-        const int prev = atomicCAS(&keys[s], kEmpty, key);
-        if (prev == kEmpty || prev == key) {
-            atomicAdd(&vals[s], w);
-            return;
-        }
-        s = s + 1 == T ? 0 : s + 1;
-    }
-}
-
 // GLOBAL: a global table of mask + 1 slots; else an LDS table of mask + 1
 // slots, or (MOD) of `mask` slots.
 template <int W, int WT, bool GLOBAL, bool MOD = false>
@@ -291,16 +277,25 @@ __device__ void insert_member_chunk(const AggArgs &a, int64_t m0, int64_t m1, in
         }
         int c[R];
 #pragma unroll
-        for (int r = 0; r < R; r++) c[r] = e[r] >= 0 ? a.cm[j[r]] : 0;
+        for (int r = 0; r < R; r++) c[r] = e[r] >= 0 ? a.cm[j[r]] : kEmpty;
+        if constexpr (GLOBAL) {
 #pragma unroll
-        for (int r = 0; r < R; r++) {
-            if (e[r] < 0) continue;
-            if constexpr (GLOBAL)
-                gbl_table_add(keys, vals, mask, c[r], w[r]);
-            else if constexpr (MOD)
-                lds_table_add_mod(keys, vals, (uint32_t)mask, c[r], w[r]);
-            else
-                lds_table_add(keys, vals, (uint32_t)mask, c[r], w[r]);
+            for (int r = 0; r < R; r++)
+                if (c[r] != kEmpty) gbl_table_add(keys, vals, mask, c[r], w[r]);
+        } else {
+            int q[R];
+            const int T = MOD ? (int)mask : (int)mask + 1;
+            table_put_all(
+                keys, vals, c, w, q,
+                [&](int key) {
+                    const uint32_t h = key_hash(key);
+                    return MOD ? (int)(((uint64_t)h * (uint32_t)T) >> 32) : (int)(h & (uint32_t)mask);
+                },
+                [&](int at, int key) {
+                    const uint32_t h = key_hash(key);
+                    if (!MOD) return (at + step_mask(h)) & (int)mask;
+                    return at + step_shift(h) >= T ? at + step_shift(h) - T : at + step_shift(h);
+                });
         }
     }
 }
@@ -525,11 +520,14 @@ __global__ void __launch_bounds__(kBlock) k_agg_chunk_k0(const int32_t *cch_comm
 // at the member holding the next chunk's first entry (or at c's last
 // member); members with entries come first, so there are at most kAggChunk.
 // Each thread resolves its four entries first and then issues their loads
-// together.
+// together.  Leaves the entries' communities in cj and their slots in slot
+// and returns the mask of the entries that claimed theirs (table_put_all).
+constexpr int kChunkPer = kAggChunk / kBlock;   // entries per thread
 template <int WT>
-__device__ __forceinline__ void reduce_hub_chunk(const AggArgs &a, const int32_t *cch_comm, int64_t nchunks,
-                                                 int64_t ch, int c, int64_t X0, int64_t X1, int *tkeys,
-                                                 double *tvals, int *win, int64_t *moff) {
+__device__ __forceinline__ unsigned reduce_hub_chunk(const AggArgs &a, const int32_t *cch_comm, int64_t nchunks,
+                                                     int64_t ch, int c, int64_t X0, int64_t X1, int *tkeys,
+                                                     double *tvals, int *win, int64_t *moff, int (&cj)[kChunkPer],
+                                                     int (&slot)[kChunkPer]) {
     const int tid = threadIdx.x;
     const int64_t k0 = a.ck0[ch];
     const int64_t m_end = a.coff[c + 1];
@@ -542,23 +540,22 @@ __device__ __forceinline__ void reduce_hub_chunk(const AggArgs &a, const int32_t
     }
     if (tid == 0) win[nm] = (int)(X1 - X0);
     __syncthreads();
-    constexpr int R = kAggChunk / kBlock;
+    constexpr int R = kChunkPer;
     int64_t e[R];
     bool ok[R];
+    int lo[R], top = 1;
+    while (2 * top < nm) top <<= 1;
 #pragma unroll
     for (int r = 0; r < R; r++) {
-        const int x = r * kBlock + tid;
-        ok[r] = X0 + x < X1;
-        e[r] = 0;
-        if (ok[r]) {
-            int lo = 0, hi = nm - 1;
-            while (lo < hi) {
-                int mid = (lo + hi + 1) >> 1;
-                if (win[mid] <= x) lo = mid; else hi = mid - 1;
-            }
-            e[r] = moff[lo] + (x - win[lo]);
-        }
+        lo[r] = 0;
+        ok[r] = X0 + r * kBlock + tid < X1;
     }
+    for (int step = top; step > 0; step >>= 1)   // the thread's entries search in step
+#pragma unroll
+        for (int r = 0; r < R; r++)
+            if (lo[r] + step < nm && win[lo[r] + step] <= r * kBlock + tid) lo[r] += step;
+#pragma unroll
+    for (int r = 0; r < R; r++) e[r] = ok[r] ? moff[lo[r]] + (r * kBlock + tid - win[lo[r]]) : 0;
     int32_t j[R];
     double w[R];
 #pragma unroll
@@ -566,13 +563,13 @@ __device__ __forceinline__ void reduce_hub_chunk(const AggArgs &a, const int32_t
         j[r] = ok[r] ? load_col(a.g.col, e[r]) : 0;
         w[r] = ok[r] ? edge_weight<WT>(a.g.w, e[r]) : 0.0;
     }
-    int cj[R];
 #pragma unroll
-    for (int r = 0; r < R; r++) cj[r] = ok[r] ? a.cm[j[r]] : 0;
-#pragma unroll
-    for (int r = 0; r < R; r++)
-        if (ok[r]) lds_table_add(tkeys, tvals, kAggChunkTable - 1, cj[r], w[r]);
+    for (int r = 0; r < R; r++) cj[r] = ok[r] ? a.cm[j[r]] : kEmpty;
+    const unsigned own = table_put_all(
+        tkeys, tvals, cj, w, slot, [](int key) { return (int)(key_hash(key) & (uint32_t)(kAggChunkTable - 1)); },
+        [](int at, int key) { return (at + step_mask(key_hash(key))) & (kAggChunkTable - 1); });
     __syncthreads();
+    return own;
 }
 
 // Hub communities, one workgroup per chunk of kAggChunk entries of the
@@ -595,16 +592,17 @@ __global__ void __launch_bounds__(kBlock) k_agg_hub_chunks(AggArgs a, const int3
         int c = cch_comm[ch];
         int64_t X0 = cch_beg[ch];
         int64_t X1 = X0 + kAggChunk < a.eoff[c + 1] ? X0 + kAggChunk : a.eoff[c + 1];
-        reduce_hub_chunk<WT>(a, cch_comm, nchunks, ch, c, X0, X1, tkeys, tvals, win, moff);
+        int cj[kChunkPer], sl[kChunkPer];
+        const unsigned own = reduce_hub_chunk<WT>(a, cch_comm, nchunks, ch, c, X0, X1, tkeys, tvals, win, moff, cj, sl);
         int64_t tb = a.ctab[c];
         uint64_t mask = comm_table_size(a.eoff[c + 1] - a.eoff[c], a.n2) - 1;
-        for (int s = threadIdx.x; s < kAggChunkTable; s += kBlock) {
-            int key = tkeys[s];
-            if (key == kEmpty) continue;
-            double v = tvals[s];
-            tkeys[s] = kEmpty;
-            tvals[s] = 0.0;
-            gbl_table_add(a.hkeys + tb, a.hvals + tb, mask, key, v);
+#pragma unroll
+        for (int r = 0; r < kChunkPer; r++) {
+            if (!((own >> r) & 1u)) continue;
+            const double v = tvals[sl[r]];
+            tkeys[sl[r]] = kEmpty;
+            tvals[sl[r]] = 0.0;
+            gbl_table_add(a.hkeys + tb, a.hvals + tb, mask, cj[r], v);
         }
         __syncthreads();
     }
@@ -698,7 +696,6 @@ constexpr int kGatherWin = 2048;       // source chunks per window of the gather
 // CU where the 4096-slot table allowed two.
 constexpr int kAggGatherSlots = 3072;
 constexpr int kAggGatherCap = 2048;
-static_assert(kAggGatherCap + kBlock < kAggGatherSlots, "the gather's table never fills");
 
 // P_c: one partition per kAggPartTarget possible distinct neighbours (at most
 // min(total degree, n2)); at most kAggMaxParts and at most the chunk count.
@@ -745,29 +742,31 @@ __global__ void __launch_bounds__(kBlock) k_agg_part_bucket(AggArgs a, const int
         int c = cch_comm[ch];
         int64_t X0 = cch_beg[ch];
         int64_t X1 = X0 + kAggChunk < a.eoff[c + 1] ? X0 + kAggChunk : a.eoff[c + 1];
-        reduce_hub_chunk<WT>(a, cch_comm, nchunks, ch, c, X0, X1, tkeys, tvals, win, moff);
+        int cj[kChunkPer], slot[kChunkPer];
+        const unsigned own =
+            reduce_hub_chunk<WT>(a, cch_comm, nchunks, ch, c, X0, X1, tkeys, tvals, win, moff, cj, slot);
         const int64_t tot = a.eoff[c + 1] - a.eoff[c];
         const int P = agg_parts(tot, a.n2);
         const int64_t s = (X0 - a.eoff[c]) / kAggChunk;
         for (int b = tid; b <= P; b += kBlock) pcnt[b] = 0;
         __syncthreads();
-        for (int sl = tid; sl < kAggChunkTable; sl += kBlock) {
-            int key = tkeys[sl];
-            if (key != kEmpty) atomicAdd(&pcnt[part_of(key, P)], 1);
-        }
+        // a thread counts, then stages, the communities whose slots it claimed
+#pragma unroll
+        for (int r = 0; r < kChunkPer; r++)
+            if ((own >> r) & 1u) atomicAdd(&pcnt[part_of(cj[r], P)], 1);
         __syncthreads();
         block_scan_excl(pcnt, P);
         uint32_t *wd = a.words + a.woff[c] + s * P;
         for (int b = tid; b < P; b += kBlock) wd[b] = ((uint32_t)pcnt[b] << 16) | (uint32_t)(pcnt[b + 1] - pcnt[b]);
         __syncthreads();
-        for (int sl = tid; sl < kAggChunkTable; sl += kBlock) {
-            int key = tkeys[sl];
-            if (key == kEmpty) continue;
-            double v = tvals[sl];
-            tkeys[sl] = kEmpty;
-            tvals[sl] = 0.0;
-            int pos = atomicAdd(&pcnt[part_of(key, P)], 1);
-            a.stage_col[X0 + pos] = key;
+#pragma unroll
+        for (int r = 0; r < kChunkPer; r++) {
+            if (!((own >> r) & 1u)) continue;
+            const double v = tvals[slot[r]];
+            tkeys[slot[r]] = kEmpty;
+            tvals[slot[r]] = 0.0;
+            const int pos = atomicAdd(&pcnt[part_of(cj[r], P)], 1);
+            a.stage_col[X0 + pos] = cj[r];
             a.stage_w[X0 + pos] = v;
         }
         __syncthreads();
@@ -821,29 +820,9 @@ __global__ void __launch_bounds__(kBlock) k_agg_part_gather(AggArgs a, const int
         for (int64_t w0 = 0; w0 < nch; w0 += kGatherWin) {
             int nw = (int)(nch - w0 < kGatherWin ? nch - w0 : kGatherWin);
             int total = load_window(wd, P, p, w0, nw, pst, srcst);
-            for (int t = tid; t < total; t += kBlock) {
-                if (*(volatile int *)&ovf) break;
-                int s = last_le(pst, nw, t);
-                int64_t idx = e0 + (w0 + s) * kAggChunk + (int64_t)srcst[s] + (t - pst[s]);
-                int key = a.stage_col[idx];
-                double v = a.stage_w[idx];
-                // at most kAggGatherCap distinct keys (plus fewer than kBlock
-                // in flight): the table never fills
-                uint32_t sl = (uint32_t)(((uint64_t)key_hash(key) * kAggGatherSlots) >> 32);
-                while (true) {
-                    int prev = atomicCAS(&tkeys[sl], kEmpty, key);
-                    if (prev == kEmpty) {
-                        if (atomicAdd(&nkeys, 1) >= kAggGatherCap) ovf = 1;
-                        atomicAdd(&tvals[sl], v);
-                        break;
-                    }
-                    if (prev == key) {
-                        atomicAdd(&tvals[sl], v);
-                        break;
-                    }
-                    sl = sl + 1 == kAggGatherSlots ? 0 : sl + 1;
-                }
-            }
+            merge_pairs<kAggGatherSlots, kAggGatherCap>(
+                pst, nw, total, a.stage_col, a.stage_w, tkeys, tvals, &nkeys, &ovf,
+                [&](int s, int t) { return e0 + (w0 + s) * kAggChunk + (int64_t)srcst[s] + (t - pst[s]); });
             __syncthreads();
             if (ovf) break;
         }

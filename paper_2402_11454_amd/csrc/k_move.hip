@@ -961,17 +961,10 @@ constexpr int kHubWin = 512;
 // at most 2560 (a partition holds about 2048 on average, as a hub has one
 // partition per chunk of 2048 entries), so that four workgroups share a
 // CU's LDS where the 4096-slot fp64 table let three.  Past the cap the hub
-// takes its global table.  Fewer than kBlock inserts overshoot the cap.
+// takes its global table.
 template <int WT> struct GatherSlots {
     static constexpr int slots = WT == W_UNIT ? kBlockTable : 3 * kBlockMaxDeg / 2;
     static constexpr int cap = WT == W_UNIT ? kPartCap : 2560;
-    static_assert(cap + kBlock < slots, "the merge table never fills");
-    __device__ static uint32_t first(int key) {
-        if constexpr (WT == W_UNIT)
-            return key_hash(key) & (uint32_t)(slots - 1);
-        else
-            return (uint32_t)(((uint64_t)key_hash(key) * slots) >> 32);
-    }
 };
 
 template <int WT>
@@ -1019,29 +1012,9 @@ __global__ void __launch_bounds__(kBlock) k_hub_gather(MoveArgs a) {
             block_scan_excl(pst, nw);
             const int total = pst[nw];
             if (tid == 0) acc.ginserts += (unsigned long long)total;
-            for (int t = tid; t < total; t += kBlock) {
-                if (*(volatile int *)&ovf) break;
-                int s = last_le(pst, nw, t);
-                int64_t idx = base + (int64_t)(w0 + s) * kHubChunk + (int64_t)srcst[s] + (t - pst[s]);
-                int key = a.skey[idx];
-                double v = a.sval[idx];
-                // insert, counting distinct keys; past kPartCap the partition
-                // stops (at most kBlock inserts overshoot: the table never fills)
-                uint32_t sl = GatherSlots<WT>::first(key);
-                while (true) {
-                    int prev = atomicCAS(&tkeys[sl], kEmpty, key);
-                    if (prev == kEmpty) {
-                        if (atomicAdd(&nkeys, 1) >= GatherSlots<WT>::cap) ovf = 1;
-                        atomicAdd(&tvals[sl], (V)v);
-                        break;
-                    }
-                    if (prev == key) {
-                        atomicAdd(&tvals[sl], (V)v);
-                        break;
-                    }
-                    sl = sl + 1 == (uint32_t)S ? 0 : sl + 1;
-                }
-            }
+            merge_pairs<S, GatherSlots<WT>::cap>(
+                pst, nw, total, a.skey, a.sval, tkeys, tvals, &nkeys, &ovf,
+                [&](int s, int t) { return base + (int64_t)(w0 + s) * kHubChunk + (int64_t)srcst[s] + (t - pst[s]); });
             __syncthreads();
             if (ovf) break;
         }
