@@ -32,39 +32,47 @@ struct Acc {          // per-thread counters, reduced per block at the end
     unsigned long long moved = 0, verts = 0, scanned = 0, keys = 0, ginserts = 0, aux = 0;
 };
 
-__device__ void flush_acc(const Acc &acc, IterCounters *ctr, int cls) {
-    constexpr int F = 6;
-    __shared__ unsigned long long sg[kBlock / kWave];
-    __shared__ unsigned long long sv[F][kBlock / kWave];
-    const unsigned long long g = (unsigned long long)group_sum_ll<kWave>((long long)acc.gain);
-    long long v[F] = {(long long)acc.moved, (long long)acc.verts, (long long)acc.scanned, (long long)acc.keys,
-                      (long long)acc.ginserts, (long long)acc.aux};
+// Adds a workgroup's counters to its stripe.  Workgroups that counted nothing
+// leave at once; in the others only the counters that some lane of a
+// wavefront has are summed over its lanes (summing all seven in every
+// workgroup took 1.5 us at the end of each launch, as long as a unit's trips
+// to memory).
+__device__ __forceinline__ void flush_acc(const Acc &acc, IterCounters *ctr, int cls) {
+    constexpr int F = 7;
+    __shared__ unsigned long long part[F][kBlock / kWave];
+    const unsigned long long v[F] = {acc.gain, acc.moved, acc.verts, acc.scanned, acc.keys, acc.ginserts, acc.aux};
+    bool some = false;
 #pragma unroll
-    for (int f = 0; f < F; f++) v[f] = group_sum_ll<kWave>(v[f]);
-    int w = threadIdx.x / kWave;
-    if (lane_id() == 0) {
-        sg[w] = g;
+    for (int f = 0; f < F; f++) some = some || v[f] != 0;
+    if (!__syncthreads_or(some)) return;
 #pragma unroll
-        for (int f = 0; f < F; f++) sv[f][w] = (unsigned long long)v[f];
+    for (int f = 0; f < F; f++) {
+        unsigned long long x = v[f];
+        const unsigned long long has = __ballot(x != 0);
+        if ((has & (has - 1)) != 0) x = (unsigned long long)group_sum_ll<kWave>((long long)x);
+        if (lane_id() == (has ? __ffsll((long long)has) - 1 : 0)) part[f][threadIdx.x / kWave] = x;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long tg = 0;
-        unsigned long long t[F] = {0, 0, 0, 0, 0, 0};
-        for (int q = 0; q < kBlock / kWave; q++) {
-            tg += sg[q];
-            for (int f = 0; f < F; f++) t[f] += sv[f][q];
-        }
+    if (threadIdx.x < F) {
+        const int f = threadIdx.x;
+        unsigned long long t = 0;
+#pragma unroll
+        for (int w = 0; w < kBlock / kWave; w++) t += part[f][w];
         CounterStripe &st = ctr->st[blockIdx.x % kStripes];
-        if (tg) atomicAdd(&st.gain, tg);
-        if (t[0]) atomicAdd(&st.moved, t[0]);
-        if (t[1]) atomicAdd(&st.verts[cls], t[1]);
-        if (t[2]) atomicAdd(&st.scanned[cls], t[2]);
-        if (t[3]) atomicAdd(&st.keys[cls], t[3]);
-        if (t[4]) atomicAdd(&st.ginserts[cls], t[4]);
-        if (t[5]) atomicAdd(&st.aux[cls], t[5]);
+        unsigned long long *to = f == 0 ? &st.gain : f == 1 ? &st.moved : f == 2 ? &st.verts[cls]
+                                 : f == 3 ? &st.scanned[cls] : f == 4 ? &st.keys[cls]
+                                 : f == 5 ? &st.ginserts[cls] : &st.aux[cls];
+        if (t) atomicAdd(to, t);
     }
 }
+
+// What a scan serves beside the plain sweeps of one graph: a batch's graphs;
+// the history, traces and D_i of the gate; move records and gain outputs.
+// The scans of untimed sweeps are compiled for none, for a batch and for
+// all: code that a sweep never runs costs it registers (the general scans
+// spill) and, as a launch on a small level is one pass through the code,
+// instruction fetches.
+enum { kScanBatch = 1, kScanHist = 2, kScanOther = 4, kScanAll = 7 };
 
 // Batch: a mover's gain and count into its graph's totals (one lane).
 __device__ __forceinline__ void graph_totals(const MoveArgs &a, int i, unsigned long long gain) {
@@ -79,9 +87,10 @@ __device__ __forceinline__ void graph_totals(const MoveArgs &a, int i, unsigned 
 // left at its move of the preceding sweep, which undoes a swap made from one
 // snapshot, counts nothing (the move is still made), and this move is
 // recorded.  One lane per mover.
+template <int F = kScanAll>
 __device__ __forceinline__ unsigned long long counted_gain(const MoveArgs &a, int i, int d, int bc, double gain,
                                                            double m2) {
-    if (a.mhist) {
+    if ((F & kScanOther) && a.mhist) {
         const int32_t sw = (int32_t)*a.sweep_dev;
         const uint64_t h = (uint64_t)a.mhist[i];
         a.mhist[i] = (int64_t)(((uint64_t)(uint32_t)d << 32) | (uint32_t)sw);
@@ -91,7 +100,10 @@ __device__ __forceinline__ unsigned long long counted_gain(const MoveArgs &a, in
 }
 
 // 2m of vertex i's graph (the level's 2m unless it holds a batch).
-__device__ __forceinline__ double m2_of(const MoveArgs &a, int i) { return a.g.M2g ? a.g.M2g[a.g.gid[i]] : a.M2; }
+template <int F = kScanAll>
+__device__ __forceinline__ double m2_of(const MoveArgs &a, int i) {
+    return (F & kScanBatch) && a.g.M2g ? a.g.M2g[a.g.gid[i]] : a.M2;
+}
 
 // Decision from the group's best candidate; identical on every lane.
 // sig_d = Sigma_d and csz_d = |d| are loaded early by the callers;
@@ -159,9 +171,10 @@ __device__ __forceinline__ void record_scan(const MoveArgs &a, double m2, int i,
 
 // A mover's entry (i, j), j != i: j is unprocessed again and, with the
 // gate's history on, D_j grows by w_ij.
+template <int F = kScanAll>
 __device__ __forceinline__ void mark_neighbour(const MoveArgs &a, int j, double w) {
     a.flag[j] = 1;
-    if (a.dmoved) unsafeAtomicAdd(&a.dmoved[j], w);
+    if ((F & kScanHist) && a.dmoved) unsafeAtomicAdd(&a.dmoved[j], w);
 }
 
 // Folds the entry (key, v) of a scan table into (bg, bc, kid).
@@ -291,23 +304,63 @@ __device__ void compact_range(const MoveArgs &a, const int32_t *bl, int64_t span
     __shared__ int nst;
     if (threadIdx.x == 0) nst = 0;
     __syncthreads();
-    for (int64_t t = lo + threadIdx.x; t < hi; t += kBlock) {
-        int b = 0;
-        while (t >= pre[b + 1]) b++;
-        const int i = bl[a.qbase[b] + (t - pre[b])];
-        bool act = a.flag[i] != 0 && (!a.gactive || a.gactive[a.g.gid[i]]);
-        if (act && a.single_only && a.csize[a.cm[i]] != 1) {
-            a.flag[i] = 0;   // merged into a sub-community: stays
-            act = false;
+    // four entries per thread in flight; the active ones of a wavefront take
+    // their places with two LDS atomics (ranks by ballot: the buckets lie bin
+    // by bin, so its lanes nearly always share one bin)
+    constexpr int R = 4;
+    for (int64_t t0 = lo; t0 < hi; t0 += R * kBlock) {   // uniform over the workgroup
+        int bin[R], v[R];
+        bool act[R];
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const int64_t t = t0 + r * kBlock + threadIdx.x;
+            int b = 0;
+#pragma unroll
+            for (int q = 1; q < kNumBins; q++) b += t >= pre[q];
+            bin[r] = b;
+            v[r] = -1;
+            if (t < hi) {
+                int64_t base = a.qbase[0];   // of bin b, less its first position
+#pragma unroll
+                for (int q = 1; q < kNumBins; q++)
+                    if (b == q) base = a.qbase[q] - pre[q];
+                v[r] = bl[base + t];
+            }
         }
-        if (b == BIN_HUB) a.hub_act[i] = act ? 1 : 0;
-        if (act) {
-            a.flag[i] = 0;
-            if (a.dmoved) a.dsnap[i] = a.dmoved[i];   // the features' D_i
-            const int rank = atomicAdd(&lcnt[b], 1);
-            const int slot = atomicAdd(&nst, 1);
-            l.sv[slot] = i;
-            l.sbr[slot] = ((uint32_t)b << 28) | (uint32_t)rank;
+#pragma unroll
+        for (int r = 0; r < R; r++) act[r] = v[r] >= 0 && a.flag[v[r]] != 0;
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const int i = v[r], b = bin[r];
+            if (act[r] && a.gactive && !a.gactive[a.g.gid[i]]) act[r] = false;
+            if (act[r] && a.single_only && a.csize[a.cm[i]] != 1) {
+                a.flag[i] = 0;   // merged into a sub-community: stays
+                act[r] = false;
+            }
+            if (b == BIN_HUB && i >= 0) a.hub_act[i] = act[r] ? 1 : 0;
+            if (act[r]) {
+                a.flag[i] = 0;
+                if (a.dmoved) a.dsnap[i] = a.dmoved[i];   // the features' D_i
+            }
+            unsigned long long left = __ballot(act[r]);
+            if (left == 0) continue;
+            const int first = __ffsll((long long)left) - 1;
+            int slot = 0;
+            if (lane_id() == first) slot = atomicAdd(&nst, __popcll(left));
+            slot = __shfl(slot, first) + __popcll(left & ((1ull << lane_id()) - 1ull));
+            while (left) {
+                const int lead = __ffsll((long long)left) - 1, lb = __shfl(b, lead);
+                const bool mine = act[r] && b == lb;
+                const unsigned long long m = __ballot(mine);
+                int rank = 0;
+                if (lane_id() == lead) rank = atomicAdd(&lcnt[lb], __popcll(m));
+                rank = __shfl(rank, lead) + __popcll(m & ((1ull << lane_id()) - 1ull));
+                if (mine) {
+                    l.sv[slot] = i;
+                    l.sbr[slot] = ((uint32_t)b << 28) | (uint32_t)rank;
+                }
+                left &= ~m;
+            }
         }
     }
     __syncthreads();
@@ -344,7 +397,7 @@ __device__ __forceinline__ void wave_lds_sync() {
 constexpr int kSmallE = 4;
 __host__ __device__ inline int small_lanes(int G) { return G > kSmallE ? G / kSmallE : 1; }
 
-template <int WT>
+template <int WT, int F>
 __device__ void small_unit(const MoveArgs &a, int bin, int G, int64_t unit, int cnt, int *wkeys, double *wvals,
                            Acc &acc) {
     const int kSlots = 2 * G, L = small_lanes(G);
@@ -368,7 +421,7 @@ __device__ void small_unit(const MoveArgs &a, int bin, int G, int64_t unit, int 
     }
     if (valid) {
         i = a.queue[a.qbase[bin] + qi];
-        m2 = m2_of(a, i);
+        m2 = m2_of<F>(a, i);
         di = a.g.deg[i];
         d = a.cm[i];
         ki = a.K[i];
@@ -401,10 +454,10 @@ __device__ void small_unit(const MoveArgs &a, int bin, int G, int64_t unit, int 
     if (mv)
 #pragma unroll
         for (int r = 0; r < kSmallE; r++)
-            if (j[r] >= 0 && j[r] != i) mark_neighbour(a, j[r], w[r]);
+            if (j[r] >= 0 && j[r] != i) mark_neighbour<F>(a, j[r], w[r]);
     bool lead = valid && gl == 0;
-    const unsigned long long cg = lead && mv ? counted_gain(a, i, d, bc, gain, m2) : 0ull;
-    if (a.ggain) {   // batch: per-graph totals, one atomic per graph met by the wavefront
+    const unsigned long long cg = lead && mv ? counted_gain<F>(a, i, d, bc, gain, m2) : 0ull;
+    if ((F & kScanBatch) && a.ggain) {   // batch: per-graph totals, one atomic per graph met by the wavefront
         int gk = valid ? a.g.gid[i] : 0;
         wave_add_u64_by_key(a.ggain, gk, cg, lead && mv);
         wave_add_u64_by_key(a.gmoved, gk, 1ull, lead && mv);
@@ -412,13 +465,13 @@ __device__ void small_unit(const MoveArgs &a, int bin, int G, int64_t unit, int 
     if (lead) {
         acc.verts++;
         acc.scanned += (unsigned long long)di;
-        if (a.hbits) record_scan(a, m2, i, d, di, ki, kid, bg, bc, mv);
+        if ((F & kScanHist) && a.hbits) record_scan(a, m2, i, d, di, ki, kid, bg, bc, mv);
         a.dec[i] = mv ? bc : d;
         if (mv) {
             acc.gain += cg;
             acc.moved++;
         }
-        if (a.gain_out) a.gain_out[i] = mv ? gain : 0.0;
+        if ((F & kScanOther) && a.gain_out) a.gain_out[i] = mv ? gain : 0.0;
     }
     wave_lds_sync();
 }
@@ -433,7 +486,7 @@ struct SmallLds {
 };
 
 // The small bins' share of workgroup `part` of `parts`.
-template <int WT>
+template <int WT, int F>
 __device__ __forceinline__ void scan_small(const MoveArgs &a, SmallLds &lds, int part, int parts) {
     int *tkeys = lds.keys;
     double *tvals = lds.vals;
@@ -459,7 +512,7 @@ __device__ __forceinline__ void scan_small(const MoveArgs &a, SmallLds &lds, int
     for (int64_t u = (int64_t)part * (kBlock / kWave) + w; u < pre[kNumSmallBins]; u += nw) {
         int b = 0;
         while (u >= pre[b + 1]) b++;
-        small_unit<WT>(a, b, 4 << b, u - pre[b], cnt[b], wkeys, wvals, acc);
+        small_unit<WT, F>(a, b, 4 << b, u - pre[b], cnt[b], wkeys, wvals, acc);
     }
     flush_acc(acc, a.ctr, 0);
 }
@@ -467,7 +520,7 @@ __device__ __forceinline__ void scan_small(const MoveArgs &a, SmallLds &lds, int
 template <int WT>
 __global__ void __launch_bounds__(kBlock, WT == W_UNIT ? 5 : 4) k_move_small(MoveArgs a) {
     __shared__ SmallLds lds;
-    scan_small<WT>(a, lds, blockIdx.x, gridDim.x);
+    scan_small<WT, kScanAll>(a, lds, blockIdx.x, gridDim.x);
 }
 
 // ---------------------------------------------------------------- large
@@ -537,7 +590,7 @@ template <int WT> struct BlockLds {
 
 // One wavefront per vertex of 65..512 entries, table in its LDS: workgroup
 // `part` of `parts`.
-template <int WT>
+template <int WT, int F>
 __device__ __forceinline__ void scan_wave(const MoveArgs &a, WaveLds<WT> &lds, int part, int parts) {
     using V = typename TabVal<WT>::T;
     constexpr int S = WaveLds<WT>::S;
@@ -554,7 +607,7 @@ __device__ __forceinline__ void scan_wave(const MoveArgs &a, WaveLds<WT> &lds, i
     Acc acc;
     for (int64_t qi = (int64_t)part * (kBlock / kWave) + w; qi < cnt; qi += nw) {
         int i = a.queue[a.qbase[BIN_WAVE] + qi];
-        const double m2 = m2_of(a, i);
+        const double m2 = m2_of<F>(a, i);
         int di = a.g.deg[i];
         int64_t beg = a.g.off[i];
         int d = a.cm[i];
@@ -589,19 +642,19 @@ __device__ __forceinline__ void scan_wave(const MoveArgs &a, WaveLds<WT> &lds, i
         if (mv)   // the lane's columns are still in registers (weights reloaded)
 #pragma unroll
             for (int r = 0; r < R; r++)
-                if (jj[r] != i) mark_neighbour(a, jj[r], a.dmoved ? edge_weight<WT>(a.g.w, beg + lane + r * kWave) : 0.0);
+                if (jj[r] != i) mark_neighbour<F>(a, jj[r], (F & kScanHist) && a.dmoved ? edge_weight<WT>(a.g.w, beg + lane + r * kWave) : 0.0);
         if (lane == 0) {
             acc.verts++;
             acc.scanned += (unsigned long long)di;
-            if (a.hbits) record_scan(a, m2, i, d, di, ki, kid, bg, bc, mv);
+            if ((F & kScanHist) && a.hbits) record_scan(a, m2, i, d, di, ki, kid, bg, bc, mv);
             a.dec[i] = mv ? bc : d;
             if (mv) {
-                const unsigned long long cg = counted_gain(a, i, d, bc, gain, m2);
+                const unsigned long long cg = counted_gain<F>(a, i, d, bc, gain, m2);
                 acc.gain += cg;
                 acc.moved++;
-                if (a.ggain) graph_totals(a, i, cg);
+                if ((F & kScanBatch) && a.ggain) graph_totals(a, i, cg);
             }
-            if (a.gain_out) a.gain_out[i] = mv ? gain : 0.0;
+            if ((F & kScanOther) && a.gain_out) a.gain_out[i] = mv ? gain : 0.0;
         }
         wave_lds_sync();
     }
@@ -611,12 +664,12 @@ __device__ __forceinline__ void scan_wave(const MoveArgs &a, WaveLds<WT> &lds, i
 template <int WT>
 __global__ void __launch_bounds__(kBlock, 4) k_move_wave(MoveArgs a) {
     __shared__ WaveLds<WT> lds;
-    scan_wave<WT>(a, lds, blockIdx.x, gridDim.x);
+    scan_wave<WT, kScanAll>(a, lds, blockIdx.x, gridDim.x);
 }
 
 // One workgroup per vertex of 513..2048 entries, table in LDS: workgroup
 // `part` of `parts`.
-template <int WT>
+template <int WT, int F>
 __device__ __forceinline__ void scan_block(const MoveArgs &a, BlockLds<WT> &lds, int part, int parts) {
     using V = typename TabVal<WT>::T;
     constexpr int S = BlockLds<WT>::S;
@@ -632,7 +685,7 @@ __device__ __forceinline__ void scan_block(const MoveArgs &a, BlockLds<WT> &lds,
     Acc acc;
     for (int64_t qi = part; qi < cnt; qi += parts) {
         int i = a.queue[a.qbase[BIN_BLOCK] + qi];
-        const double m2 = m2_of(a, i);
+        const double m2 = m2_of<F>(a, i);
         int di = a.g.deg[i];
         int64_t beg = a.g.off[i];
         int d = a.cm[i];
@@ -664,19 +717,19 @@ __device__ __forceinline__ void scan_block(const MoveArgs &a, BlockLds<WT> &lds,
         if (mv)   // the thread's columns are still in registers (weights reloaded)
 #pragma unroll
             for (int r = 0; r < R; r++)
-                if (jj[r] != i) mark_neighbour(a, jj[r], a.dmoved ? edge_weight<WT>(a.g.w, beg + tid + r * kBlock) : 0.0);
+                if (jj[r] != i) mark_neighbour<F>(a, jj[r], (F & kScanHist) && a.dmoved ? edge_weight<WT>(a.g.w, beg + tid + r * kBlock) : 0.0);
         if (tid == 0) {
             acc.verts++;
             acc.scanned += (unsigned long long)di;
-            if (a.hbits) record_scan(a, m2, i, d, di, ki, kid, bg, bc, mv);
+            if ((F & kScanHist) && a.hbits) record_scan(a, m2, i, d, di, ki, kid, bg, bc, mv);
             a.dec[i] = mv ? bc : d;
             if (mv) {
-                const unsigned long long cg = counted_gain(a, i, d, bc, gain, m2);
+                const unsigned long long cg = counted_gain<F>(a, i, d, bc, gain, m2);
                 acc.gain += cg;
                 acc.moved++;
-                if (a.ggain) graph_totals(a, i, cg);
+                if ((F & kScanBatch) && a.ggain) graph_totals(a, i, cg);
             }
-            if (a.gain_out) a.gain_out[i] = mv ? gain : 0.0;
+            if ((F & kScanOther) && a.gain_out) a.gain_out[i] = mv ? gain : 0.0;
         }
         __syncthreads();
     }
@@ -686,7 +739,7 @@ __device__ __forceinline__ void scan_block(const MoveArgs &a, BlockLds<WT> &lds,
 template <int WT>
 __global__ void __launch_bounds__(kBlock, 4) k_move_block(MoveArgs a) {
     __shared__ BlockLds<WT> lds;
-    scan_block<WT>(a, lds, blockIdx.x, gridDim.x);
+    scan_block<WT, kScanAll>(a, lds, blockIdx.x, gridDim.x);
 }
 
 // The three scans above in one launch: workgroups [0, nb) take the workgroup
@@ -702,16 +755,16 @@ template <int WT> union ScanLds {
     BlockLds<WT> block;
 };
 
-template <int WT>
+template <int WT, int F>
 __global__ void __launch_bounds__(kBlock, 4) k_move_scan(MoveArgs a, int nb, int nw) {
     __shared__ ScanLds<WT> lds;
     const int k = blockIdx.x;
     if (k < nb)
-        scan_block<WT>(a, lds.block, k, nb);
+        scan_block<WT, F>(a, lds.block, k, nb);
     else if (k < nb + nw)
-        scan_wave<WT>(a, lds.wave, k - nb, nw);
+        scan_wave<WT, F>(a, lds.wave, k - nb, nw);
     else
-        scan_small<WT>(a, lds.small, k - nb - nw, gridDim.x - nb - nw);
+        scan_small<WT, F>(a, lds.small, k - nb - nw, gridDim.x - nb - nw);
 }
 
 // ---------------------------------------------------------------- hubs
@@ -1403,12 +1456,22 @@ void launch_move_scan(const MoveArgs &a, hipStream_t s) {
     const int ns = units ? (int)cap_grid((units + 3) / 4, sched_cap(a, 8192)) : 0;
     const int gr = nb + nw + ns;
     if (gr == 0) return;
+    const int f = (a.g.gid ? kScanBatch : 0) | (a.hbits || a.dmoved ? kScanHist : 0) |
+                  (a.mhist || a.gain_out ? kScanOther : 0);
+    auto go = [&](auto none, auto batch, auto all) {
+        if (f == 0)
+            none<<<gr, kBlock, 0, s>>>(a, nb, nw);
+        else if (f == kScanBatch)
+            batch<<<gr, kBlock, 0, s>>>(a, nb, nw);
+        else
+            all<<<gr, kBlock, 0, s>>>(a, nb, nw);
+    };
     if (a.g.wt == W_UNIT)
-        k_move_scan<W_UNIT><<<gr, kBlock, 0, s>>>(a, nb, nw);
+        go(k_move_scan<W_UNIT, 0>, k_move_scan<W_UNIT, kScanBatch>, k_move_scan<W_UNIT, kScanAll>);
     else if (a.g.wt == W_F32)
-        k_move_scan<W_F32><<<gr, kBlock, 0, s>>>(a, nb, nw);
+        go(k_move_scan<W_F32, 0>, k_move_scan<W_F32, kScanBatch>, k_move_scan<W_F32, kScanAll>);
     else
-        k_move_scan<W_F64><<<gr, kBlock, 0, s>>>(a, nb, nw);
+        go(k_move_scan<W_F64, 0>, k_move_scan<W_F64, kScanBatch>, k_move_scan<W_F64, kScanAll>);
 }
 
 void launch_move_hub_scan(const MoveArgs &a, hipStream_t s) {
