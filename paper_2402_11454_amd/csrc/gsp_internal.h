@@ -301,7 +301,8 @@ void launch_move_apply(const MoveArgs &a, int64_t cap, hipStream_t s);
 void launch_move_apply_compact(const MoveArgs &a, const MoveArgs &next, const WorkLists &wl, hipStream_t s);
 
 // ---- k_rest.hip ----
-// The rest of a run on a small level, a workgroup per graph: every remaining
+// The rest of a run on a small level (at most kRestVertices vertices and
+// rest_entries of them), a workgroup per graph: every remaining
 // pass of the level (or, of a batch, of graphs which[0..graphs)) with plain
 // pruning, the split in every pass and no options beyond those below.
 // label[v] <- the number of v's final community (from 0 within its graph,
@@ -309,7 +310,13 @@ void launch_move_apply_compact(const MoveArgs &a, const MoveArgs &next, const Wo
 // fit (vertices, entries, a row beyond kBlockMaxDeg entries) or takes
 // more than kRestPasses passes; nothing of the graph has changed then.
 constexpr int kRestVertices = 1536;
-constexpr int kRestEntries = 65535;
+// Entries a level of n vertices may have: four times as many where every
+// wavefront has a dense table over the communities (measured: levels of 316
+// and 404 vertices with 98k and 150k entries take 0.35 ms through all their
+// passes against 0.66 ms per pass in level-wide kernels; one of 1,058 with
+// 455k, seven dense tables, 1.4 ms longer than those).
+constexpr int kRestDense = 512;
+__host__ __device__ inline int64_t rest_entries(int64_t n) { return n <= kRestDense ? 262144 : 65536; }
 constexpr int kRestPasses = 64;
 struct RestOut {
     int status, passes, ncomm, sweeps;

@@ -1,5 +1,5 @@
 // k_rest.hip - the rest of a run on small levels: once a graph's level has at
-// most kRestVertices vertices and kRestEntries entries, one workgroup takes
+// most kRestVertices vertices and rest_entries entries, one workgroup takes
 // it through every remaining pass of Algorithm "louvain" (local moving, split,
 // renumbering, the pass tests, aggregation) with the level's state in LDS.
 //
@@ -14,7 +14,7 @@
 // which share one LDS) and 15 us for its split and aggregation.  Whole runs:
 // 1,013 vertices 2.60 -> 0.54 ms, 10,000 vertices (the first level goes
 // through the level-wide kernels) 3.80 -> 1.84 ms.  The entries stay in
-// memory, read once per scan; beyond kRestEntries the one compute unit's rate
+// memory, read once per scan; beyond rest_entries the one compute unit's rate
 // costs more than the launches do, and beyond kRestVertices the state does
 // not fit the LDS.
 //
@@ -34,8 +34,10 @@ constexpr int kSlots = 8192;             // table slots of the workgroup
 constexpr int kWaveSlots = kSlots / kWaves;
 // Rows by length: up to 32 entries eight lanes, up to 64 sixteen, up to kRowC
 // a wavefront, each with eight table slots per lane (half full, the
-// wavefront's two thirds); longer ones the whole workgroup, with a dense
-// table over the communities.
+// wavefront's two thirds); longer ones a wavefront with a dense table over
+// the communities, which up to kWaveSlots of them every wavefront has (the
+// shorter wavefront rows then take it too: no compare-and-swaps), beyond as
+// many wavefronts as the pool has room for.
 constexpr int kClasses = 4;
 constexpr int kPerLane = 8;
 constexpr int kRow8 = 32, kRow16 = 64, kRowC = kWaveSlots * 2 / 3;
@@ -48,7 +50,7 @@ struct Pool {   // scans: hash tables; split: parents; aggregation: dense rows
     double vals[kSlots];
     int keys[kSlots];
 };
-static_assert(kN <= kSlots && kDense <= kSlots, "pool views");
+static_assert(kN <= kSlots && kDense <= kSlots && kRestDense <= kWaveSlots, "pool views");
 
 struct State {
     Pool pool;
@@ -62,11 +64,8 @@ struct State {
     uint8_t rnd[kN];           // sub-round (255: no entries)
     int beg[kMaxRounds * kClasses + 1];
     int wi[kWaves];
-    double wg[kWaves], wk[kWaves];
-    int wc[kWaves];
     unsigned long long gain, verts, scanned[3];
     unsigned moved;            // at most 64 passes of 100 sweeps of kN
-    uint32_t bits[kN / 32];
     int bad;
 };
 
@@ -193,76 +192,71 @@ __device__ __noinline__ void scan_rows(const int32_t *col, const double *w, int 
     __builtin_amdgcn_wave_barrier();
 }
 
-// The longest rows, list[k0 .. k1), the whole workgroup each: sums and
-// presence bits per community of the level (a community met through entries
-// of weight 0 only is a candidate too).  The pool's values are 0 and the
-// bits clear on entry and on return.
-__device__ __noinline__ void scan_long(const int32_t *col, const double *w, int k0, int k1, int n, double m2) {
+// Scan of row list[k] by a wavefront with a dense table over the level's n
+// communities at slot `at` of the pool: no probing, any row length.  A key
+// marks a community as met (one met through entries of weight 0 only is a
+// candidate too).  Keys are empty and values 0 on entry and on return.
+__device__ __noinline__ void scan_dense(const int32_t *col, const double *w, int k, int at, int n, double m2) {
     State &s = state();
-    const int tid = threadIdx.x, wv = tid / kWave;
-    double *acc = s.pool.vals;
-    for (int k = k0; k < k1; k++) {
-        const int i = s.list[k];
-        if (!s.flag[i]) continue;   // the same in every thread
-        const int di = s.deg[i];
-        const int64_t b = s.rowb[i];
-        for (int e = tid; e < di; e += kT) {
-            const int j = col[b + e];
-            if (j == i) continue;
-            const int c = s.cm[j];
-            atomicAdd(&acc[c], w[b + e]);
-            atomicOr(&s.bits[c >> 5], 1u << (c & 31));
+    const int lane = lane_id();
+    int *keys = s.pool.keys + at;
+    double *vals = s.pool.vals + at;
+    const int i = s.list[k];
+    if (!s.flag[i]) return;   // the same in every lane
+    const int di = s.deg[i];
+    const int64_t b = s.rowb[i];
+    constexpr int R = 8;
+    for (int e0 = 0; e0 < di; e0 += R * kWave) {
+        int j[R];
+        double x[R];
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const int e = e0 + r * kWave + lane;
+            j[r] = e < di ? col[b + e] : i;
+            x[r] = e < di ? w[b + e] : 0.0;
         }
-        __syncthreads();
-        const int d = s.cm[i];
-        const double ki = s.K[i];
-        double bg = -INFINITY, kid = 0.0;
-        int bc = kIntMax;
-        for (int c = tid; c < n; c += kT) {
-            if (!((s.bits[c >> 5] >> (c & 31)) & 1u)) continue;
-            const double v = acc[c];
-            acc[c] = 0.0;
-            if (c == d)
-                kid = v;
-            else
-                offer(m2 * v - ki * s.sig[c], c, bg, bc);
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            if (j[r] == i) continue;
+            const int c = s.cm[j[r]];
+            keys[c] = c;
+            atomicAdd(&vals[c], x[r]);
         }
-        const double top = group_max<kWave>(bg);
-        bc = group_min<kWave>(bg == top ? bc : kIntMax);
-        bg = top;
-        kid = group_max<kWave>(kid);
-        if (lane_id() == 0) {
-            s.wg[wv] = bg;
-            s.wc[wv] = bc;
-            s.wk[wv] = kid;
-        }
-        __syncthreads();
-        if (tid < kN / 32) s.bits[tid] = 0;
-        if (tid == 0) {
-            for (int q = 1; q < kWaves; q++) {
-                offer(s.wg[q], s.wc[q], bg, bc);
-                kid += s.wk[q];
-            }
-            bool mv = false;
-            if (bc != kIntMax) {
-                const double gstay = m2 * kid - ki * (s.sig[d] - ki);
-                mv = bg > gstay && !(bc > d && s.csz[d] == 1 && s.csz[bc] == 1);
-                if (mv) {
-                    atomicAdd(&s.gain, gain_units(bg - gstay, m2));
-                    atomicAdd(&s.moved, 1u);
-                }
-            }
-            s.dec[i] = (uint16_t)(mv ? bc : d);
-            s.wi[0] = mv;
-        }
-        __syncthreads();
-        if (s.wi[0])
-            for (int e = tid; e < di; e += kT) {
-                const int j = col[b + e];
-                if (j != i) s.next[j] = 1;
-            }
-        __syncthreads();
     }
+    __builtin_amdgcn_wave_barrier();
+    const int d = s.cm[i];
+    const double ki = s.K[i], sgd = s.sig[d];
+    double bg = -INFINITY, kid = 0.0;
+    int bc = kIntMax;
+    for (int c = lane; c < n; c += kWave) {
+        if (keys[c] == kEmpty) continue;
+        const double v = vals[c];
+        keys[c] = kEmpty;
+        vals[c] = 0.0;
+        if (c == d)
+            kid = v;
+        else
+            offer(m2 * v - ki * s.sig[c], c, bg, bc);
+    }
+    const double top = group_max<kWave>(bg);
+    bc = group_min<kWave>(bg == top ? bc : kIntMax);
+    kid = group_max<kWave>(kid);
+    bool mv = false;
+    if (bc != kIntMax) {
+        const double gstay = m2 * kid - ki * (sgd - ki);
+        mv = top > gstay && !(bc > d && s.csz[d] == 1 && s.csz[bc] == 1);
+        if (mv && lane == 0) {
+            atomicAdd(&s.gain, gain_units(top - gstay, m2));
+            atomicAdd(&s.moved, 1u);
+        }
+    }
+    if (lane == 0) s.dec[i] = (uint16_t)(mv ? bc : d);
+    if (mv)
+        for (int e = lane; e < di; e += kWave) {
+            const int j = col[b + e];
+            if (j != i) s.next[j] = 1;
+        }
+    __builtin_amdgcn_wave_barrier();
 }
 
 // The local-moving phase; returns l_i (the same in every thread).
@@ -275,7 +269,8 @@ __device__ __noinline__ int move_phase(int shift, int max_iter, const int32_t *c
         s.pool.keys[q] = kEmpty;
         s.pool.vals[q] = 0.0;
     }
-    if (tid < kN / 32) s.bits[tid] = 0;
+    const bool dense = n <= kRestDense;
+    const int room = kSlots / n < kWaves ? kSlots / n : kWaves;   // wavefronts with a dense table
     for (int q = tid; q <= P * kClasses; q += kT) s.beg[q] = 0;
     __syncthreads();
     auto bucket = [&](int i) {   // (sub-round, class) of a vertex with entries
@@ -303,7 +298,7 @@ __device__ __noinline__ int move_phase(int shift, int max_iter, const int32_t *c
         if (s.deg[i]) s.list[atomicAdd(&s.beg[bucket(i)], 1)] = (uint16_t)i;
     __syncthreads();
     // the cursors now stand at the buckets' ends: bucket k is [end[k - 1], end[k])
-    unsigned verts = 0, sc[3] = {0, 0, 0};   // at most 100 sweeps of kRestEntries
+    unsigned verts = 0, sc[3] = {0, 0, 0};   // at most 100 sweeps of rest_entries
     int li = 0;
     while (li < max_iter) {
         if (tid == 0) s.gain = 0;
@@ -312,17 +307,23 @@ __device__ __noinline__ int move_phase(int shift, int max_iter, const int32_t *c
             const int k0 = p ? s.beg[p * kClasses - 1] : 0, k1 = s.beg[p * kClasses], k2 = s.beg[p * kClasses + 1],
                       k3 = s.beg[p * kClasses + 2], k4 = s.beg[p * kClasses + 3];
             if (k0 == k4) continue;   // the same in every thread
-            const int u8 = (k1 - k0 + 7) / 8, u16 = u8 + (k2 - k1 + 3) / 4, uw = u16 + (k3 - k2);
+            const int kw = dense ? k4 : k3;   // wavefront rows
+            const int u8 = (k1 - k0 + 7) / 8, u16 = u8 + (k2 - k1 + 3) / 4, uw = u16 + (kw - k2);
             for (int u = wv; u < uw; u += kWaves) {
                 if (u < u8)
                     scan_rows<8, 4>(col, w, k0 + 8 * u, k1, m2);
                 else if (u < u16)
                     scan_rows<16, 4>(col, w, k1 + 4 * (u - u8), k2, m2);
+                else if (dense)
+                    scan_dense(col, w, k2 + (u - u16), wv * kWaveSlots, n, m2);
                 else
                     scan_rows<kWave, (kRowC + kWave - 1) / kWave>(col, w, k2 + (u - u16), k3, m2);
             }
             __syncthreads();
-            if (k4 > k3) scan_long(col, w, k3, k4, n, m2);
+            if (k4 > kw) {   // the tables change shape
+                for (int k = kw + wv; wv < room && k < k4; k += room) scan_dense(col, w, k, wv * n, n, m2);
+                __syncthreads();
+            }
             // the moves, and the flags: a scanned vertex is processed unless
             // a mover marked it in this very sub-round
             for (int i = tid; i < n; i += kT) {
@@ -553,7 +554,7 @@ __global__ void __launch_bounds__(kT) k_rest_of_run(RestArgs a) {
         }
     if (ent) atomicAdd(&s.gain, ent);
     __syncthreads();
-    if (s.bad || s.gain > kRestEntries) {
+    if (s.bad || s.gain > (unsigned long long)rest_entries(nv)) {
         if (tid == 0) out->status = 1;
         return;
     }

@@ -160,6 +160,13 @@ SMALL = {
     "n1537": lambda: _dense(1537, 8 / 1537, True, 2),
     "entries": lambda: _dense(1500, 42 / 1500, False, 3),
     "over": lambda: _dense(1500, 46 / 1500, False, 4),
+    # up to 512 vertices every wavefront has a dense table (and four times
+    # the entries fit); beyond, rows of more than 341 entries share a few
+    "complete512": lambda: _dense(512, 12.0, True, 11),
+    "complete513": lambda: _dense(513, 12.0, True, 12),
+    "long-rows": lambda: gi.sbm(150, 1, 0.9, 0.9, 3, weights=(1.0, 4.0)),
+    "hubs600": lambda: _csr(600, np.repeat(np.arange(40), 599), np.concatenate(
+        [np.setdiff1d(np.arange(600), [i]) for i in range(40)]), True, 13),
     # rows around the classes' ends: 64 / 65, 341 / 342 entries, a star
     "rows64": lambda: _dense(900, 64 / 900, True, 5, loops=True),
     "rows341": lambda: gi.sbm(180, 2, 0.97, 0.9, 3, weights=(1.0, 4.0)),
