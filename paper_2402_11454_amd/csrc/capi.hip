@@ -97,6 +97,8 @@ struct gsp_ctx {
     };
     std::vector<SweepGraph> sweep_graphs;
     void drop_sweep_graphs() {
+        // a sweep's result is awaited inside its last kernel
+        if (!sweep_graphs.empty() && stream) (void)hipStreamSynchronize(stream);
         for (auto &x : sweep_graphs) (void)hipGraphExecDestroy(x.exec);
         sweep_graphs.clear();
     }
@@ -148,9 +150,10 @@ struct gsp_ctx {
     Scratch sc;
     IterCounters *ctr = nullptr;      // device, 2 slots
     IterCounters *ctr_h = nullptr;    // pinned host mirror
+    uint64_t *box = nullptr;          // results for the host (kBoxHead and box_words words), then act_h
+    int64_t box_words = 0;
+    uint8_t *act_h = nullptr;         // pinned: gactive as last copied (box_words bytes)
     int64_t *i64_h = nullptr;         // pinned host scalars
-    RestOut *rest_h = nullptr;        // pinned: the record of run_rest
-    double *f64_h = nullptr;
 
     // learned gate: per-vertex history of the current pass and the gated
     // sweeps' candidate lists (graph-sized, allocated on first use)
@@ -221,6 +224,21 @@ struct gsp_ctx {
                 return;
             }
     }
+    // A box that holds `words`; nothing may be under way.
+    hipError_t ensure_box(int64_t words) {
+        if (words <= box_words) return hipSuccess;
+        if (stream) (void)hipStreamSynchronize(stream);
+        if (box) (void)hipHostFree(box);
+        box = nullptr;
+        box_words = 0;
+        hipError_t e = hipHostMalloc((void **)&box, (kBoxHead + words) * sizeof(uint64_t) + words,
+                                     hipHostMallocCoherent);
+        if (e != hipSuccess) return e;
+        box_words = words;
+        act_h = reinterpret_cast<uint8_t *>(box + kBoxHead + words);
+        sc.box = box;
+        return e;
+    }
     template <class T>
     T *dalloc(size_t count, hipError_t *e) {
         void *p = nullptr;
@@ -241,6 +259,7 @@ struct gsp_ctx {
         if (sc.hvals) (void)hipFree(sc.hvals);
         if (sc.hbuck) (void)hipFree(sc.hbuck);
         sc = Scratch();
+        sc.box = box;
         for (int k = 0; k < 2; k++) {
             offL[k] = nullptr;
             colL[k] = nullptr;
@@ -386,11 +405,10 @@ gsp_status take_membership(gsp_ctx *ctx, const int32_t *memb, int where) {
     if (where != GSP_HOST && where != GSP_DEVICE) return ctx->fail(GSP_EINVAL, "bad `where`");
     gsp_status st = copy_in_i32(ctx, ctx->cm, memb, ctx->n, where);
     if (st != GSP_OK) return st;
-    HIP_TRY(hipMemsetAsync(ctx->sc.err, 0, sizeof(int), ctx->stream));
+    launch_fill_i32(ctx->sc.err, 0, 2, ctx->stream);
     launch_check_labels(ctx->cm, ctx->n, ctx->sc.err, ctx->stream);
-    int bad = 0;
-    HIP_TRY(hipMemcpyAsync(&bad, ctx->sc.err, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
-    HIP_TRY(hipStreamSynchronize(ctx->stream));
+    int64_t bad = 0;
+    HIP_TRY(fetch_i64(reinterpret_cast<const int64_t *>(ctx->sc.err), &bad, ctx->box, ctx->stream));
     if (bad) return ctx->fail(GSP_EINVAL, "membership label outside [0, n)");
     return GSP_OK;
 }
@@ -399,9 +417,7 @@ gsp_status take_membership(gsp_ctx *ctx, const int32_t *memb, int where) {
 // number of labels in use goes to *count (host).
 gsp_status renumber(gsp_ctx *ctx, const int32_t *labels, int64_t n, int32_t *out, int64_t *count) {
     launch_renumber(labels, n, out, ctx->sc.i32a, ctx->sc.i32b, ctx->sc.i64e, ctx->sc.scan_tmp, ctx->stream);
-    HIP_TRY(hipMemcpyAsync(ctx->i64_h, ctx->sc.i64e, sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
-    HIP_TRY(hipStreamSynchronize(ctx->stream));
-    *count = ctx->i64_h[0];
+    HIP_TRY(fetch_i64(ctx->sc.i64e, count, ctx->box, ctx->stream));
     return GSP_OK;
 }
 
@@ -541,7 +557,6 @@ gsp_status move_phase(gsp_ctx *ctx, const Level &g, const double *K, const WorkL
     const bool batch = g.gid != nullptr;
     const int64_t G = batch ? g.graphs : 0;
     std::vector<uint8_t> act;
-    std::vector<unsigned long long> gg, gm;
     // batches: each graph runs the single graph's sweep sequence (gated,
     // confirming, plain) on its own; gmode holds its current mode
     std::vector<uint8_t> gmode, ggated_h, gconfirm_h;
@@ -554,11 +569,15 @@ gsp_status move_phase(gsp_ctx *ctx, const Level &g, const double *K, const WorkL
         act.assign(G, 1);
         for (int64_t k = 0; k < G; k++) act[k] = cfg.gdone && cfg.gdone[k] ? 0 : 1;
         cfg.li_g.assign(G, 0);
-        gg.resize(G);
-        gm.resize(G);
     }
-    // One sweep: clear its counters (a fill kernel, so that the sweep can be
-    // captured), then every sub-round's kernels, on stream cs.
+    // each sweep's end clears the counters for the next
+    launch_fill_u64(reinterpret_cast<unsigned long long *>(ctx->ctr), 0, sizeof(IterCounters) / 8, s);
+    if (batch) {
+        launch_fill_u64(ctx->ggain, 0, G, s);
+        launch_fill_u64(ctx->gmoved, 0, G, s);
+    }
+    // One sweep: every sub-round's kernels, then its totals to the host's box,
+    // on stream cs.
     // Sweeps repeat the same launches with the same arguments within a pass
     // (per mode: plain, gated, confirming): each is captured once as a graph
     // and replayed; l_i, the one argument that changes, is read from device
@@ -567,11 +586,6 @@ gsp_status move_phase(gsp_ctx *ctx, const Level &g, const double *K, const WorkL
     const bool capture = cfg.use_graphs && !ctx->tracing && !cfg.timing_k;
     auto enqueue_sweep = [&](int sweep, IterCounters *ctr, hipStream_t cs) {
         int64_t *launches = ctx->kernel_launches;
-        launch_fill_u64(reinterpret_cast<unsigned long long *>(ctr), 0, sizeof(IterCounters) / 8, cs);
-        if (batch) {
-            launch_fill_u64(ctx->ggain, 0, G, cs);
-            launch_fill_u64(ctx->gmoved, 0, G, cs);
-        }
         // the sub-rounds with vertices
         std::vector<MoveArgs> subs;
         bool hubs = false;
@@ -738,6 +752,7 @@ gsp_status move_phase(gsp_ctx *ctx, const Level &g, const double *K, const WorkL
                 launches[GSP_K_MOVE_APPLY]++;
             }
         }
+        launch_sweep_end(ctr, ctx->ggain, ctx->gmoved, G, ctx->box, cs);
     };
     std::vector<int64_t> key;
     if (capture) {
@@ -746,7 +761,7 @@ gsp_status move_phase(gsp_ctx *ctx, const Level &g, const double *K, const WorkL
         key = {g.n, g.nnz, g.wt, g.graphs, ptr(g.off), ptr(g.col), ptr(g.w), ptr(g.deg), ptr(g.gid), ptr(g.vbase),
                ptr(K), P, (int64_t)cfg.grid_cap, ptr(wl.bl), ptr(wl.ch_vert), ptr(wl.ch_beg), ptr(wl.hub_off), ptr(ctx->sc.hkeys),
                ptr(ctx->sc.hvals), ptr(ctx->sc.part_g), ptr(ctx->sc.hbuck), (int64_t)(batch ? 1 : 0),
-               ptr(ctx->ggated), ptr(ctx->giter), ptr(g.orig), g.nlong};
+               ptr(ctx->ggated), ptr(ctx->giter), ptr(g.orig), g.nlong, ptr(ctx->box)};
         for (int k = 0; k <= kNumBins * P; k++) key.push_back(wl.boff[k]);
         for (int p = 0; p <= P; p++) key.push_back(wl.ch_poff[p]);
         int64_t m2bits;
@@ -777,7 +792,10 @@ gsp_status move_phase(gsp_ctx *ctx, const Level &g, const double *K, const WorkL
                 any_confirm = any_confirm || gconfirm_h[k];
             }
             if (!any) break;
-            HIP_TRY(hipMemcpyAsync(ctx->gactive, act.data(), G, hipMemcpyHostToDevice, s));
+            if (cfg.sweeps == 0 || memcmp(ctx->act_h, act.data(), G) != 0) {
+                memcpy(ctx->act_h, act.data(), G);
+                HIP_TRY(hipMemcpyAsync(ctx->gactive, ctx->act_h, G, hipMemcpyHostToDevice, s));
+            }
             if (cfg.gated) {
                 HIP_TRY(hipMemcpyAsync(ctx->ggated, ggated_h.data(), G, hipMemcpyHostToDevice, s));
                 HIP_TRY(hipMemcpyAsync(ctx->giter, giter_h.data(), G * sizeof(int32_t), hipMemcpyHostToDevice, s));
@@ -801,11 +819,14 @@ gsp_status move_phase(gsp_ctx *ctx, const Level &g, const double *K, const WorkL
             launch_fill_u8(ctx->flag, 1, g.n, s);
             cfg.confirm_sweeps++;
         }
-        IterCounters *ctr = capture ? ctx->ctr : ctx->ctr + (sweep & 1);
-        // l_i (the gate's feature) and the sweep index, read by the kernels
-        ctx->i64_h[6] = li;
-        ctx->i64_h[7] = sweep;
-        HIP_TRY(hipMemcpyAsync(ctx->iter_dev, &ctx->i64_h[6], 2 * sizeof(int64_t), hipMemcpyHostToDevice, s));
+        IterCounters *ctr = ctx->ctr;
+        if (hist || cfg.return_moves) {
+            // l_i (the gate's feature) and the sweep index, read by the kernels
+            ctx->i64_h[6] = li;
+            ctx->i64_h[7] = sweep;
+            HIP_TRY(hipMemcpyAsync(ctx->iter_dev, &ctx->i64_h[6], 2 * sizeof(int64_t), hipMemcpyHostToDevice, s));
+        }
+        box_arm(ctx->box);
         if (capture) {
             std::vector<int64_t> km = key;
             km.push_back((int64_t)mode);
@@ -828,27 +849,10 @@ gsp_status move_phase(gsp_ctx *ctx, const Level &g, const double *K, const WorkL
             enqueue_sweep(sweep, ctr, s);
         }
         HIP_TRY(hipGetLastError());
-        HIP_TRY(hipMemcpyAsync(ctx->ctr_h, ctr, sizeof(IterCounters), hipMemcpyDeviceToHost, s));
-        if (batch) {
-            HIP_TRY(hipMemcpyAsync(gg.data(), ctx->ggain, G * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
-            HIP_TRY(hipMemcpyAsync(gm.data(), ctx->gmoved, G * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
-        }
-        HIP_TRY(hipStreamSynchronize(s));
+        HIP_TRY(box_wait(ctx->box, s));
+        const uint64_t *res = ctx->box + kBoxHead, *gg = res + kSweepWords + 1, *gm = gg + G;
         CounterStripe h;
-        memset(&h, 0, sizeof(h));
-        for (int q = 0; q < kStripes; q++) {
-            const CounterStripe &x = ctx->ctr_h->st[q];
-            h.gain += x.gain;   // integer units: exact, in any order
-            h.moved += x.moved;
-            h.pruned += x.pruned;
-            for (int c = 0; c < kMoveClasses; c++) {
-                h.verts[c] += x.verts[c];
-                h.scanned[c] += x.scanned[c];
-                h.keys[c] += x.keys[c];
-                h.ginserts[c] += x.ginserts[c];
-                h.aux[c] += x.aux[c];
-            }
-        }
+        memcpy(&h, res, kSweepWords * sizeof(uint64_t));
         const double dq = ldexp((double)h.gain, -61);   // the movers' delta-modularity (gain_units)
         ctx->stats.moves += (int64_t)h.moved;
         cfg.pruned += (int64_t)h.pruned;
@@ -862,9 +866,7 @@ gsp_status move_phase(gsp_ctx *ctx, const Level &g, const double *K, const WorkL
         if (mode == GATED && cfg.kernel_bytes) {
             // per candidate: vertex id, degree, K, membership, Sigma, history
             // (9 B) in; queue slot out
-            int64_t nc = 0;
-            for (int p = 0; p < P; p++)
-                for (int b = 0; b < kNumBins; b++) nc += ctx->ctr_h->ccnt[p][b];
+            const int64_t nc = (int64_t)res[kSweepWords];
             cfg.kernel_bytes[GSP_K_GATE] += 41.0 * (double)nc;
             ctx->stats.kernels[GSP_K_GATE].items += nc;
         }
@@ -970,9 +972,7 @@ gsp_status refine_level(gsp_ctx *ctx, const Level &g, const double *K, const Wor
     // aggregation's rows) is idle here: a byte per entry of g
     HIP_TRY(bound_subgraph(g, wl, ctx->bnd, ctx->degL[slot], ctx->offL[slot], ctx->colL[slot], ctx->wL[slot],
                            ctx->sc.cch_k0, reinterpret_cast<uint8_t *>(ctx->gap_col), ctx->sc.scan_tmp, s));
-    HIP_TRY(hipMemcpyAsync(ctx->i64_h, ctx->offL[slot] + g.n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    r.nnz = ctx->i64_h[0];
+    HIP_TRY(fetch_i64(ctx->offL[slot] + g.n, &r.nnz, ctx->box, s));
     WorkLists wr = make_lists(ctx);
     HIP_TRY(build_work_lists(r, rounds, wr, ctx->sc, s));
     pc.single_only = true;
@@ -1157,7 +1157,7 @@ gsp_status load_impl(gsp_ctx *ctx, int64_t n, int64_t nnz, const int64_t *off64,
     if ((st = A(sc.part_g, sc.ch_cap, "hipMalloc(hub partials)")) != GSP_OK) return st;
     if ((st = A(sc.part_kid, sc.ch_cap, "hipMalloc(hub partials)")) != GSP_OK) return st;
     if ((st = A(sc.part_c, sc.ch_cap, "hipMalloc(hub partials)")) != GSP_OK) return st;
-    if ((st = A(ctx->ctr, 2, "hipMalloc(iteration counters)")) != GSP_OK) return st;
+    if ((st = A(ctx->ctr, 1, "hipMalloc(iteration counters)")) != GSP_OK) return st;
     if ((st = A(ctx->lp_counts, 4, "hipMalloc(split counters)")) != GSP_OK) return st;
 
     // copy in
@@ -1171,11 +1171,10 @@ gsp_status load_impl(gsp_ctx *ctx, int64_t n, int64_t nnz, const int64_t *off64,
     if (nnz) HIP_TRY(hipMemcpyAsync(ctx->col0, cols, nnz * sizeof(int32_t), kind, s));
     if (wt == W_F32 && nnz) HIP_TRY(hipMemcpyAsync(ctx->w0, weights, nnz * sizeof(float), kind, s));
     if (wt == W_F64 && nnz) HIP_TRY(hipMemcpyAsync(ctx->w0, weights, nnz * sizeof(double), kind, s));
-    HIP_TRY(hipMemsetAsync(sc.err, 0, sizeof(int), s));
+    launch_fill_i32(sc.err, 0, 2, s);
     launch_validate(ctx->off0, ctx->col0, ctx->w0, wt, n, nnz, sc.err, s);
-    int bad = 0;
-    HIP_TRY(hipMemcpyAsync(&bad, sc.err, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    int64_t bad = 0;
+    HIP_TRY(fetch_i64(reinterpret_cast<const int64_t *>(sc.err), &bad, ctx->box, s));
     if (bad) {
         ctx->free_graph();
         std::string m = "malformed CSR:";
@@ -1196,32 +1195,29 @@ gsp_status load_impl(gsp_ctx *ctx, int64_t n, int64_t nnz, const int64_t *off64,
         unsigned long long *u = sc.u64;
         launch_fill_u64(u, 0, 3, s);
         launch_weight_max(ctx->w0, wt, nnz, u, s);
-        HIP_TRY(hipMemcpyAsync(ctx->i64_h, u, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
+        const int64_t *res = reinterpret_cast<const int64_t *>(u);
+        int64_t word = 0;
+        HIP_TRY(fetch_i64(res, &word, ctx->box, s));
         double wmax = 0.0;
-        memcpy(&wmax, ctx->i64_h, sizeof(double));
+        memcpy(&wmax, &word, sizeof(double));
         if (wmax > 0.0) {
             int ew = 0;
             (void)std::frexp(wmax, &ew);
             const int T = 62 - bit_length((uint64_t)nnz) - ew;
             launch_weight_bound(ctx->w0, wt, nnz, T, u + 1, s);
-            HIP_TRY(hipMemcpyAsync(ctx->i64_h, u + 1, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-            HIP_TRY(hipStreamSynchronize(s));
-            const int S = std::min(1022, std::max(-1000, 52 - bit_length((uint64_t)ctx->i64_h[0]) + T));
+            HIP_TRY(fetch_i64(res + 1, &word, ctx->box, s));
+            const int S = std::min(1022, std::max(-1000, 52 - bit_length((uint64_t)word) + T));
             launch_weight_grid(ctx->w0, wt, nnz, S, u + 2, s);
-            HIP_TRY(hipMemcpyAsync(ctx->i64_h, u + 2, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-            HIP_TRY(hipStreamSynchronize(s));
+            HIP_TRY(fetch_i64(res + 2, &ctx->grid_moved, ctx->box, s));
             ctx->grid_S = S;
-            ctx->grid_moved = ctx->i64_h[0];
         }
     }
-    HIP_TRY(hipMemsetAsync(sc.f64, 0, sizeof(double), s));
+    launch_fill_f64(sc.f64, 0.0, 1, s);
     Level g = level0(ctx);
     launch_vertex_weights(g, ctx->K0, sc.f64, s);
-    HIP_TRY(hipMemcpyAsync(ctx->f64_h, sc.f64, sizeof(double), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    HIP_TRY(hipGetLastError());
-    ctx->M2 = ctx->f64_h[0];
+    int64_t m2 = 0;
+    HIP_TRY(fetch_i64(reinterpret_cast<const int64_t *>(sc.f64), &m2, ctx->box, s));
+    memcpy(&ctx->M2, &m2, sizeof(double));
     ctx->loaded = true;
     return GSP_OK;
 }
@@ -1251,11 +1247,14 @@ gsp_status modularity_of(gsp_ctx *ctx, const int32_t *m, double *out) {
         launch_inside_weight(level0(ctx), m, ctx->sc.f64, s);
     }
     launch_sum_squares(ctx->sig, ctx->n, ctx->M2, ctx->sc.u64, s);
-    HIP_TRY(hipMemcpyAsync(ctx->f64_h, ctx->sc.f64, sizeof(double), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(ctx->i64_h, ctx->sc.u64, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    HIP_TRY(hipGetLastError());
-    *out = ctx->f64_h[0] / ctx->M2 - ldexp((double)(uint64_t)ctx->i64_h[0], -62);
+    PostArgs pa;
+    pa.src[0] = ctx->sc.f64;
+    pa.src[1] = ctx->sc.u64;
+    pa.n[0] = pa.n[1] = 1;
+    HIP_TRY(fetch_words(pa, ctx->box, s));
+    double inside = 0.0;
+    memcpy(&inside, ctx->box + kBoxHead, sizeof(double));
+    *out = inside / ctx->M2 - ldexp((double)ctx->box[kBoxHead + 1], -62);
     return GSP_OK;
 }
 
@@ -1342,9 +1341,11 @@ gsp_status gsp_create(int device, void *hip_stream, gsp_ctx **out) {
         ctx->own_stream = true;
     }
     if (hipHostMalloc((void **)&ctx->ctr_h, sizeof(IterCounters), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void **)&ctx->i64_h, 16 * sizeof(int64_t), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void **)&ctx->rest_h, sizeof(RestOut), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void **)&ctx->f64_h, 8 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+        hipHostMalloc((void **)&ctx->i64_h, 16 * sizeof(int64_t), hipHostMallocDefault) != hipSuccess) {
+        gsp_destroy(ctx);
+        return GSP_ENOMEM;
+    }
+    if (ctx->ensure_box(kBoxWords) != hipSuccess) {
         gsp_destroy(ctx);
         return GSP_ENOMEM;
     }
@@ -1361,9 +1362,8 @@ gsp_status gsp_destroy(gsp_ctx *ctx) {
     for (void *p : ctx->persist) (void)hipFree(p);
     ctx->persist.clear();
     if (ctx->ctr_h) (void)hipHostFree(ctx->ctr_h);
+    if (ctx->box) (void)hipHostFree(ctx->box);
     if (ctx->i64_h) (void)hipHostFree(ctx->i64_h);
-    if (ctx->rest_h) (void)hipHostFree(ctx->rest_h);
-    if (ctx->f64_h) (void)hipHostFree(ctx->f64_h);
     if (ctx->own_stream && ctx->stream) (void)hipStreamDestroy(ctx->stream);
     ctx->drop_sweep_graphs();
     if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
@@ -1424,11 +1424,13 @@ gsp_status run_split(gsp_ctx *ctx, const Level &g, const WorkLists &wl, const in
 }
 
 // The rest of a run of at most `left` passes from level g (pass lp, tolerance
-// tau) in one launch; *done = false, and nothing changed, if g does not fit.
+// tau) in one launch, *taken passes; 0, and nothing changed, if g does not fit.
 gsp_status run_rest(gsp_ctx *ctx, const Level &g, const double *K, const gsp_options &opt, double tau, int lp,
-                    int left, int next, bool *done) {
+                    int left, int next, int *taken) {
     hipStream_t s = ctx->stream;
     static_assert(sizeof(RestOut) <= kScratchU64 * sizeof(unsigned long long), "the record fits the counters");
+    static_assert(sizeof(RestOut) % sizeof(uint64_t) == 0 && sizeof(RestOut) / sizeof(uint64_t) <= kBoxWords,
+                  "the record fits the box");
     RestArgs a;
     a.g = g;
     a.K = K;
@@ -1446,12 +1448,14 @@ gsp_status run_rest(gsp_ctx *ctx, const Level &g, const double *K, const gsp_opt
     a.label = ctx->cm;
     a.out = reinterpret_cast<RestOut *>(ctx->sc.u64);
     launch_rest_of_run(a, 1, s);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(ctx->rest_h, a.out, sizeof(RestOut), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    const RestOut &r = *ctx->rest_h;
-    *done = r.status == 0;
-    if (!*done) return GSP_OK;
+    PostArgs pa;
+    pa.src[0] = a.out;
+    pa.n[0] = sizeof(RestOut) / sizeof(uint64_t);
+    HIP_TRY(fetch_words(pa, ctx->box, s));
+    RestOut r;
+    memcpy(&r, ctx->box + kBoxHead, sizeof(r));
+    *taken = r.status == 0 ? r.passes : 0;
+    if (!*taken) return GSP_OK;
     for (int k = 0; k < r.passes && lp + k < GSP_MAX_PASSES_STATS; k++) {
         ctx->stats.iterations[lp + k] = r.iterations[k];
         ctx->stats.vertices[lp + k] = r.vertices[k];
@@ -1530,10 +1534,14 @@ gsp_status run_passes(gsp_ctx *ctx, double tolerance, int32_t max_passes, const 
         launch_fill_f64(ctx->sc.f64, 0.0, 1, s);
         launch_vertex_weights(g, K0, ctx->sc.f64, s);
         if (batch) launch_batch_m2(K0, ctx->vbase0, G, ctx->M2g, s);
-        HIP_TRY(hipMemcpyAsync(ctx->f64_h, ctx->sc.f64, sizeof(double), hipMemcpyDeviceToHost, s));
-        if (batch) HIP_TRY(hipMemcpyAsync(ctx->M2g_h.data(), ctx->M2g, G * sizeof(double), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        ctx->M2 = ctx->f64_h[0];
+        PostArgs pa;
+        pa.src[0] = ctx->sc.f64;
+        pa.n[0] = 1;
+        pa.src[1] = ctx->M2g;
+        pa.n[1] = batch ? G : 0;
+        HIP_TRY(fetch_words(pa, ctx->box, s));
+        memcpy(&ctx->M2, ctx->box + kBoxHead, sizeof(double));
+        if (batch) memcpy(ctx->M2g_h.data(), ctx->box + kBoxHead + 1, G * sizeof(double));
         ctx->timer.end(t);
     }
     const double *K = K0;
@@ -1548,11 +1556,11 @@ gsp_status run_passes(gsp_ctx *ctx, double tolerance, int32_t max_passes, const 
                       opt.hub_global == 0 && opt.hub_max_parts == 0 && ctx->nnz < (int64_t(1) << 32);
     for (int lp = 0; lp < max_passes; lp++) {
         if (rest && !g.orig && g.n <= kRestVertices && g.nnz <= rest_entries(g.n)) {
-            bool done = false;
-            st = run_rest(ctx, g, K, opt, tau, lp, max_passes - lp, next, &done);
+            int taken = 0;
+            st = run_rest(ctx, g, K, opt, tau, lp, max_passes - lp, next, &taken);
             if (st != GSP_OK) return st;
-            if (done) {
-                passes = lp + ctx->rest_h->passes;
+            if (taken) {
+                passes = lp + taken;
                 break;
             }
         }
@@ -1691,10 +1699,13 @@ gsp_status run_passes(gsp_ctx *ctx, double tolerance, int32_t max_passes, const 
             launch_lookup(ctx->top, ctx->n, ctx->cm, s);
             // each graph's communities: [cfirst[k], cfirst[k+1])
             launch_batch_cfirst(ctx->sc.i32b, g.vbase, G, ctx->sc.i64e, ctx->cfirst, s);
-            HIP_TRY(hipMemcpyAsync(cfirst_h.data(), ctx->cfirst, (G + 1) * sizeof(int64_t), hipMemcpyDeviceToHost, s));
-            std::vector<int64_t> vb(G + 1);
-            HIP_TRY(hipMemcpyAsync(vb.data(), g.vbase, (G + 1) * sizeof(int64_t), hipMemcpyDeviceToHost, s));
-            HIP_TRY(hipStreamSynchronize(s));
+            PostArgs pa;
+            pa.src[0] = ctx->cfirst;
+            pa.src[1] = g.vbase;
+            pa.n[0] = pa.n[1] = G + 1;
+            HIP_TRY(fetch_words(pa, ctx->box, s));
+            memcpy(cfirst_h.data(), ctx->box + kBoxHead, (G + 1) * sizeof(int64_t));
+            const int64_t *vb = reinterpret_cast<const int64_t *>(ctx->box + kBoxHead + G + 1);
             bool all = true;
             for (int64_t k = 0; k < G; k++) {
                 if (gdone[k]) continue;
@@ -1893,6 +1904,7 @@ gsp_status gsp_load_batch(gsp_ctx *ctx, int32_t graphs, const int64_t *n, const 
     if (e == hipSuccess) ctx->ggated = ctx->dalloc<uint8_t>(G, &e);
     if (e == hipSuccess) ctx->gconfirm = ctx->dalloc<uint8_t>(G, &e);
     if (e == hipSuccess) ctx->giter = ctx->dalloc<int32_t>(G, &e);
+    if (e == hipSuccess) e = ctx->ensure_box(std::max<int64_t>(kBoxWords, kSweepWords + 2 + 2 * G));
     if (e != hipSuccess) {
         ctx->free_graph();
         return ctx->fail_hip(e, "hipMalloc(batch state)");
@@ -1924,18 +1936,18 @@ gsp_status gsp_get_batch_membership(gsp_ctx *ctx, int32_t graph, int32_t *out, i
     if (check_where(ctx, where) != GSP_OK) return GSP_EINVAL;
     hipStream_t s = ctx->stream;
     int64_t b = ctx->vbase0_h[graph], len = ctx->vbase0_h[graph + 1] - b;
-    int32_t first = 0;
-    HIP_TRY(hipMemcpyAsync(&first, ctx->top + b, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    if (len == 0) return GSP_OK;
     if (where == GSP_DEVICE) {
-        HIP_TRY(hipMemcpyAsync(out, ctx->top + b, len * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-        launch_add_i32(out, len, -first, s);
+        launch_from_first(ctx->top + b, len, out, s);
+        HIP_TRY(hipGetLastError());
     } else {
         HIP_TRY(hipMemcpyAsync(out, ctx->top + b, len * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     }
     HIP_TRY(hipStreamSynchronize(s));
-    if (where == GSP_HOST)
+    if (where == GSP_HOST) {
+        const int32_t first = out[0];
         for (int64_t v = 0; v < len; v++) out[v] -= first;
+    }
     return GSP_OK;
 }
 

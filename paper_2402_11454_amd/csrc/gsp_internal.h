@@ -263,6 +263,38 @@ __device__ __forceinline__ unsigned long long gain_units(double gain, double m2)
     return (unsigned long long)(long long)rint(ldexp((2.0 * gain) / (m2 * m2), 61));
 }
 
+// ---- results for the host ----
+// A box is pinned coherent host memory: box[0] is the flag, the words from
+// box[kBoxHead] are the result.  The host arms the box, a kernel on the
+// stream stores its words and then the flag, and the host waits on the flag
+// itself.  A copy into pinned memory and a stream wait in its place cost
+// about 20 us more per result: run on 15M vertices of degree 2 to 4, 160
+// sweeps, 59.8 -> 56.7 ms; 10k-vertex graph 1.73 -> 1.45 ms.
+// One result is under way at a time; a context owns one box.
+constexpr int kBoxHead = 16;
+constexpr int64_t kBoxWords = 1024;      // words a box holds without a batch's
+static_assert(2 * kNumBuckets <= kBoxWords, "the work lists' counts fit the box");
+void box_arm(uint64_t *box);
+// Waits for the flag.  After 200 us of polling, or on any error of the stream,
+// the stream's own wait decides.  The stream's last kernel may still be ending
+// on return: what is enqueued behind it is ordered, what is freed or destroyed
+// synchronizes first.
+hipError_t box_wait(uint64_t *box, hipStream_t s);
+// Ends a kernel of one workgroup whose threads have stored their words.
+__device__ __forceinline__ void box_post(uint64_t *box) {
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(box, (uint64_t)1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+// Up to four ranges of 64-bit words into the box, one after the other.
+struct PostArgs {
+    const void *src[4] = {nullptr, nullptr, nullptr, nullptr};
+    int64_t n[4] = {0, 0, 0, 0};
+};
+// Arms the box, posts the ranges and waits for them.
+hipError_t fetch_words(const PostArgs &a, uint64_t *box, hipStream_t s);
+hipError_t fetch_i64(const int64_t *src, int64_t *out, uint64_t *box, hipStream_t s);
+
 // ---- k_bins.hip ----
 // Builds the work lists of a level (all buckets of all sub-rounds).
 // Needs a host sync inside (bucket and chunk offsets are copied back).
@@ -278,6 +310,12 @@ hipError_t bin_vertices(const int32_t *deg, int64_t n, int rounds, WorkLists &wl
 void launch_community_totals(const double *K, const int32_t *cm, int64_t n, double *sig, int32_t *csize,
                              hipStream_t s);
 void launch_move_compact(const MoveArgs &a, const WorkLists &wl, hipStream_t s);
+// The end of a sweep: the stripes' sums (as one CounterStripe), the gated
+// candidates' count and, of a batch of G graphs, ggain and gmoved go to the
+// box; all of them are cleared for the next sweep.
+constexpr int kSweepWords = 3 + 5 * kMoveClasses;
+void launch_sweep_end(IterCounters *ctr, unsigned long long *ggain, unsigned long long *gmoved, int64_t G,
+                      uint64_t *box, hipStream_t s);
 void launch_move_small(const MoveArgs &a, const WorkLists &wl, hipStream_t s);
 void launch_move_wave(const MoveArgs &a, hipStream_t s);
 void launch_move_block(const MoveArgs &a, hipStream_t s);
@@ -311,10 +349,11 @@ void launch_move_apply_compact(const MoveArgs &a, const MoveArgs &next, const Wo
 // more than kRestPasses passes; nothing of the graph has changed then.
 constexpr int kRestVertices = 1536;
 // Entries a level of n vertices may have: four times as many where every
-// wavefront has a dense table over the communities (measured: levels of 316
-// and 404 vertices with 98k and 150k entries take 0.35 ms through all their
-// passes against 0.66 ms per pass in level-wide kernels; one of 1,058 with
-// 455k, seven dense tables, 1.4 ms longer than those).
+// wavefront has a dense table over the communities.  Measured on a run over
+// 100k vertices whose levels have 1,058, 404 and 316 of them with 455k, 150k
+// and 98k entries: 5.49 ms with this rule, 5.72 ms with 65,536 throughout (the
+// last two passes in level-wide kernels), 6.97 ms with 524,288 throughout (the
+// first level's rows, too long for seven dense tables to keep up with).
 constexpr int kRestDense = 512;
 __host__ __device__ inline int64_t rest_entries(int64_t n) { return n <= kRestDense ? 262144 : 65536; }
 constexpr int kRestPasses = 64;
@@ -393,7 +432,8 @@ void launch_batch_cfirst(const int32_t *rank, const int64_t *vbase, int64_t G, c
 // community ids, graph g's in [cfirst[g], cfirst[g+1]); sig = Sigma_c).
 void launch_batch_modularity(const Level &g, const int32_t *memb, const double *sig, const int64_t *cfirst,
                              double *qin, double *q, hipStream_t s);
-void launch_add_i32(int32_t *p, int64_t n, int32_t delta, hipStream_t s);
+// out[v] <- in[v] - in[0].
+void launch_from_first(const int32_t *in, int64_t n, int32_t *out, hipStream_t s);
 // flag[v] = 1 for every vertex of a graph with gconfirm set (its confirming sweep)
 void launch_batch_flag_confirm(const int32_t *gid, const uint8_t *gconfirm, int64_t n, uint8_t *flag, hipStream_t s);
 
@@ -486,6 +526,7 @@ struct Scratch {
     int *part_c = nullptr;
     int64_t ch_cap = 0;
     uint64_t *mem_used = nullptr;  // not owned
+    uint64_t *box = nullptr;       // not owned: the context's box
 };
 
 // Grows the hub-table pool of sc to at least `slots` (keys empty, values 0).

@@ -972,25 +972,25 @@ hipError_t aggregate(const Level &g, const WorkLists &wl, const int32_t *cm, int
         k_agg_hub_sizes<<<gr, kBlock, 0, s>>>(cwl.bl, hb, H, eoff, n2, ctot);    // ctot is free now
         scan_exclusive_i64(ctot, tmp, H, sc.scan_tmp, s);
         k_agg_hub_off<<<gr, kBlock, 0, s>>>(cwl.bl, hb, H, tmp, ctab);
-        int64_t host[4] = {0, 0, 0, 0};
-        e = hipMemcpyAsync(&host[0], tmp + H, sizeof(int64_t), hipMemcpyDeviceToHost, s);
-        if (e != hipSuccess) return e;
+        launch_copy_i32(reinterpret_cast<int32_t *>(sc.f64), reinterpret_cast<const int32_t *>(tmp + H), 2, s);
         k_agg_hub_nchunks<<<gr, kBlock, 0, s>>>(cwl.bl, hb, H, eoff, ctot);
         scan_exclusive_i64(ctot, mpre, H, sc.scan_tmp, s);                        // mpre as temp
-        e = hipMemcpyAsync(&host[1], mpre + H, sizeof(int64_t), hipMemcpyDeviceToHost, s);
-        if (e != hipSuccess) return e;
         k_agg_hub_nsegs<<<gr, kBlock, 0, s>>>(cwl.bl, hb, H, eoff, n2, ctot);
         scan_exclusive_i64(ctot, tmp, H, sc.scan_tmp, s);
-        e = hipMemcpyAsync(&host[2], tmp + H, sizeof(int64_t), hipMemcpyDeviceToHost, s);
-        if (e != hipSuccess) return e;
         if (hub_parts) {   // partition words per hub community (scan by hub index in i64g)
             k_agg_part_words<<<gr, kBlock, 0, s>>>(cwl.bl, hb, H, eoff, n2, ctot);
             scan_exclusive_i64(ctot, sc.i64g, H, sc.scan_tmp, s);
-            e = hipMemcpyAsync(&host[3], sc.i64g + H, sizeof(int64_t), hipMemcpyDeviceToHost, s);
-            if (e != hipSuccess) return e;
         }
-        e = hipStreamSynchronize(s);
+        PostArgs pa;
+        pa.src[0] = sc.f64;   // the tables' total: tmp holds the segments' by now
+        pa.src[1] = mpre + H;
+        pa.src[2] = tmp + H;
+        pa.src[3] = sc.i64g + H;
+        for (int k = 0; k < 3 + hub_parts; k++) pa.n[k] = 1;
+        e = fetch_words(pa, sc.box, s);
         if (e != hipSuccess) return e;
+        int64_t host[4] = {0, 0, 0, 0};
+        for (int k = 0; k < 3 + hub_parts; k++) host[k] = (int64_t)sc.box[kBoxHead + k];
         nchunks = host[1];
         nsegs = host[2];
         if (nchunks > sc.ch_cap || nsegs > sc.ch_cap) return hipErrorInvalidValue;
@@ -1052,11 +1052,8 @@ hipError_t aggregate(const Level &g, const WorkLists &wl, const int32_t *cm, int
     if (nsegs) k_agg_hub_emit<<<(unsigned)(nsegs < 8192 ? nsegs : 8192), kBlock, 0, s>>>(a, sc.cseg_comm, sc.cseg_beg, nsegs);
     // entries of G'' (the row lengths' total)
     scan_exclusive_i32_to_i64(out.deg, tmp, n2, sc.scan_tmp, s);
-    e = hipMemcpyAsync(nnz_out, tmp + n2, sizeof(int64_t), hipMemcpyDeviceToHost, s);
-    if (e != hipSuccess) return e;
-    e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return e;
-    return hipGetLastError();
+    e = hipGetLastError();
+    return e == hipSuccess ? fetch_i64(tmp + n2, nnz_out, sc.box, s) : e;
 }
 
 hipError_t compact_rows(const int64_t *eoff, const int32_t *deg, int64_t n2, const int32_t *col, const double *w,

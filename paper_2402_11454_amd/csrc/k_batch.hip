@@ -83,8 +83,10 @@ __global__ void __launch_bounds__(kBlock) k_batch_flag_confirm(const int32_t *gi
         if (gconfirm[gid[v]]) flag[v] = 1;
 }
 
-__global__ void __launch_bounds__(kBlock) k_add_i32(int32_t *p, int64_t n, int32_t delta) {
-    for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) p[i] += delta;
+__global__ void __launch_bounds__(kBlock) k_from_first(const int32_t *in, int64_t n, int32_t *out) {
+    const int32_t first = in[0];
+    for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock)
+        out[i] = in[i] - first;
 }
 
 inline unsigned grid_of(int64_t n, int64_t per, int64_t cap) {
@@ -119,8 +121,8 @@ void launch_batch_flag_confirm(const int32_t *gid, const uint8_t *gconfirm, int6
     if (n > 0) k_batch_flag_confirm<<<grid_of(n, kBlock * 4, 4096), kBlock, 0, s>>>(gid, gconfirm, n, flag);
 }
 
-void launch_add_i32(int32_t *p, int64_t n, int32_t delta, hipStream_t s) {
-    if (n > 0 && delta != 0) k_add_i32<<<grid_of(n, kBlock * 4, 4096), kBlock, 0, s>>>(p, n, delta);
+void launch_from_first(const int32_t *in, int64_t n, int32_t *out, hipStream_t s) {
+    if (n > 0) k_from_first<<<grid_of(n, kBlock * 4, 4096), kBlock, 0, s>>>(in, n, out);
 }
 
 }  // namespace gsp

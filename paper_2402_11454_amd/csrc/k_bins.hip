@@ -1,8 +1,6 @@
 // k_bins.hip - per-level work lists: every vertex with at least one entry is
 // put in bucket (bin of its degree, its sub-round); hubs are cut into chunks
 // and get a slot range in the global hub-table pool.
-#include <vector>
-
 #include "gsp_internal.h"
 
 namespace gsp {
@@ -48,6 +46,25 @@ __global__ void __launch_bounds__(kBlock) k_bin_count(const int32_t *deg, int64_
             atomicAdd(&cnt[k], (unsigned long long)lcnt[k]);
             atomicAdd(&ent[k], lent[k]);
         }
+}
+
+// The counts to the host's box; cnt[k] becomes the begin of bucket k, so that
+// the fill need not wait for the host.
+__global__ void __launch_bounds__(kBlock) k_bin_post(unsigned long long *cnt, const unsigned long long *ent, int nb,
+                                                    uint64_t *box) {
+    __shared__ unsigned long long c[kNumBuckets];
+    for (int k = threadIdx.x; k < nb; k += kBlock) {
+        c[k] = cnt[k];
+        box[kBoxHead + k] = c[k];
+        box[kBoxHead + nb + k] = ent[k];
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < nb; k += kBlock) {
+        unsigned long long b = 0;
+        for (int j = 0; j < k; j++) b += c[j];
+        cnt[k] = b;
+    }
+    box_post(box);
 }
 
 // Places vertex ids into their buckets.  cursor[k] starts at the bucket's
@@ -99,6 +116,23 @@ __global__ void __launch_bounds__(kBlock) k_hub_sizes(const int32_t *bl, int64_t
     }
 }
 
+// The totals of the hubs' tables, partition words and chunks, and the first
+// chunk of each sub-round's hubs (pos: their positions among the hubs).
+struct HubPositions {
+    int64_t at[kMaxRounds + 1];
+};
+__global__ void __launch_bounds__(kBlock) k_hub_post(const int64_t *toff, const int64_t *boff, const int64_t *coff,
+                                                    int64_t H, HubPositions pos, int rounds, uint64_t *box) {
+    static_assert(kMaxRounds + 1 <= kBlock, "a thread per sub-round");
+    const int p = threadIdx.x;
+    if (p <= rounds) box[kBoxHead + 2 + p] = (uint64_t)coff[pos.at[p]];
+    if (p == 0) {
+        box[kBoxHead] = (uint64_t)toff[H];
+        box[kBoxHead + 1] = (uint64_t)boff[H];
+    }
+    box_post(box);
+}
+
 __global__ void __launch_bounds__(kBlock) k_hub_fill(const int32_t *bl, int64_t hb, int64_t H, const int32_t *deg,
                                                     const int64_t *off, const int64_t *toff, const int64_t *coff,
                                                     const int64_t *boff, int64_t *hub_off, int32_t *hub_ch0,
@@ -127,36 +161,22 @@ hipError_t bin_vertices(const int32_t *deg, int64_t n, int rounds, WorkLists &wl
     int nb = kNumBins * rounds;
     unsigned long long *cnt = sc.u64;          // nb counters at u64[0..nb)
     unsigned long long *ent = sc.u64 + kNumBuckets;
-    hipError_t e = hipMemsetAsync(sc.u64, 0, sizeof(unsigned long long) * 2 * kNumBuckets, s);
-    if (e != hipSuccess) return e;
-    if (n > 0) {
-        int64_t gr = (n + kBinTile - 1) / kBinTile;
-        if (gr > 4096) gr = 4096;
-        k_bin_count<<<(unsigned)gr, kBlock, 0, s>>>(deg, n, rounds, shift, gid, vbase, orig, cnt, ent);
-    }
-    unsigned long long hc[2 * kNumBuckets];
-    e = hipMemcpyAsync(hc, sc.u64, sizeof(unsigned long long) * 2 * kNumBuckets, hipMemcpyDeviceToHost, s);
-    if (e != hipSuccess) return e;
-    e = hipStreamSynchronize(s);
+    int64_t gr = (n + kBinTile - 1) / kBinTile;
+    if (gr > 4096) gr = 4096;
+    launch_fill_u64(sc.u64, 0, 2 * kNumBuckets, s);
+    if (n > 0) k_bin_count<<<(unsigned)gr, kBlock, 0, s>>>(deg, n, rounds, shift, gid, vbase, orig, cnt, ent);
+    box_arm(sc.box);
+    k_bin_post<<<1, kBlock, 0, s>>>(cnt, ent, nb, sc.box);
+    if (n > 0) k_bin_fill<<<(unsigned)gr, kBlock, 0, s>>>(deg, n, rounds, shift, gid, vbase, orig, sc.u64, wl.bl);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = box_wait(sc.box, s);
     if (e != hipSuccess) return e;
     wl.boff[0] = 0;
     for (int k = 0; k < nb; k++) {
-        wl.boff[k + 1] = wl.boff[k] + (int64_t)hc[k];
-        wl.bucket_entries[k] = (int64_t)hc[kNumBuckets + k];
+        wl.boff[k + 1] = wl.boff[k] + (int64_t)sc.box[kBoxHead + k];
+        wl.bucket_entries[k] = (int64_t)sc.box[kBoxHead + nb + k];
     }
-    // cursors = bucket begins
-    unsigned long long hcur[kNumBuckets];
-    for (int k = 0; k < nb; k++) hcur[k] = (unsigned long long)wl.boff[k];
-    e = hipMemcpyAsync(sc.u64, hcur, sizeof(unsigned long long) * nb, hipMemcpyHostToDevice, s);
-    if (e != hipSuccess) return e;
-    e = hipStreamSynchronize(s);  // hcur lives on this stack frame
-    if (e != hipSuccess) return e;
-    if (n > 0) {
-        int64_t gr = (n + kBinTile - 1) / kBinTile;
-        if (gr > 4096) gr = 4096;
-        k_bin_fill<<<(unsigned)gr, kBlock, 0, s>>>(deg, n, rounds, shift, gid, vbase, orig, sc.u64, wl.bl);
-    }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 hipError_t build_work_lists(const Level &g, int rounds, WorkLists &wl, Scratch &sc, hipStream_t s) {
@@ -175,24 +195,19 @@ hipError_t build_work_lists(const Level &g, int rounds, WorkLists &wl, Scratch &
         scan_exclusive_i64(sc.i64a, sc.i64b, H, sc.scan_tmp, s);   // i64b = table offsets
         scan_exclusive_i64(sc.i64c, sc.i64a, H, sc.scan_tmp, s);   // i64a = chunk offsets
         scan_exclusive_i64(sc.i64d, sc.i64e, H, sc.scan_tmp, s);   // i64e = partition word offsets
-        std::vector<int64_t> tmp(H + 1);
-        int64_t ttot = 0, btot = 0;
-        e = hipMemcpyAsync(&ttot, sc.i64b + H, sizeof(int64_t), hipMemcpyDeviceToHost, s);
+        HubPositions pos;
+        for (int p = 0; p <= rounds; p++)
+            pos.at[p] = (p < rounds ? wl.bucket_begin(BIN_HUB, p) : wl.bin_begin(BIN_HUB) + H) - hb;
+        box_arm(sc.box);
+        k_hub_post<<<1, kBlock, 0, s>>>(sc.i64b, sc.i64e, sc.i64a, H, pos, rounds, sc.box);
+        e = hipGetLastError();
+        if (e == hipSuccess) e = box_wait(sc.box, s);
         if (e != hipSuccess) return e;
-        e = hipMemcpyAsync(&btot, sc.i64e + H, sizeof(int64_t), hipMemcpyDeviceToHost, s);
-        if (e != hipSuccess) return e;
-        e = hipMemcpyAsync(tmp.data(), sc.i64a, sizeof(int64_t) * (H + 1), hipMemcpyDeviceToHost, s);
-        if (e != hipSuccess) return e;
-        e = hipStreamSynchronize(s);
-        if (e != hipSuccess) return e;
-        wl.nchunks = tmp[H];
-        wl.hub_table_total = (uint64_t)ttot;
-        wl.bucket_total = (uint64_t)btot;
+        wl.hub_table_total = sc.box[kBoxHead];
+        wl.bucket_total = sc.box[kBoxHead + 1];
+        for (int p = 0; p <= rounds; p++) wl.ch_poff[p] = (int64_t)sc.box[kBoxHead + 2 + p];
+        wl.nchunks = wl.ch_poff[rounds];
         if (wl.nchunks > sc.ch_cap) return hipErrorInvalidValue;
-        for (int p = 0; p <= rounds; p++) {
-            int64_t pos = (p < rounds ? wl.bucket_begin(BIN_HUB, p) : wl.bin_begin(BIN_HUB) + H) - hb;
-            wl.ch_poff[p] = tmp[pos];
-        }
         e = ensure_hub_tables(sc, wl.hub_table_total, s);
         if (e != hipSuccess) return e;
         e = ensure_hub_buckets(sc, wl.bucket_total, s);

@@ -1367,6 +1367,45 @@ inline unsigned cap_grid(int64_t units, int64_t cap) {
 // A kernel's cap under the run's launch schedule.
 inline int64_t sched_cap(const MoveArgs &a, int64_t cap) { return a.grid_cap > 0 && a.grid_cap < cap ? a.grid_cap : cap; }
 
+// One workgroup; the stripes are 18 KB, so it is a chain of one read, the
+// stores to the host's memory and the flag behind them.  Clearing here and not
+// before the sweep saves the fill's launch.
+__global__ void __launch_bounds__(kBlock) k_sweep_end(IterCounters *ctr, unsigned long long *ggain,
+                                                     unsigned long long *gmoved, int64_t G, uint64_t *box) {
+    static_assert(kSweepWords <= kBlock && sizeof(CounterStripe) >= kSweepWords * 8, "a thread per counter");
+    __shared__ int cands;
+    const int t = threadIdx.x;
+    if (t == 0) cands = 0;
+    __syncthreads();
+    int *q = &ctr->qcnt[0][0], *c = &ctr->ccnt[0][0];
+    for (int k = t; k < kMaxRounds * kNumBins; k += kBlock) {
+        const int v = c[k];
+        if (v) atomicAdd(&cands, v);
+        c[k] = 0;
+        q[k] = 0;
+    }
+    uint64_t *o = box + kBoxHead;
+    if (t < kSweepWords) {
+        unsigned long long sum = 0;
+#pragma unroll
+        for (int r = 0; r < kStripes; r++) {
+            unsigned long long *w = reinterpret_cast<unsigned long long *>(&ctr->st[r]) + t;
+            sum += *w;   // integer units: exact, in any order
+            *w = 0;
+        }
+        o[t] = sum;
+    }
+    __syncthreads();
+    if (t == 0) o[kSweepWords] = (uint64_t)cands;
+    for (int64_t k = t; k < G; k += kBlock) {
+        o[kSweepWords + 1 + k] = ggain[k];
+        o[kSweepWords + 1 + G + k] = gmoved[k];
+        ggain[k] = 0;
+        gmoved[k] = 0;
+    }
+    box_post(box);
+}
+
 }  // namespace
 
 void launch_community_totals(const double *K, const int32_t *cm, int64_t n, double *sig, int32_t *csize,
@@ -1394,6 +1433,11 @@ static int64_t bucket_total(const MoveArgs &a) {
     int64_t total = 0;
     for (int b = 0; b < kNumBins; b++) total += a.qcap[b];
     return total;
+}
+
+void launch_sweep_end(IterCounters *ctr, unsigned long long *ggain, unsigned long long *gmoved, int64_t G,
+                      uint64_t *box, hipStream_t s) {
+    k_sweep_end<<<1, kBlock, 0, s>>>(ctr, ggain, gmoved, G, box);
 }
 
 void launch_move_compact(const MoveArgs &a, const WorkLists &wl, hipStream_t s) {

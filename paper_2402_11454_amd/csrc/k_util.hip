@@ -2,6 +2,8 @@
 // weights (Section 3: K_i = sum_j w_ij) and the parts of modularity (Eq. 1).
 #include <math.h>
 
+#include <chrono>
+
 #include "gsp_internal.h"
 
 namespace gsp {
@@ -479,6 +481,17 @@ __global__ void __launch_bounds__(kBlock) k_check_labels(const int32_t *memb, in
     if (bad) atomicOr(err, 1);
 }
 
+__global__ void __launch_bounds__(kBlock) k_post(PostArgs a, uint64_t *box) {
+    uint64_t *o = box + kBoxHead;
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+        const uint64_t *src = static_cast<const uint64_t *>(a.src[r]);
+        for (int64_t k = threadIdx.x; k < a.n[r]; k += kBlock) o[k] = src[k];
+        o += a.n[r];
+    }
+    box_post(box);
+}
+
 }  // namespace
 
 void launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s) {
@@ -501,6 +514,35 @@ void launch_fill_i64(int64_t *p, int64_t v, int64_t n, hipStream_t s) {
 }
 void launch_iota_i32(int32_t *p, int64_t n, hipStream_t s) {
     if (n > 0) k_iota<<<grid_for(n, kBlock * 4, 8192), kBlock, 0, s>>>(p, n);
+}
+void box_arm(uint64_t *box) { __atomic_store_n(box, (uint64_t)0, __ATOMIC_RELEASE); }
+// Polling for at most 200 us: a result that takes longer gains nothing from it
+// (the stream's wait adds about 10 us to it).
+hipError_t box_wait(uint64_t *box, hipStream_t s) {
+    const auto t0 = std::chrono::steady_clock::now();
+    do {
+        for (int k = 0; k < 64; k++) {
+            if (__atomic_load_n(box, __ATOMIC_ACQUIRE)) return hipSuccess;
+            __builtin_ia32_pause();
+        }
+    } while (std::chrono::steady_clock::now() - t0 < std::chrono::microseconds(200));
+    hipError_t e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return e;
+    return __atomic_load_n(box, __ATOMIC_ACQUIRE) ? hipSuccess : hipErrorUnknown;
+}
+hipError_t fetch_words(const PostArgs &a, uint64_t *box, hipStream_t s) {
+    box_arm(box);
+    k_post<<<1, kBlock, 0, s>>>(a, box);
+    hipError_t e = hipGetLastError();
+    return e == hipSuccess ? box_wait(box, s) : e;
+}
+hipError_t fetch_i64(const int64_t *src, int64_t *out, uint64_t *box, hipStream_t s) {
+    PostArgs a;
+    a.src[0] = src;
+    a.n[0] = 1;
+    hipError_t e = fetch_words(a, box, s);
+    if (e == hipSuccess) *out = (int64_t)box[kBoxHead];
+    return e;
 }
 void launch_copy_i32(int32_t *dst, const int32_t *src, int64_t n, hipStream_t s) {
     if (n > 0) k_copy_i32<<<grid_for(n, kBlock * 4, 8192), kBlock, 0, s>>>(dst, src, n);

@@ -106,6 +106,35 @@ def test_batch_modularity_with_many_graphs_in_a_tile(ctx, weighted):
         assert abs(q[k] - _modularity(g, ctx.batch_membership(k))) <= 1e-12
 
 
+@pytest.mark.parametrize("graphs", [1, 495, 496, 1500])
+def test_batches_around_the_results_capacity(ctx, graphs):
+    """A sweep's totals and every graph's own come back through one buffer of
+    1,024 words that larger batches replace: batches on both sides of it (33
+    totals, one count, two words a graph), in turn on one context, and a
+    single graph after each."""
+    import torch
+    r = np.random.default_rng(graphs)
+    gs = []
+    for _ in range(graphs):
+        n = int(r.integers(2, 12))
+        u, v = r.integers(0, n, 2 * n), r.integers(0, n, 2 * n)
+        gs.append(_csr(n, u[u != v], v[u != v], False, 0))
+    ctx.load_batch(gs)
+    ctx.run_batch(1e-2, 10)
+    passes = ctx.batch_passes()
+    for k, g in enumerate(gs):
+        ref = oracle.louvain(g, 1e-2, 10, sync=True, rounds=8)
+        assert np.array_equal(ctx.batch_membership(k), ref.membership), k
+        assert passes[k] == ref.passes, k
+    for k in {0, graphs - 1}:
+        d = torch.full((gs[k].n,), -1, dtype=torch.int32, device="cuda")
+        ctx._check(gsp.lib().gsp_get_batch_membership(ctx._h, k, d.data_ptr(), gsp.DEVICE), "membership")
+        assert np.array_equal(d.cpu().numpy(), ctx.batch_membership(k))
+    ctx.load_graph(gs[0])
+    assert np.array_equal(ctx.louvain(1e-2, 10).membership,
+                          oracle.louvain(gs[0], 1e-2, 10, sync=True, rounds=8).membership)
+
+
 def _same_run(ctx, g, **kw):
     """A whole run equal to the oracle's: membership, passes, iterations,
     communities."""
