@@ -148,7 +148,7 @@ struct gsp_ctx {
     int64_t *hub_off = nullptr, *hub_b0 = nullptr;
     double *gain_tmp = nullptr;
     Scratch sc;
-    IterCounters *ctr = nullptr;      // device, 2 slots
+    IterCounters *ctr = nullptr;      // device
     IterCounters *ctr_h = nullptr;    // pinned host mirror
     uint64_t *box = nullptr;          // results for the host (kBoxHead and box_words words), then act_h
     int64_t box_words = 0;

@@ -272,111 +272,94 @@ __device__ __forceinline__ void take_owned(const MoveArgs &a, double m2, int *ke
 
 // ---------------------------------------------------------------- compact
 
-constexpr int kCompactSpan = 4096;   // entries of the buckets per compaction workgroup, at most
-
 // Unprocessed vertices of the sub-round's buckets -> per-bin queues (or,
 // in a gated sweep, per-bin candidate lists for the gate).  A workgroup
-// takes the contiguous range [part span, (part + 1) span) of the buckets (span <=
-// kCompactSpan), stages its active vertices in LDS with their rank in their
-// bin, reserves their queue slots with one atomic per bin, then writes them.
-// The queue counters are shared by every workgroup, so their atomics, not
-// the reads, bound this kernel on large levels: one per bin per workgroup
-// (not per 256 entries) keeps them few.
-struct CompactLds {
-    int32_t sv[kCompactSpan];     // staged vertex
-    uint32_t sbr[kCompactSpan];   // its bin (top 4 bits) and rank in the bin
-};
+// takes a range of 256 << shift entries of one bucket, all loaded together,
+// and reserves its queue slots with one atomic.  The queue counters are shared
+// by every workgroup, and each of their atomics costs the kernel about 9 ns, so
+// ranges grow once there are 256 of them.  (Ranges across the buckets, staged
+// in LDS with a rank per bin, took a level of 2,900,000 vertices with a nearly
+// empty frontier 14.0 us a sub-round, with the moves' application, and one of
+// 6,500,000 16.7 us; now 8.3 and 11.4.)
+constexpr int kCompactMax = 3;                   // shift at most
+constexpr int kCompactR = 1 << kCompactMax;      // entries per thread at most
+constexpr int kBlockLog = 8;
+static_assert(kBlock == 1 << kBlockLog, "a workgroup's entries by shifts");
 
-__device__ void compact_range(const MoveArgs &a, const int32_t *bl, int64_t span, int64_t part, CompactLds &l) {
-    __shared__ int lcnt[kNumBins];
-    __shared__ int lbase[kNumBins];
-    int64_t pre[kNumBins + 1];
-    pre[0] = 0;
+__device__ void compact_range(const MoveArgs &a, const int32_t *bl, int shift, int64_t part) {
+    const int64_t span = (int64_t)kBlock << shift;
+    int b = 0;
+    int64_t cap = 0, base = 0;
+    bool found = false;
 #pragma unroll
-    for (int b = 0; b < kNumBins; b++) pre[b + 1] = pre[b] + a.qcap[b];
-    const int64_t total = pre[kNumBins];
-    const bool gated = a.cand != nullptr;   // the gate fills the queue from the candidates
-    int *qcnt = gated ? a.ctr->ccnt[a.round] : a.ctr->qcnt[a.round];
-    int32_t *qout = gated ? a.cand : a.queue;
-    const int64_t lo = part * span;
-    const int64_t hi = lo + span < total ? lo + span : total;
-    if (threadIdx.x < kNumBins) lcnt[threadIdx.x] = 0;
-    __shared__ int nst;
-    if (threadIdx.x == 0) nst = 0;
-    __syncthreads();
-    // four entries per thread in flight; the active ones of a wavefront take
-    // their places with two LDS atomics (ranks by ballot: the buckets lie bin
-    // by bin, so its lanes nearly always share one bin)
-    constexpr int R = 4;
-    for (int64_t t0 = lo; t0 < hi; t0 += R * kBlock) {   // uniform over the workgroup
-        int bin[R], v[R];
-        bool act[R];
-#pragma unroll
-        for (int r = 0; r < R; r++) {
-            const int64_t t = t0 + r * kBlock + threadIdx.x;
-            int b = 0;
-#pragma unroll
-            for (int q = 1; q < kNumBins; q++) b += t >= pre[q];
-            bin[r] = b;
-            v[r] = -1;
-            if (t < hi) {
-                int64_t base = a.qbase[0];   // of bin b, less its first position
-#pragma unroll
-                for (int q = 1; q < kNumBins; q++)
-                    if (b == q) base = a.qbase[q] - pre[q];
-                v[r] = bl[base + t];
-            }
+    for (int q = 0; q < kNumBins; q++) {
+        const int64_t ranges = (a.qcap[q] + span - 1) >> (kBlockLog + shift);
+        if (!found && part < ranges) {
+            found = true;
+            b = q;
+            cap = a.qcap[q];
+            base = a.qbase[q];
+        } else if (!found) {
+            part -= ranges;
         }
+    }
+    const bool gated = a.cand != nullptr;   // the gate fills the queue from the candidates
+    const int64_t lo = part * span + threadIdx.x;
+    int v[kCompactR];
+    bool act[kCompactR];
 #pragma unroll
-        for (int r = 0; r < R; r++) act[r] = v[r] >= 0 && a.flag[v[r]] != 0;
+    for (int r = 0; r < kCompactR; r++) {
+        v[r] = -1;
+        if (r < (1 << shift) && lo + r * kBlock < cap) v[r] = bl[base + lo + r * kBlock];
+    }
 #pragma unroll
-        for (int r = 0; r < R; r++) {
-            const int i = v[r], b = bin[r];
-            if (act[r] && a.gactive && !a.gactive[a.g.gid[i]]) act[r] = false;
-            if (act[r] && a.single_only && a.csize[a.cm[i]] != 1) {
-                a.flag[i] = 0;   // merged into a sub-community: stays
-                act[r] = false;
-            }
-            if (b == BIN_HUB && i >= 0) a.hub_act[i] = act[r] ? 1 : 0;
-            if (act[r]) {
-                a.flag[i] = 0;
-                if (a.dmoved) a.dsnap[i] = a.dmoved[i];   // the features' D_i
-            }
-            unsigned long long left = __ballot(act[r]);
-            if (left == 0) continue;
-            const int first = __ffsll((long long)left) - 1;
-            int slot = 0;
-            if (lane_id() == first) slot = atomicAdd(&nst, __popcll(left));
-            slot = __shfl(slot, first) + __popcll(left & ((1ull << lane_id()) - 1ull));
-            while (left) {
-                const int lead = __ffsll((long long)left) - 1, lb = __shfl(b, lead);
-                const bool mine = act[r] && b == lb;
-                const unsigned long long m = __ballot(mine);
-                int rank = 0;
-                if (lane_id() == lead) rank = atomicAdd(&lcnt[lb], __popcll(m));
-                rank = __shfl(rank, lead) + __popcll(m & ((1ull << lane_id()) - 1ull));
-                if (mine) {
-                    l.sv[slot] = i;
-                    l.sbr[slot] = ((uint32_t)b << 28) | (uint32_t)rank;
-                }
-                left &= ~m;
-            }
+    for (int r = 0; r < kCompactR; r++) act[r] = r < (1 << shift) && v[r] >= 0 && a.flag[v[r]] != 0;
+    unsigned long long m[kCompactR];
+    int total = 0;
+#pragma unroll
+    for (int r = 0; r < kCompactR; r++) {
+        const int i = v[r];
+        if (act[r] && a.gactive && !a.gactive[a.g.gid[i]]) act[r] = false;
+        if (act[r] && a.single_only && a.csize[a.cm[i]] != 1) {
+            a.flag[i] = 0;   // merged into a sub-community: stays
+            act[r] = false;
+        }
+        if (b == BIN_HUB && i >= 0) a.hub_act[i] = act[r] ? 1 : 0;
+        if (act[r]) {
+            a.flag[i] = 0;
+            if (a.dmoved) a.dsnap[i] = a.dmoved[i];   // the features' D_i
+        }
+        m[r] = __ballot(act[r]);
+        total += __popcll(m[r]);
+    }
+    __shared__ int first[kBlock / kWave];
+    const int w = threadIdx.x / kWave;
+    if (lane_id() == 0) first[w] = total;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int sum = 0;
+#pragma unroll
+        for (int k = 0; k < kBlock / kWave; k++) sum += first[k];
+        int at = 0;
+        if (sum > 0) at = atomicAdd(gated ? &a.ctr->ccnt[a.round][b] : &a.ctr->qcnt[a.round][b], sum);
+#pragma unroll
+        for (int k = 0; k < kBlock / kWave; k++) {
+            const int t = first[k];
+            first[k] = at;
+            at += t;
         }
     }
     __syncthreads();
-    if (threadIdx.x < kNumBins && lcnt[threadIdx.x] > 0)
-        lbase[threadIdx.x] = atomicAdd(&qcnt[threadIdx.x], lcnt[threadIdx.x]);
-    __syncthreads();
-    for (int k = threadIdx.x; k < nst; k += kBlock) {
-        const uint32_t br = l.sbr[k];
-        const int b = (int)(br >> 28);
-        qout[a.qbase[b] + lbase[b] + (int64_t)(br & 0x0FFFFFFFu)] = l.sv[k];
+    int32_t *out = (gated ? a.cand : a.queue) + base + first[w];
+#pragma unroll
+    for (int r = 0; r < kCompactR; r++) {
+        if (act[r]) out[__popcll(m[r] & ((1ull << lane_id()) - 1ull))] = v[r];
+        out += __popcll(m[r]);
     }
 }
 
-__global__ void __launch_bounds__(kBlock) k_move_compact(MoveArgs a, const int32_t *bl, int64_t span) {
-    __shared__ CompactLds l;
-    compact_range(a, bl, span, blockIdx.x, l);
+__global__ void __launch_bounds__(kBlock) k_move_compact(MoveArgs a, const int32_t *bl, int shift) {
+    compact_range(a, bl, shift, blockIdx.x);
 }
 
 // ---------------------------------------------------------------- small
@@ -493,11 +476,6 @@ __device__ __forceinline__ void scan_small(const MoveArgs &a, SmallLds &lds, int
     const int w = threadIdx.x / kWave;
     int *wkeys = tkeys + w * kWaveSlots;
     double *wvals = tvals + w * kWaveSlots;
-    for (int k = lane_id(); k < kWaveSlots; k += kWave) {
-        wkeys[k] = kEmpty;
-        wvals[k] = 0.0;
-    }
-    wave_lds_sync();
     int cnt[kNumSmallBins];
     int64_t pre[kNumSmallBins + 1];
     pre[0] = 0;
@@ -507,6 +485,13 @@ __device__ __forceinline__ void scan_small(const MoveArgs &a, SmallLds &lds, int
         int vpw = small_vpw(b);
         pre[b + 1] = pre[b] + (cnt[b] + vpw - 1) / vpw;
     }
+    // late sweeps queue little: a workgroup without a unit leaves here
+    if ((int64_t)part * (kBlock / kWave) >= pre[kNumSmallBins]) return;
+    for (int k = lane_id(); k < kWaveSlots; k += kWave) {
+        wkeys[k] = kEmpty;
+        wvals[k] = 0.0;
+    }
+    wave_lds_sync();
     Acc acc;
     const int64_t nw = (int64_t)parts * (kBlock / kWave);
     for (int64_t u = (int64_t)part * (kBlock / kWave) + w; u < pre[kNumSmallBins]; u += nw) {
@@ -1201,10 +1186,10 @@ __global__ void __launch_bounds__(kBlock) k_move_hub_final(MoveArgs a) {
 
 // ---------------------------------------------------------------- apply
 
-// Moves of the sub-round.  Blocks [0, nq) walk the sub-round's queue: every
+// Moves of the sub-round.  Workgroups [0, nq) walk the sub-round's queue: every
 // vertex whose decision differs from its community moves (C'[i] <- c*);
 // the Sigma and size changes of a tile are summed per community in LDS
-// first (movers crowd into a few popular communities).  Blocks [nq, ...)
+// first (movers crowd into a few popular communities).  Workgroups [nq, ...)
 // take the sub-round's hub chunks and mark the chunk's neighbours of a hub
 // that moved.
 constexpr int kApplyTable = 4 * kBlock;
@@ -1213,11 +1198,11 @@ struct ApplyLds {
     int tk[kApplyTable], tc[kApplyTable];
 };
 
-__device__ __forceinline__ void apply_moves(const MoveArgs &a, int nq, int nh, ApplyLds &lds) {
+__device__ __forceinline__ void apply_moves(const MoveArgs &a, int part, int nq, int nh, ApplyLds &lds) {
     int *tk = lds.tk, *tc = lds.tc;
     double *tv = lds.tv;
-    if ((int)blockIdx.x >= nq) {
-        for (int64_t k = a.ch_first + (blockIdx.x - nq); k < a.ch_first + a.ch_count; k += nh) {
+    if (part >= nq) {
+        for (int64_t k = a.ch_first + (part - nq); k < a.ch_first + a.ch_count; k += nh) {
             int i = a.ch_vert[k];
             if (a.hub_act[i] != 2) continue;
             int64_t beg = a.ch_beg[k];
@@ -1235,20 +1220,21 @@ __device__ __forceinline__ void apply_moves(const MoveArgs &a, int nq, int nh, A
         }
         return;
     }
+    int64_t pre[kNumBins + 1];
+    pre[0] = 0;
+#pragma unroll
+    for (int b = 0; b < kNumBins; b++) pre[b + 1] = pre[b] + a.ctr->qcnt[a.round][b];
+    if (part * (int64_t)kBlock >= pre[kNumBins]) return;
     for (int s = threadIdx.x; s < kApplyTable; s += kBlock) {
         tk[s] = kEmpty;
         tv[s] = 0.0;
         tc[s] = 0;
     }
     __syncthreads();
-    int64_t pre[kNumBins + 1];
-    pre[0] = 0;
-#pragma unroll
-    for (int b = 0; b < kNumBins; b++) pre[b + 1] = pre[b] + a.ctr->qcnt[a.round][b];
     int32_t *cm = const_cast<int32_t *>(a.cm);
     double *sig = const_cast<double *>(a.sig);
     int32_t *csize = const_cast<int32_t *>(a.csize);
-    for (int64_t t0 = blockIdx.x * (int64_t)kBlock; t0 < pre[kNumBins]; t0 += (int64_t)nq * kBlock) {
+    for (int64_t t0 = part * (int64_t)kBlock; t0 < pre[kNumBins]; t0 += (int64_t)nq * kBlock) {
         int64_t t = t0 + threadIdx.x;
         if (t < pre[kNumBins]) {
             int b = 0;
@@ -1285,25 +1271,22 @@ __device__ __forceinline__ void apply_moves(const MoveArgs &a, int nq, int nh, A
 
 __global__ void __launch_bounds__(kBlock) k_move_apply(MoveArgs a, int nq) {
     __shared__ ApplyLds lds;
-    apply_moves(a, nq, gridDim.x - nq, lds);
+    apply_moves(a, blockIdx.x, nq, gridDim.x - nq, lds);
 }
 
-// Apply of one sub-round and, in workgroups [nq, ...), the compaction of the
+// Apply of one sub-round and, in workgroups [0, nc), the compaction of the
 // next (`next`): on a level without hubs every mover's neighbours are marked
 // by the scans, so the next sub-round's frontier is final when they end, and
 // neither half reads what the other writes (apply: memberships, Sigma,
 // sizes; compaction: flags, queues).  One dependent launch fewer per
 // sub-round.
-__global__ void __launch_bounds__(kBlock) k_move_apply_compact(MoveArgs a, int nq, MoveArgs next, const int32_t *bl,
-                                                              int64_t span) {
-    __shared__ union {
-        ApplyLds apply;
-        CompactLds compact;
-    } lds;
-    if ((int)blockIdx.x < nq)
-        apply_moves(a, nq, 0, lds.apply);
+__global__ void __launch_bounds__(kBlock) k_move_apply_compact(MoveArgs a, int nc, MoveArgs next, const int32_t *bl,
+                                                              int shift) {
+    __shared__ ApplyLds lds;
+    if ((int)blockIdx.x < nc)
+        compact_range(next, bl, shift, blockIdx.x);
     else
-        compact_range(next, bl, span, blockIdx.x - nq, lds.compact);
+        apply_moves(a, blockIdx.x - nc, gridDim.x - nc, 0, lds);
 }
 
 // sig[c] += K_i and csize[c] += 1 over the vertices i of community c.  A
@@ -1418,21 +1401,21 @@ void launch_community_totals(const double *K, const int32_t *cm, int64_t n, doub
         k_community_totals<false><<<gr, kBlock, 0, s>>>(K, cm, n, sig, nullptr);
 }
 
-// Workgroups of a compaction of `total` bucket entries and the entries each
-// takes: one pass of 256 per workgroup while that gives at most 1024
-// workgroups, then longer ranges (at most kCompactSpan entries).
-static int64_t compact_blocks(int64_t total, int64_t *span) {
-    int64_t blocks = (total + kBlock - 1) / kBlock;
-    if (blocks > 1024) blocks = 1024;
-    if (blocks < (total + kCompactSpan - 1) / kCompactSpan) blocks = (total + kCompactSpan - 1) / kCompactSpan;
-    *span = ((total + blocks - 1) / blocks + kBlock - 1) / kBlock * kBlock;
-    return (total + *span - 1) / *span;
-}
-
 static int64_t bucket_total(const MoveArgs &a) {
     int64_t total = 0;
     for (int b = 0; b < kNumBins; b++) total += a.qcap[b];
     return total;
+}
+
+// Workgroups of a compaction: ranges of 256 << *shift entries of one bucket.
+static int64_t compact_blocks(const MoveArgs &a, int *shift) {
+    const int64_t total = bucket_total(a);
+    *shift = 0;
+    while (*shift < kCompactMax && total > (int64_t)256 * (kBlock << *shift)) (*shift)++;
+    const int64_t span = (int64_t)kBlock << *shift;
+    int64_t blocks = 0;
+    for (int b = 0; b < kNumBins; b++) blocks += (a.qcap[b] + span - 1) / span;
+    return blocks;
 }
 
 void launch_sweep_end(IterCounters *ctr, unsigned long long *ggain, unsigned long long *gmoved, int64_t G,
@@ -1441,11 +1424,9 @@ void launch_sweep_end(IterCounters *ctr, unsigned long long *ggain, unsigned lon
 }
 
 void launch_move_compact(const MoveArgs &a, const WorkLists &wl, hipStream_t s) {
-    const int64_t total = bucket_total(a);
-    if (total == 0) return;
-    int64_t span = 0;
-    const int64_t blocks = compact_blocks(total, &span);
-    k_move_compact<<<(unsigned)blocks, kBlock, 0, s>>>(a, wl.bl, span);
+    int shift = 0;
+    const int64_t blocks = compact_blocks(a, &shift);
+    if (blocks > 0) k_move_compact<<<(unsigned)blocks, kBlock, 0, s>>>(a, wl.bl, shift);
 }
 
 // wave units of the small bins, at most
@@ -1575,9 +1556,9 @@ void launch_move_apply(const MoveArgs &a, int64_t cap, hipStream_t s) {
 
 void launch_move_apply_compact(const MoveArgs &a, const MoveArgs &next, const WorkLists &wl, hipStream_t s) {
     const int nq = (int)cap_grid((bucket_total(a) + kBlock - 1) / kBlock, sched_cap(a, 2048));
-    int64_t span = 0;
-    const int64_t blocks = compact_blocks(bucket_total(next), &span);
-    k_move_apply_compact<<<(unsigned)(nq + blocks), kBlock, 0, s>>>(a, nq, next, wl.bl, span);
+    int shift = 0;
+    const int64_t blocks = compact_blocks(next, &shift);
+    k_move_apply_compact<<<(unsigned)(blocks + nq), kBlock, 0, s>>>(a, (int)blocks, next, wl.bl, shift);
 }
 
 }  // namespace gsp
