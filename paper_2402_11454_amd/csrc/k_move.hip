@@ -1192,11 +1192,110 @@ __global__ void __launch_bounds__(kBlock) k_move_hub_final(MoveArgs a) {
 // first (movers crowd into a few popular communities).  Workgroups [nq, ...)
 // take the sub-round's hub chunks and mark the chunk's neighbours of a hub
 // that moved.
-constexpr int kApplyTable = 4 * kBlock;
+//
+// Atomics to one address follow each other at about 25 ns, so a popular
+// community costs a sub-round that times the tiles with movers into it: long
+// queues go in tiles of 1,024 entries (4M-vertex DC-SBM, 232,000 entries with
+// 68,000 movers among 1,992 tiles of 256: 54 us, now 29; 4.3 -> 2.9 ms of its
+// run).  A shorter queue leaves the chip idle in such tiles and waits for four
+// rounds of table operations instead (139,000 entries with few movers: 26 us
+// with the next compaction, 40 in wide tiles).
+constexpr int kApplyR = 4;                     // queue entries per thread and tile, of long queues
+constexpr int64_t kApplyWide = 163840;         // those above this many entries
+constexpr int kApplyTable = 2 * kApplyR * kBlock;   // slots
+constexpr int kApplyProbes = 12;               // a community that finds no slot in as many goes straight on
 struct ApplyLds {
     double tv[kApplyTable];
     int tk[kApplyTable], tc[kApplyTable];
 };
+
+// Tiles of R queue entries per thread; the workgroup's table is empty before
+// and after.
+template <int R>
+__device__ __forceinline__ void apply_tiles(const MoveArgs &a, const int64_t (&pre)[kNumBins + 1], int part, int nq,
+                                            ApplyLds &lds) {
+    constexpr int kTile = R * kBlock;
+    int *tk = lds.tk, *tc = lds.tc;
+    double *tv = lds.tv;
+    int32_t *cm = const_cast<int32_t *>(a.cm);
+    double *sig = const_cast<double *>(a.sig);
+    int32_t *csize = const_cast<int32_t *>(a.csize);
+    for (int64_t t0 = part * (int64_t)kTile; t0 < pre[kNumBins]; t0 += (int64_t)nq * kTile) {
+        int i[R], c[R], d[R];
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const int64_t t = t0 + r * kBlock + threadIdx.x;
+            i[r] = -1;
+            if (t < pre[kNumBins]) {
+                int64_t at = t + a.qbase[0];
+#pragma unroll
+                for (int b = 1; b < kNumBins; b++)
+                    if (t >= pre[b]) at = t - pre[b] + a.qbase[b];
+                i[r] = a.queue[at];
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            c[r] = i[r] >= 0 ? a.dec[i[r]] : 0;
+            d[r] = i[r] >= 0 ? cm[i[r]] : 0;
+        }
+        double ki[R];
+#pragma unroll
+        for (int r = 0; r < R; r++) ki[r] = c[r] != d[r] ? a.K[i[r]] : 0.0;
+        // entry 2k: the community left, 2k + 1: the one joined; the first
+        // compare-and-swaps of all go out together
+        int at[2 * R];
+        unsigned own = 0, open = 0;
+#pragma unroll
+        for (int r = 0; r < 2 * R; r++) {
+            const int key = r & 1 ? c[r / 2] : d[r / 2];
+            at[r] = (int)(key_hash(key) & (kApplyTable - 1));
+            if (c[r / 2] == d[r / 2]) continue;
+            if (r & 1) cm[i[r / 2]] = key;
+            const int prev = atomicCAS(&tk[at[r]], kEmpty, key);
+            own |= (prev == kEmpty ? 1u : 0u) << r;
+            open |= (prev != kEmpty && prev != key ? 1u : 0u) << r;
+        }
+        for (int probe = 1; open && probe < kApplyProbes; probe++) {
+#pragma unroll
+            for (int r = 0; r < 2 * R; r++) {
+                if (!((open >> r) & 1u)) continue;
+                const int key = r & 1 ? c[r / 2] : d[r / 2];
+                at[r] = (int)((at[r] + step_mask(key_hash(key))) & (kApplyTable - 1));
+                const int prev = atomicCAS(&tk[at[r]], kEmpty, key);
+                own |= (prev == kEmpty ? 1u : 0u) << r;
+                if (prev == kEmpty || prev == key) open &= ~(1u << r);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 2 * R; r++) {
+            if (c[r / 2] == d[r / 2]) continue;
+            const int one = r & 1 ? 1 : -1;
+            const double x = r & 1 ? ki[r / 2] : -ki[r / 2];
+            if ((open >> r) & 1u) {
+                const int key = r & 1 ? c[r / 2] : d[r / 2];
+                if (x != 0.0) unsafeAtomicAdd(&sig[key], x);
+                atomicAdd(&csize[key], one);
+            } else {
+                if (x != 0.0) atomicAdd(&tv[at[r]], x);
+                atomicAdd(&tc[at[r]], one);
+            }
+        }
+        __syncthreads();
+        // who claimed a slot empties it
+#pragma unroll
+        for (int r = 0; r < 2 * R; r++) {
+            if (!((own >> r) & 1u)) continue;
+            const int s = at[r], key = r & 1 ? c[r / 2] : d[r / 2], n = tc[s];
+            const double x = tv[s];
+            if (x != 0.0) unsafeAtomicAdd(&sig[key], x);
+            if (n != 0) atomicAdd(&csize[key], n);
+            tk[s] = kEmpty;
+            tv[s] = 0.0;
+            tc[s] = 0;
+        }
+        __syncthreads();
+    }}
 
 __device__ __forceinline__ void apply_moves(const MoveArgs &a, int part, int nq, int nh, ApplyLds &lds) {
     int *tk = lds.tk, *tc = lds.tc;
@@ -1224,49 +1323,17 @@ __device__ __forceinline__ void apply_moves(const MoveArgs &a, int part, int nq,
     pre[0] = 0;
 #pragma unroll
     for (int b = 0; b < kNumBins; b++) pre[b + 1] = pre[b] + a.ctr->qcnt[a.round][b];
-    if (part * (int64_t)kBlock >= pre[kNumBins]) return;
+    if (part * (int64_t)kBlock * (pre[kNumBins] > kApplyWide ? kApplyR : 1) >= pre[kNumBins]) return;
     for (int s = threadIdx.x; s < kApplyTable; s += kBlock) {
         tk[s] = kEmpty;
         tv[s] = 0.0;
         tc[s] = 0;
     }
     __syncthreads();
-    int32_t *cm = const_cast<int32_t *>(a.cm);
-    double *sig = const_cast<double *>(a.sig);
-    int32_t *csize = const_cast<int32_t *>(a.csize);
-    for (int64_t t0 = part * (int64_t)kBlock; t0 < pre[kNumBins]; t0 += (int64_t)nq * kBlock) {
-        int64_t t = t0 + threadIdx.x;
-        if (t < pre[kNumBins]) {
-            int b = 0;
-            while (t >= pre[b + 1]) b++;
-            int i = a.queue[a.qbase[b] + (t - pre[b])];
-            int c = a.dec[i];
-            int d = cm[i];
-            if (c != d) {
-                double ki = a.K[i];
-                cm[i] = c;
-                int sd = lds_table_slot(tk, kApplyTable - 1, d);
-                int sc = lds_table_slot(tk, kApplyTable - 1, c);
-                if (ki != 0.0) {
-                    atomicAdd(&tv[sd], -ki);
-                    atomicAdd(&tv[sc], ki);
-                }
-                atomicSub(&tc[sd], 1);
-                atomicAdd(&tc[sc], 1);
-            }
-        }
-        __syncthreads();
-        for (int s = threadIdx.x; s < kApplyTable; s += kBlock) {
-            int key = tk[s];
-            if (key == kEmpty) continue;
-            if (tv[s] != 0.0) unsafeAtomicAdd(&sig[key], tv[s]);
-            if (tc[s] != 0) atomicAdd(&csize[key], tc[s]);
-            tk[s] = kEmpty;
-            tv[s] = 0.0;
-            tc[s] = 0;
-        }
-        __syncthreads();
-    }
+    if (pre[kNumBins] > kApplyWide)
+        apply_tiles<kApplyR>(a, pre, part, nq, lds);
+    else
+        apply_tiles<1>(a, pre, part, nq, lds);
 }
 
 __global__ void __launch_bounds__(kBlock) k_move_apply(MoveArgs a, int nq) {

@@ -174,6 +174,27 @@ def test_sub_rounds_without_hubs(ctx, n, sub_rounds, use_graphs):
         _same_run(ctx, g, sub_rounds=sub_rounds, use_graphs=use_graphs, return_moves=rm)
 
 
+@pytest.mark.parametrize("n", [163840, 163841, 300000])
+@pytest.mark.parametrize("hub", [False, True])
+def test_long_queues_are_applied_in_wide_tiles(ctx, n, hub):
+    """One sub-round holds every vertex: queues of 163,840 entries and one
+    more, where the tiles of the moves grow, and more; first every vertex in
+    a community of its own (more communities than the tile's table takes),
+    then communities that many movers join; with a hub and without."""
+    r = np.random.default_rng(n + hub)
+    u, v = r.integers(0, n, 2 * n), r.integers(0, n, 2 * n) // 40
+    u, v = np.concatenate([u, np.arange(n)]), np.concatenate([v, (np.arange(n) + 1) % n])
+    if hub:
+        u, v = np.concatenate([u, np.zeros(6000, np.int64)]), np.concatenate([v, np.arange(1, 6001) * 17])
+    g = _csr(n, u[u != v], v[u != v], hub, n)
+    ctx.load_graph(g)
+    ref = oracle.louvain(g, 1e-2, 3, sync=True, rounds=1)
+    for kw in (dict(), dict(vertex_order=gsp.ORDER_DEGREE)):
+        res = ctx.louvain(1e-2, 3, sub_rounds=1, **kw)
+        assert np.array_equal(res.membership, ref.membership)
+        assert res.stats["iterations"] == list(ref.iterations)
+
+
 def _dense(n, p, weighted, seed, loops=False):
     """A random graph with mean degree p n; weights dyadic."""
     r = np.random.default_rng(seed)
