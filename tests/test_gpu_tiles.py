@@ -278,3 +278,40 @@ def test_small_graph_with_duplicates_and_fp64_weights(ctx):
     g = oracle.CSR(n, off, col, wg)
     ref = oracle.louvain(g, 1e-2, 10, sync=True, rounds=8)
     assert np.array_equal(ctx.louvain(1e-2, 10).membership, ref.membership)
+
+
+@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 5000])
+def test_aggregation_counts_at_the_tiles_edges(ctx, n):
+    """Members and degrees are counted in one word per community by tiles of
+    1,024 vertices: one vertex, a tile less one and more, several tiles;
+    communities of isolated vertices only, of both kinds, one for all."""
+    r = np.random.default_rng(n)
+    ends = r.choice(n, max(2, n // 2)) if n > 1 else np.zeros(2, np.int64)
+    u, v = r.choice(ends, 3 * n), r.choice(ends, 3 * n)   # half of the vertices have no entries
+    g = _csr(n, u[u != v].astype(np.int64), v[u != v].astype(np.int64), True, n)
+    ctx.load_graph(g)
+    for m in (np.zeros(n, np.int32), np.arange(n, dtype=np.int32), r.integers(0, max(1, n // 7), n).astype(np.int32),
+              np.where(np.diff(g.offsets) > 0, 0, n - 1).astype(np.int32)):
+        mr, G = oracle.renumber(m)
+        ref = oracle.aggregate(g, mr, G)
+        n2, off, col, w = ctx.step_aggregate(m)
+        assert n2 == G
+        assert np.array_equal(off, ref.off)
+        for c in range(n2):
+            a, b = slice(int(off[c]), int(off[c + 1])), slice(int(ref.off[c]), int(ref.off[c + 1]))
+            o, q = np.argsort(col[a]), np.argsort(ref.col[b])
+            assert np.array_equal(col[a][o], ref.col[b][q]) and np.array_equal(w[a][o], ref.w[b][q])
+
+
+@pytest.mark.parametrize("n", [2, 7, 8, 63, 64, 65, 513, 4097])
+def test_degree_order_label_minima(ctx, n):
+    """The smallest caller's id of each community in degree order, taken over
+    a 64th, an eighth and the rest of the vertices: sizes where these are
+    empty or one vertex (a whole run, one pass and several)."""
+    r = np.random.default_rng(n)
+    u, v = r.integers(0, n, 5 * n), r.integers(0, n, 5 * n)
+    g = _csr(n, u[u != v], v[u != v], True, n)
+    ctx.load_graph(g)
+    for passes in (1, 10):
+        ref = oracle.louvain(g, 1e-2, passes, sync=True, rounds=8)
+        assert np.array_equal(ctx.louvain(1e-2, passes, vertex_order=gsp.ORDER_DEGREE).membership, ref.membership)
