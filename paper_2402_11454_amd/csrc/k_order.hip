@@ -207,14 +207,18 @@ __global__ void __launch_bounds__(kBlock) k_vertex_weights_long(Level g, double 
     if (threadIdx.x == 0 && blk != 0.0) unsafeAtomicAdd(M2, blk);
 }
 
-// minorig[l] = min orig[v] over lab[v] = l.  The values only decrease, so a
-// plain read that already shows a value at most orig[v] makes the atomic
-// unnecessary; this keeps the atomics on a large community's word few.
-__global__ void __launch_bounds__(kBlock) k_min_orig_of_label(const int32_t *lab, const int32_t *orig, int64_t n,
-                                                             int32_t *minorig) {
-    for (int64_t v = blockIdx.x * (int64_t)kBlock + threadIdx.x; v < n; v += (int64_t)gridDim.x * kBlock) {
+// minorig[l] = min orig[v] over lab[v] = l, v in [v0, v1).  The values only
+// decrease, so a plain read that already shows a value at most orig[v] makes
+// the atomic, which this kernel is bound by, unnecessary.  The read may come
+// from a cache that misses the other XCDs' minima; launches over a 64th and an
+// eighth of the vertices first leave values that all see (4M vertices, 70k
+// labels: with reads past the caches 0.65 ms, with cached ones 0.41, with a
+// launch over an eighth first 0.28, so 0.07).
+__global__ void __launch_bounds__(kBlock) k_min_orig_of_label(const int32_t *lab, const int32_t *orig, int64_t v0,
+                                                             int64_t v1, int32_t *minorig) {
+    for (int64_t v = v0 + blockIdx.x * (int64_t)kBlock + threadIdx.x; v < v1; v += (int64_t)gridDim.x * kBlock) {
         const int l = lab[v], o = orig[v];
-        if (o < __hip_atomic_load(&minorig[l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(&minorig[l], o);
+        if (o < __hip_atomic_load(&minorig[l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) atomicMin(&minorig[l], o);
     }
 }
 
@@ -316,7 +320,12 @@ void launch_vertex_weights_long(const Level &g, double *K, double *M2, hipStream
 void launch_labels_min_orig(int32_t *lab, const int32_t *orig, int64_t n, int32_t *tmp, hipStream_t s) {
     if (n == 0) return;
     launch_fill_i32(tmp, 0x7fffffff, n, s);
-    k_min_orig_of_label<<<grid_of(n, kBlock * 4, 8192), kBlock, 0, s>>>(lab, orig, n, tmp);
+    const int64_t to[3] = {n / 64, n / 8, n};
+    for (int k = 0; k < 3; k++) {
+        const int64_t from = k ? to[k - 1] : 0;
+        if (to[k] > from)
+            k_min_orig_of_label<<<grid_of(to[k] - from, kBlock, 8192), kBlock, 0, s>>>(lab, orig, from, to[k], tmp);
+    }
     k_label_lookup<<<grid_of(n, kBlock * 4, 8192), kBlock, 0, s>>>(lab, tmp, n);
 }
 
