@@ -1409,6 +1409,78 @@ __global__ void __launch_bounds__(kBlock) k_community_totals(const double *K, co
     }
 }
 
+// The same for many vertices: a workgroup per CU keeps one table over all of its
+// tiles and empties it when half of the slots are taken, so that few
+// communities cost an atomic per workgroup instead of one per tile (4M
+// vertices in 606 communities, where each took one from nearly every tile:
+// 0.56 ms, now 0.06; 16.8M in 7.9M, some giant: 1.03, now 0.18).
+constexpr int kKeptThreads = 1024;
+constexpr int kKeptTable = 8192;
+constexpr int kKeptR = 2;
+constexpr int64_t kKeptFrom = 256 * kKeptThreads * kKeptR;   // a tile for every workgroup
+template <bool SIZES>
+__global__ void __launch_bounds__(kKeptThreads) k_community_totals_kept(const double *K, const int32_t *cm, int64_t n,
+                                                                       double *sig, int32_t *csize) {
+    constexpr int kTile = kKeptThreads * kKeptR;
+    static_assert(kKeptTable / 2 + kTile <= kKeptTable, "a tile fits beside a half full table");
+    __shared__ int tk[kKeptTable];
+    __shared__ double tv[kKeptTable];
+    __shared__ int tc[SIZES ? kKeptTable : 1];
+    __shared__ int taken;
+    const int tid = threadIdx.x;
+    for (int q = tid; q < kKeptTable; q += kKeptThreads) {
+        tk[q] = kEmpty;
+        tv[q] = 0.0;
+        if (SIZES) tc[q] = 0;
+    }
+    if (tid == 0) taken = 0;
+    __syncthreads();
+    for (int64_t i0 = blockIdx.x * (int64_t)kTile; i0 < n; i0 += (int64_t)gridDim.x * kTile) {
+        int c[kKeptR];
+        double k[kKeptR];
+#pragma unroll
+        for (int r = 0; r < kKeptR; r++) {
+            const int64_t i = i0 + r * kKeptThreads + tid;
+            c[r] = i < n ? cm[i] : kEmpty;
+            k[r] = i < n ? K[i] : 0.0;
+        }
+        int own = 0;
+#pragma unroll
+        for (int r = 0; r < kKeptR; r++) {
+            if (c[r] == kEmpty) continue;
+            const uint32_t h = key_hash(c[r]);
+            int q = (int)(h & (kKeptTable - 1));
+            while (true) {
+                const int prev = tk[q] == c[r] ? c[r] : atomicCAS(&tk[q], kEmpty, c[r]);
+                own += prev == kEmpty;
+                if (prev == kEmpty || prev == c[r]) break;
+                q = (int)((q + step_mask(h)) & (kKeptTable - 1));
+            }
+            if (k[r] != 0.0) atomicAdd(&tv[q], k[r]);
+            if (SIZES) atomicAdd(&tc[q], 1);
+        }
+        own = (int)group_sum_ll<kWave>(own);
+        if (own && lane_id() == 0) atomicAdd(&taken, own);
+        __syncthreads();
+        const bool last = i0 + (int64_t)gridDim.x * kTile >= n;
+        if (last || taken > kKeptTable / 2) {   // the same in every thread
+            __syncthreads();
+            if (tid == 0) taken = 0;
+#pragma unroll
+            for (int r = 0; r < kKeptTable / kKeptThreads; r++) {
+                const int q = r * kKeptThreads + tid, key = tk[q];
+                if (key == kEmpty) continue;
+                if (tv[q] != 0.0) unsafeAtomicAdd(&sig[key], tv[q]);
+                if (SIZES) atomicAdd(&csize[key], tc[q]);
+                tk[q] = kEmpty;
+                tv[q] = 0.0;
+                if (SIZES) tc[q] = 0;
+            }
+            __syncthreads();
+        }
+    }
+}
+
 inline unsigned cap_grid(int64_t units, int64_t cap) {
     if (units < 1) units = 1;
     return (unsigned)(units < cap ? units : cap);
@@ -1462,7 +1534,11 @@ void launch_community_totals(const double *K, const int32_t *cm, int64_t n, doub
                              hipStream_t s) {
     if (n == 0) return;
     const unsigned gr = cap_grid((n + kTotalsTile - 1) / kTotalsTile, 8192);
-    if (csize)
+    if (n >= kKeptFrom && csize)
+        k_community_totals_kept<true><<<256, kKeptThreads, 0, s>>>(K, cm, n, sig, csize);
+    else if (n >= kKeptFrom)
+        k_community_totals_kept<false><<<256, kKeptThreads, 0, s>>>(K, cm, n, sig, nullptr);
+    else if (csize)
         k_community_totals<true><<<gr, kBlock, 0, s>>>(K, cm, n, sig, csize);
     else
         k_community_totals<false><<<gr, kBlock, 0, s>>>(K, cm, n, sig, nullptr);

@@ -315,3 +315,16 @@ def test_degree_order_label_minima(ctx, n):
     for passes in (1, 10):
         ref = oracle.louvain(g, 1e-2, passes, sync=True, rounds=8)
         assert np.array_equal(ctx.louvain(1e-2, passes, vertex_order=gsp.ORDER_DEGREE).membership, ref.membership)
+
+
+@pytest.mark.parametrize("n", [524287, 524288, 526337])
+@pytest.mark.parametrize("communities", [1, 4000, 4097, 300000])
+def test_community_totals_in_kept_tables(ctx, n, communities):
+    """From 524,288 vertices on a workgroup keeps its table of 8,192 slots over
+    several tiles and empties it when half of them are taken: one community,
+    as many as never fill half, just more, and more in a tile than half."""
+    r = np.random.default_rng(n + communities)
+    g = _csr(n, np.arange(n - 1, dtype=np.int64), np.arange(1, n, dtype=np.int64), True, n)
+    m = r.integers(0, communities, n).astype(np.int32)
+    ctx.load_graph(g)
+    assert abs(ctx.modularity(m) - _modularity(g, m)) <= 1e-12
