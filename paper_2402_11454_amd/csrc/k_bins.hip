@@ -1,13 +1,22 @@
 // k_bins.hip - per-level work lists: every vertex with at least one entry is
 // put in bucket (bin of its degree, its sub-round); hubs are cut into chunks
 // and get a slot range in the global hub-table pool.
+#include <algorithm>
+
 #include "gsp_internal.h"
 
 namespace gsp {
 
 namespace {
 
+// Vertices per tile and workgroup: a bucket's counters take an atomic from
+// every tile that meets it, and atomics to one address follow each other at
+// about 25 ns, so tiles grow with the level (kBinTiles of them at most, 16
+// vertices a thread).  (16.8M vertices in tiles of 1,024: 120 us to fill, now 48;
+// 15M 130, now 62.)
 constexpr int kBinTile = kBlock * 4;
+constexpr int kBinWide = kBlock * 16;
+constexpr int64_t kBinTiles = 512;
 
 // Sub-round of vertex v: by its id within its graph when the level holds a
 // batch of graphs (gid: graph of each vertex, vbase: first vertex of each
@@ -69,19 +78,20 @@ __global__ void __launch_bounds__(kBlock) k_bin_post(unsigned long long *cnt, co
 
 // Places vertex ids into their buckets.  cursor[k] starts at the bucket's
 // begin; each block reserves its slots with one atomic per bucket.
+template <int TILE>
 __global__ void __launch_bounds__(kBlock) k_bin_fill(const int32_t *deg, int64_t n, int rounds, int shift,
                                                     const int32_t *gid, const int64_t *vbase, const int32_t *orig,
                                                     unsigned long long *cursor, int32_t *bl) {
     __shared__ unsigned int lcnt[kNumBuckets];
     __shared__ unsigned long long lbase[kNumBuckets];
     int nb = kNumBins * rounds;
-    for (int64_t t0 = blockIdx.x * (int64_t)kBinTile; t0 < n; t0 += (int64_t)gridDim.x * kBinTile) {
+    for (int64_t t0 = blockIdx.x * (int64_t)TILE; t0 < n; t0 += (int64_t)gridDim.x * TILE) {
         for (int k = threadIdx.x; k < nb; k += kBlock) lcnt[k] = 0;
         __syncthreads();
-        int bk[4];
-        unsigned rk[4];
+        int bk[TILE / kBlock];
+        unsigned rk[TILE / kBlock];
 #pragma unroll
-        for (int r = 0; r < 4; r++) {
+        for (int r = 0; r < TILE / kBlock; r++) {
             int64_t v = t0 + (int64_t)r * kBlock + threadIdx.x;
             bk[r] = -1;
             if (v < n) {
@@ -97,7 +107,7 @@ __global__ void __launch_bounds__(kBlock) k_bin_fill(const int32_t *deg, int64_t
             if (lcnt[k]) lbase[k] = atomicAdd(&cursor[k], (unsigned long long)lcnt[k]);
         __syncthreads();
 #pragma unroll
-        for (int r = 0; r < 4; r++) {
+        for (int r = 0; r < TILE / kBlock; r++) {
             int64_t v = t0 + (int64_t)r * kBlock + threadIdx.x;
             if (bk[r] >= 0) bl[lbase[bk[r]] + rk[r]] = (int32_t)v;
         }
@@ -161,13 +171,17 @@ hipError_t bin_vertices(const int32_t *deg, int64_t n, int rounds, WorkLists &wl
     int nb = kNumBins * rounds;
     unsigned long long *cnt = sc.u64;          // nb counters at u64[0..nb)
     unsigned long long *ent = sc.u64 + kNumBuckets;
-    int64_t gr = (n + kBinTile - 1) / kBinTile;
-    if (gr > 4096) gr = 4096;
+    const bool wide = n > kBinTiles * kBinTile;
+    const int64_t gc = std::min<int64_t>((n + kBinTile - 1) / kBinTile, kBinTiles);
+    const int64_t gf = std::min<int64_t>((n + (wide ? kBinWide : kBinTile) - 1) / (wide ? kBinWide : kBinTile), 4096);
     launch_fill_u64(sc.u64, 0, 2 * kNumBuckets, s);
-    if (n > 0) k_bin_count<<<(unsigned)gr, kBlock, 0, s>>>(deg, n, rounds, shift, gid, vbase, orig, cnt, ent);
+    if (n > 0) k_bin_count<<<(unsigned)gc, kBlock, 0, s>>>(deg, n, rounds, shift, gid, vbase, orig, cnt, ent);
     box_arm(sc.box);
     k_bin_post<<<1, kBlock, 0, s>>>(cnt, ent, nb, sc.box);
-    if (n > 0) k_bin_fill<<<(unsigned)gr, kBlock, 0, s>>>(deg, n, rounds, shift, gid, vbase, orig, sc.u64, wl.bl);
+    if (n > 0 && wide)
+        k_bin_fill<kBinWide><<<(unsigned)gf, kBlock, 0, s>>>(deg, n, rounds, shift, gid, vbase, orig, sc.u64, wl.bl);
+    else if (n > 0)
+        k_bin_fill<kBinTile><<<(unsigned)gf, kBlock, 0, s>>>(deg, n, rounds, shift, gid, vbase, orig, sc.u64, wl.bl);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = box_wait(sc.box, s);
     if (e != hipSuccess) return e;

@@ -328,3 +328,15 @@ def test_community_totals_in_kept_tables(ctx, n, communities):
     m = r.integers(0, communities, n).astype(np.int32)
     ctx.load_graph(g)
     assert abs(ctx.modularity(m) - _modularity(g, m)) <= 1e-12
+
+
+@pytest.mark.parametrize("n, sub_rounds", [(524288, 8), (524289, 8), (524289, 64), (530001, 1)])
+def test_work_lists_in_wide_tiles(ctx, n, sub_rounds):
+    """Above 524,288 vertices the work lists are filled in tiles of 4,096."""
+    r = np.random.default_rng(n)
+    u, v = r.integers(0, n, n), r.integers(0, n, n) // 9
+    g = _csr(n, u[u != v], v[u != v], False, 0)
+    ctx.load_graph(g)
+    ref = oracle.louvain(g, 1e-2, 1, sync=True, rounds=sub_rounds)
+    res = ctx.louvain(1e-2, 1, sub_rounds=sub_rounds, vertex_order=gsp.ORDER_LOADED)
+    assert np.array_equal(res.membership, ref.membership)
