@@ -86,6 +86,84 @@ __global__ void __launch_bounds__(kBlock) k_agg_count(Level g, const int32_t *cm
     }
 }
 
+// The same for many vertices: a workgroup per CU keeps one table over the
+// tiles of its range and empties it when half of the slots are taken; the
+// vertices counted since then, each thread its own, add the places reserved
+// to their own.  A popular community then takes an atomic per table and not
+// per tile (atomics to one address follow each other: 4M vertices in 70k
+// communities 0.51 -> 0.09 ms).  With few members each, nothing is popular, and
+// the second look at the table is lost (15M in 6.5M 0.66 -> 0.71): it takes
+// eight members a community.
+constexpr int kKeptThreads = 1024, kKeptTable = 8192, kKeptR = 2, kKeptGroups = 256;
+constexpr int kKeptTile = kKeptThreads * kKeptR;
+constexpr int64_t kKeptFrom = (int64_t)kKeptGroups * kKeptTile;   // a tile for every workgroup
+static_assert(kKeptTable / 2 + kKeptTile <= kKeptTable, "a tile fits beside a half full table");
+
+__global__ void __launch_bounds__(kKeptThreads) k_agg_count_kept(Level g, const int32_t *cm, int shift, int64_t range,
+                                                                unsigned long long *packed, int32_t *zero,
+                                                                int32_t *rank) {
+    __shared__ int tk[kKeptTable];
+    __shared__ int tz[kKeptTable];
+    __shared__ unsigned long long tp[kKeptTable];
+    __shared__ int taken;
+    const int tid = threadIdx.x;
+    for (int s = tid; s < kKeptTable; s += kKeptThreads) { tk[s] = kEmpty; tz[s] = 0; tp[s] = 0; }
+    if (tid == 0) taken = 0;
+    __syncthreads();
+    const int64_t lo = blockIdx.x * range, hi = lo + range < g.n ? lo + range : g.n;   // range: whole tiles
+    auto slot_of = [&](int c, int *own) {
+        const uint32_t h = key_hash(c);
+        int q = (int)(h & (kKeptTable - 1));
+        while (true) {
+            const int prev = tk[q] == c ? c : atomicCAS(&tk[q], kEmpty, c);
+            *own += prev == kEmpty;
+            if (prev == kEmpty || prev == c) return q;
+            q = (int)((q + step_mask(h)) & (kKeptTable - 1));
+        }
+    };
+    int64_t since = lo;   // vertices counted but not placed
+    for (int64_t t0 = lo; t0 < hi; t0 += kKeptTile) {
+        int c[kKeptR], d[kKeptR], own = 0;
+#pragma unroll
+        for (int r = 0; r < kKeptR; r++) {
+            const int64_t v = t0 + r * kKeptThreads + tid;
+            c[r] = v < hi ? cm[v] : kEmpty;
+            d[r] = v < hi ? g.deg[v] : 0;
+        }
+#pragma unroll
+        for (int r = 0; r < kKeptR; r++) {
+            if (c[r] == kEmpty) continue;
+            const int q = slot_of(c[r], &own);
+            rank[t0 + r * kKeptThreads + tid] =
+                d[r] ? (int)(atomicAdd(&tp[q], (1ull << shift) | (unsigned)d[r]) >> shift) : ~atomicAdd(&tz[q], 1);
+        }
+        own = (int)group_sum_ll<kWave>(own);
+        if (own && lane_id() == 0) atomicAdd(&taken, own);
+        __syncthreads();
+        if (t0 + kKeptTile >= hi || taken > kKeptTable / 2) {   // the same in every thread
+            __syncthreads();
+            if (tid == 0) taken = 0;
+#pragma unroll
+            for (int r = 0; r < kKeptTable / kKeptThreads; r++) {
+                const int q = r * kKeptThreads + tid, k = tk[q];
+                if (k == kEmpty) continue;
+                if (tp[q]) tp[q] = atomicAdd(&packed[k], tp[q]) >> shift;
+                if (tz[q]) tz[q] = atomicAdd(&zero[k], tz[q]);
+            }
+            __syncthreads();
+            for (int64_t v = since + tid; v < t0 + kKeptTile && v < hi; v += kKeptThreads) {
+                const int at = rank[v];   // this thread's own store
+                const int q = slot_of(cm[v], &own);
+                rank[v] = at >= 0 ? (int)tp[q] + at : ~(tz[q] + ~at);
+            }
+            since = t0 + kKeptTile;
+            __syncthreads();
+            for (int s = tid; s < kKeptTable; s += kKeptThreads) { tk[s] = kEmpty; tz[s] = 0; tp[s] = 0; }
+            __syncthreads();
+        }
+    }
+}
+
 __global__ void __launch_bounds__(kBlock) k_agg_unpack(int64_t *ctot, const int32_t *zero, int64_t n2, int shift,
                                                       int32_t *csz) {
     for (int64_t c = blockIdx.x * (int64_t)kBlock + threadIdx.x; c < n2; c += (int64_t)gridDim.x * kBlock) {
@@ -915,8 +993,14 @@ hipError_t aggregate(const Level &g, const WorkLists &wl, const int32_t *cm, int
     while (g.nnz >> shift) shift++;
     launch_fill_i32(zero, 0, n2, s);
     launch_fill_i64(ctot, 0, n2, s);
-    k_agg_count<<<grid1((g.n + 3) / 4, 4096), kBlock, 0, s>>>(g, cm, shift, reinterpret_cast<unsigned long long *>(ctot),
-                                                              zero, rank);
+    unsigned long long *packed = reinterpret_cast<unsigned long long *>(ctot);
+    if (g.n >= kKeptFrom && n2 <= g.n / 8) {
+        const int64_t tiles = (g.n + kKeptTile - 1) / kKeptTile;
+        const int64_t range = (tiles + kKeptGroups - 1) / kKeptGroups * kKeptTile;
+        k_agg_count_kept<<<kKeptGroups, kKeptThreads, 0, s>>>(g, cm, shift, range, packed, zero, rank);
+    } else {
+        k_agg_count<<<grid1((g.n + 3) / 4, 4096), kBlock, 0, s>>>(g, cm, shift, packed, zero, rank);
+    }
     k_agg_unpack<<<grid1(n2), kBlock, 0, s>>>(ctot, zero, n2, shift, csz);
     scan_exclusive_i32_to_i64(csz, coff, n2, sc.scan_tmp, s);
     scan_exclusive_i64(ctot, eoff, n2, sc.scan_tmp, s);

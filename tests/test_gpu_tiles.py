@@ -340,3 +340,25 @@ def test_work_lists_in_wide_tiles(ctx, n, sub_rounds):
     ref = oracle.louvain(g, 1e-2, 1, sync=True, rounds=sub_rounds)
     res = ctx.louvain(1e-2, 1, sub_rounds=sub_rounds, vertex_order=gsp.ORDER_LOADED)
     assert np.array_equal(res.membership, ref.membership)
+
+
+@pytest.mark.parametrize("n", [524287, 524288, 600001])
+@pytest.mark.parametrize("communities", [1, 4097, 60000, 300000])
+def test_aggregation_counts_in_kept_tables(ctx, n, communities):
+    """From 524,288 vertices on a workgroup keeps its table of communities over
+    the tiles of its range and places the vertices when it empties it: row
+    totals of the aggregated graph against numpy (exact weights)."""
+    r = np.random.default_rng(n + communities)
+    i = np.arange(n // 2 - 1, dtype=np.int64)   # the second half has no entries
+    g = _csr(n, i, i + 1, True, n)
+    m = r.integers(0, communities, n).astype(np.int32)
+    ctx.load_graph(g)
+    n2, off, col, w = ctx.step_aggregate(m)
+    used, mr = np.unique(m, return_inverse=True)
+    assert n2 == used.shape[0]
+    row = np.repeat(np.arange(n), np.diff(g.offsets))
+    key, at = np.unique(mr[row].astype(np.int64) * n2 + mr[g.cols], return_inverse=True)
+    ref = np.bincount(at, weights=g.weights_f64())
+    got = np.repeat(np.arange(n2), np.diff(off)) * np.int64(n2) + col
+    o = np.argsort(got)
+    assert np.array_equal(got[o], key) and np.array_equal(w[o], ref)
