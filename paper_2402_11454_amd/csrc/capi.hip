@@ -204,6 +204,8 @@ struct gsp_ctx {
         return st;
     }
     gsp_status fail_hip(hipError_t e, const char *what) {
+        // nothing of the failed call may post into the box of the next
+        if (stream) (void)hipStreamSynchronize(stream);
         err = std::string(what) + ": " + hipGetErrorString(e);
         return e == hipErrorOutOfMemory ? GSP_ENOMEM : GSP_EHIP;
     }
