@@ -13,7 +13,7 @@
 // cycles for the row's entries from memory, 1700 for the compare-and-swaps,
 // which share one LDS) and 15 us for its split and aggregation.  Whole runs:
 // 1,013 vertices 2.60 -> 0.54 ms, 10,000 vertices (the first level goes
-// through the level-wide kernels) 3.80 -> 1.84 ms.  The entries stay in
+// through the level-wide kernels) 3.80 -> 1.84 ms, 1.50 since.  The entries stay in
 // memory, read once per scan; beyond rest_entries the one compute unit's rate
 // costs more than the launches do, and beyond kRestVertices the state does
 // not fit the LDS.
