@@ -53,7 +53,8 @@ def run_workload(runs: int, workload: str, learned: bool, order: str = "auto", l
     if learned:
         ctx.pruner_set(load_params(DEFAULT_OUT))
         from bench import WORKLOADS
-        kw.update(prune_mode=gsp.PRUNE_LEARNED, prune_threshold=THETA_BY_CLASS[WORKLOADS[workload]["kind"]])
+        # the bench's timed runs launch every scan by itself (timing = 2)
+        kw.update(prune_mode=gsp.PRUNE_LEARNED, prune_threshold=THETA_BY_CLASS[WORKLOADS[workload]["kind"]], timing=2)
     if leiden:
         kw.update(leiden=1)
     for k in range(runs):
