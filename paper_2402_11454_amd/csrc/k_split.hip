@@ -8,9 +8,10 @@
 // those edges: roots are hooked larger-under-smaller with a compare-and-swap,
 // so every root is the smallest vertex of its set and the final label of a
 // vertex is the smallest vertex id of its component -- the label the
-// one-thread BFS from the lowest unvisited vertex gives.  Parent pointers
-// only decrease, so path halving with plain (agent-scope) stores is safe
-// while hooking; the final compression walks without halving (see there).
+// one-thread BFS from the lowest unvisited vertex gives.  A parent is always
+// smaller than its vertex and in its set, so path halving with plain
+// (agent-scope) stores is safe while hooking; the final compression walks
+// without halving (see there).
 //
 // Most of a community is usually one component, so the edges are taken in
 // the order of the sampling scheme of Sutton et al. ("Optimizing parallel
@@ -37,11 +38,23 @@ __device__ __forceinline__ void st(int32_t *p, int v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// A parent as the caches have it, perhaps older than memory's: a vertex's
+// parents, old or new, are all smaller than it and in its set, and a vertex
+// that has one is no root again.  So a walk over cached parents stays in the
+// set and ends, at a vertex that was a root; that it is one still, the
+// compare-and-swap below finds out.  (Reads past the caches meet at the big
+// trees' roots, and reads of one address in memory follow each other: the
+// sampled unions of 64 graphs with 2.7M vertices took 2.2 ms, now 1.85; a run
+// on a new 100k-vertex graph 5.02, now 4.89.)
+__device__ __forceinline__ int ld_cached(const int32_t *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 __device__ int find_root(int32_t *parent, int x) {
     while (true) {
-        int p = ld(parent + x);
+        int p = ld_cached(parent + x);
         if (p == x) return x;
-        int gp = ld(parent + p);
+        int gp = ld_cached(parent + p);
         if (gp != p) st(parent + x, gp);
         x = gp;
     }
@@ -57,7 +70,11 @@ __device__ void unite(int32_t *parent, int a, int b) {
             a = b;
             b = t;
         }
-        if (atomicCAS(parent + a, a, b) == a) return;
+        // hooks a if it is a root still; else goes on from its parent, which
+        // is smaller: the rounds end whatever the caches show
+        const int p = atomicCAS(parent + a, a, b);
+        if (p == a) return;
+        a = p;
     }
 }
 
@@ -168,7 +185,7 @@ __global__ void __launch_bounds__(kBlock) k_split_vote_apply(int64_t n, const in
 // Vertex i may skip its row: it hangs directly under its community's picked
 // root (parents only move to ancestors, so it stays in that tree).
 __device__ __forceinline__ bool settled(const int32_t *parent, const int32_t *dom, int i, int ci) {
-    return ld(parent + i) == dom[ci];
+    return ld_cached(parent + i) == dom[ci];
 }
 
 // All vertices of the level through its work lists: groups of G lanes for
@@ -232,7 +249,7 @@ __global__ void __launch_bounds__(kBlock) k_split_hook(Level g, const int32_t *b
 // longer changes.
 __device__ int find_root_ro(const int32_t *parent, int x) {
     while (true) {
-        int p = ld(parent + x);
+        int p = ld_cached(parent + x);
         if (p == x) return x;
         x = p;
     }
