@@ -362,3 +362,35 @@ def test_aggregation_counts_in_kept_tables(ctx, n, communities):
     got = np.repeat(np.arange(n2), np.diff(off)) * np.int64(n2) + col
     o = np.argsort(got)
     assert np.array_equal(got[o], key) and np.array_equal(w[o], ref)
+
+
+def test_contexts_in_threads(ctx):
+    """Each context waits on a buffer of its own: four threads with a context
+    and a stream each, running side by side, repeat the oracle's results."""
+    import threading
+    gs = [gi.rmat_small(12, 5), gi.planted_sbm_10k(), _dense(300, 0.2, True, 3), _path(20000, 12000, False)]
+    want = [oracle.louvain(g, 1e-2, 10, sync=True, rounds=8).membership for g in gs]
+    bad = []
+
+    def work(k):
+        try:
+            c = gsp.Context(0)
+            for _ in range(5):
+                for q in (k, (k + 1) % len(gs)):
+                    c.load_graph(gs[q])
+                    if not np.array_equal(c.louvain(1e-2, 10).membership, want[q]):
+                        bad.append((k, q))
+            c.load_batch(gs)
+            c.run_batch(1e-2, 10)
+            bad.extend((k, "batch", q) for q in range(len(gs))
+                       if not np.array_equal(c.batch_membership(q), want[q]))
+            c.close()
+        except Exception as e:   # reported below, in the test's own thread
+            bad.append((k, repr(e)))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(100)
+    assert not any(t.is_alive() for t in threads) and not bad
