@@ -1462,9 +1462,9 @@ __global__ void __launch_bounds__(kKeptThreads) k_community_totals_kept(const do
         own = (int)group_sum_ll<kWave>(own);
         if (own && lane_id() == 0) atomicAdd(&taken, own);
         __syncthreads();
-        const bool last = i0 + (int64_t)gridDim.x * kTile >= n;
-        if (last || taken > kKeptTable / 2) {   // the same in every thread
-            __syncthreads();
+        const bool empty = taken > kKeptTable / 2 || i0 + (int64_t)gridDim.x * kTile >= n;
+        __syncthreads();   // every thread has read the count before any adds the next tile's to it
+        if (empty) {
             if (tid == 0) taken = 0;
 #pragma unroll
             for (int r = 0; r < kKeptTable / kKeptThreads; r++) {

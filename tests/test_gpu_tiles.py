@@ -330,6 +330,27 @@ def test_community_totals_in_kept_tables(ctx, n, communities):
     assert abs(ctx.modularity(m) - _modularity(g, m)) <= 1e-12
 
 
+@pytest.mark.parametrize("communities", [1, 6000, 200000, 2700001])
+def test_community_totals_emptied_in_mid_range(ctx, communities):
+    """Five or six tiles of 2,048 vertices per workgroup: any three of them
+    hold more communities than half a table, so it is emptied and used again
+    before the last (6,000: once or twice; more: every third tile).  Totals by
+    the modularity, totals and sizes by a step's decisions (a third of the
+    vertices alone in their communities)."""
+    n = 2700001
+    r = np.random.default_rng(communities)
+    g = _csr(n, np.arange(n - 1, dtype=np.int64), np.arange(1, n, dtype=np.int64), True, n)
+    ctx.load_graph(g)
+    m = r.integers(0, communities, n).astype(np.int32)
+    assert abs(ctx.modularity(m) - _modularity(g, m)) <= 1e-12
+    if communities < n:
+        alone = np.flatnonzero(r.integers(0, 3, n) == 0)
+        m[alone[alone >= communities]] = alone[alone >= communities]
+    dec, gain, moved = ctx.step_move(m)
+    ref = oracle.move_sync_step(g, m)
+    assert np.array_equal(dec, ref[0])
+
+
 @pytest.mark.parametrize("n, sub_rounds", [(524288, 8), (524289, 8), (524289, 64), (530001, 1)])
 def test_work_lists_in_wide_tiles(ctx, n, sub_rounds):
     """Above 524,288 vertices the work lists are filled in tiles of 4,096."""
