@@ -140,8 +140,9 @@ __global__ void __launch_bounds__(kKeptThreads) k_agg_count_kept(Level g, const 
         own = (int)group_sum_ll<kWave>(own);
         if (own && lane_id() == 0) atomicAdd(&taken, own);
         __syncthreads();
-        if (t0 + kKeptTile >= hi || taken > kKeptTable / 2) {   // the same in every thread
-            __syncthreads();
+        const bool empty = taken > kKeptTable / 2 || t0 + kKeptTile >= hi;
+        __syncthreads();   // every thread has read the count before any adds the next tile's to it
+        if (empty) {
             if (tid == 0) taken = 0;
 #pragma unroll
             for (int r = 0; r < kKeptTable / kKeptThreads; r++) {

@@ -385,6 +385,29 @@ def test_aggregation_counts_in_kept_tables(ctx, n, communities):
     assert np.array_equal(got[o], key) and np.array_equal(w[o], ref)
 
 
+@pytest.mark.parametrize("communities", [6000, 200000, 330000])
+def test_aggregation_counts_emptied_in_mid_range(ctx, communities):
+    """Six tiles of 2,048 vertices per workgroup: its table is emptied, and the
+    vertices placed, before the last tile and again after (6,000 communities:
+    about every fourth tile; more: every third): members, degrees and row
+    totals of the aggregated graph against numpy (exact weights)."""
+    n = 2700001
+    r = np.random.default_rng(communities)
+    i = np.arange(n - 1, dtype=np.int64)[r.integers(0, 3, n - 1) > 0]   # some vertices have no entries
+    g = _csr(n, i, i + 1, True, n)
+    m = r.integers(0, communities, n).astype(np.int32)
+    ctx.load_graph(g)
+    n2, off, col, w = ctx.step_aggregate(m)
+    used, mr = np.unique(m, return_inverse=True)
+    assert n2 == used.shape[0]
+    row = np.repeat(np.arange(n), np.diff(g.offsets))
+    key, at = np.unique(mr[row].astype(np.int64) * n2 + mr[g.cols], return_inverse=True)
+    ref = np.bincount(at, weights=g.weights_f64())
+    got = np.repeat(np.arange(n2), np.diff(off)) * np.int64(n2) + col
+    o = np.argsort(got)
+    assert np.array_equal(got[o], key) and np.array_equal(w[o], ref)
+
+
 def test_contexts_in_threads(ctx):
     """Each context waits on a buffer of its own: four threads with a context
     and a stream each, running side by side, repeat the oracle's results."""
