@@ -1023,12 +1023,15 @@ __global__ void __launch_bounds__(kBlock) k_hub_gather(MoveArgs a) {
     Acc acc;
     for (int64_t k = a.ch_first + blockIdx.x; k < a.ch_first + a.ch_count; k += gridDim.x) {
         int i = a.ch_vert[k];
-        // 0: not in this sub-round's frontier; 3: the hub goes through its
-        // global table (set by the chunk kernel, or by a partition that
-        // overflowed: the decision kernel takes it)
-        if (a.hub_act[i] != 1) continue;
+        // 0: not in this sub-round's frontier; more chunks than max_parts: the
+        // hub goes through its global table.  A partition that overflows
+        // sends its hub there too (3) while other workgroups gather the hub's
+        // other partitions: 1 and 3 are the same here, so that the threads
+        // of a workgroup take the barriers below together whichever they see
+        if (a.hub_act[i] == 0) continue;
         int di = a.g.deg[i];
         int P = (di + kHubChunk - 1) / kHubChunk;
+        if (P > a.max_parts) continue;
         {
         int p = (int)((a.ch_beg[k] - a.g.off[i]) / kHubChunk);
         const uint32_t *words = a.hbuck + a.hub_b0[i];

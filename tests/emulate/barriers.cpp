@@ -40,6 +40,89 @@ static int totals(int waves) {
 static int run(int waves) { return totals<true>(waves) ? 1 : totals<false>(waves); }
 #endif
 
+#ifdef HUBS
+// A hub of three partitions; at some instant another workgroup, whose
+// partition overflowed, marks the hub for its global table.
+static int run(int) {
+    const int D = 2 * kHubChunk + 500, P = 3, comm = 3000;
+    std::mt19937 r(3);
+    std::vector<int64_t> off(D + 2), ch_beg = {0, kHubChunk, 2 * kHubChunk}, hub_b0(D + 1, 0);
+    std::vector<int32_t> col(D), deg(D + 1, 0), cm(D + 1), csize(D + 1, 1), ch_vert(P, 0);
+    std::vector<float> w(D);
+    std::vector<double> K(D + 1, 1.0), sig(comm, 0.0), part_g(P), part_kid(P), sval(D);
+    std::vector<int> part_c(P), skey(D);
+    std::vector<uint32_t> hbuck(P * P);
+    std::vector<uint8_t> act(D + 1, 0);
+    std::vector<IterCounters> ctr(1);
+    deg[0] = D;
+    for (int v = 1; v <= D + 1; v++) off[v] = D;
+    for (int e = 0; e < D; e++) {
+        col[e] = e + 1;
+        w[e] = (float)(1 + r() % 7) / 4.0f;
+    }
+    for (int v = 0; v <= D; v++) cm[v] = (int32_t)(r() % comm);
+    for (double &x : sig) x = (double)(r() % 50);
+    MoveArgs a = {};
+    a.g.n = D + 1;
+    a.g.nnz = D;
+    a.g.off = off.data();
+    a.g.col = col.data();
+    a.g.w = w.data();
+    a.g.wt = W_F32;
+    a.g.deg = deg.data();
+    a.K = K.data();
+    a.sig = sig.data();
+    a.csize = csize.data();
+    a.cm = cm.data();
+    a.M2 = 64.0;
+    a.ctr = ctr.data();
+    a.ch_vert = ch_vert.data();
+    a.ch_beg = ch_beg.data();
+    a.ch_count = P;
+    a.hub_act = act.data();
+    a.part_g = part_g.data();
+    a.part_kid = part_kid.data();
+    a.part_c = part_c.data();
+    a.max_parts = kMaxParts;
+    a.skey = skey.data();
+    a.sval = sval.data();
+    a.hbuck = hbuck.data();
+    a.hub_b0 = hub_b0.data();
+    std::vector<double> tot(comm, 0.0), best(P, -INFINITY), kid(P, 0.0);
+    std::vector<int> at(P, kIntMax);
+    for (int e = 0; e < D; e++) tot[cm[e + 1]] += (double)w[e];
+    for (int c = 0; c < comm; c++) {
+        if (tot[c] == 0.0) continue;
+        const int p = part_of(c, P);
+        const double g = a.M2 * tot[c] - K[0] * sig[c];
+        if (c == cm[0])
+            kid[p] = tot[c];
+        else if (better(g, c, best[p], at[p], nullptr)) {
+            best[p] = g;
+            at[p] = c;
+        }
+    }
+    act[0] = 1;
+    emu::launch(P, kBlock, 0, [&] { k_hub_bucket<W_F32>(a); });
+    long instants = 1;
+    for (long k = 0; k < instants; k++) {
+        long now = 0;
+        act[0] = 1;
+        emu::after_wave = [&](int) {
+            if (now++ == k) act[0] = 3;
+        };
+        emu::launch(1, kBlock, kBlock / kWave - 1, [&] { k_hub_gather<W_F32>(a); });
+        emu::after_wave = nullptr;
+        instants = now;
+        // the hub goes through its global table then, whatever is here; a
+        // partition that was gathered is right all the same
+        for (int p = 0; p < P && k + 1 == instants; p++)
+            if (part_g[p] != best[p] || part_c[p] != at[p] || part_kid[p] != kid[p]) return fail("partition", p);
+    }
+    return 0;
+}
+#endif
+
 #ifdef PLACES
 // As the totals: members, degrees and places, some members without entries.
 static int run(int waves) {

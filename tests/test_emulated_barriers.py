@@ -15,7 +15,7 @@ EMULATE = os.path.join(ROOT, "tests", "emulate")
 
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
-@pytest.mark.parametrize("case, source", [("TOTALS", "k_move.hip"), ("PLACES", "k_aggregate.hip")])
+@pytest.mark.parametrize("case, source", [("TOTALS", "k_move.hip"), ("PLACES", "k_aggregate.hip"), ("HUBS", "k_move.hip")])
 def test_barriers_are_met_by_all(tmp_path, case, source):
     with open(os.path.join(CSRC, source)) as f:
         kernels = f.read().split("}  // namespace\n")[0]   # the kernels come first
