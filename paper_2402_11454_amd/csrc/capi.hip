@@ -226,16 +226,16 @@ struct gsp_ctx {
                 return;
             }
     }
-    // A box that holds `words`; nothing may be under way.
+    // A box that holds `words`; nothing may be under way.  Without memory for
+    // a larger one the context keeps the one it has.
     hipError_t ensure_box(int64_t words) {
         if (words <= box_words) return hipSuccess;
+        uint64_t *p = nullptr;
+        hipError_t e = hipHostMalloc((void **)&p, (kBoxHead + words) * sizeof(uint64_t) + words, hipHostMallocCoherent);
+        if (e != hipSuccess) return e;
         if (stream) (void)hipStreamSynchronize(stream);
         if (box) (void)hipHostFree(box);
-        box = nullptr;
-        box_words = 0;
-        hipError_t e = hipHostMalloc((void **)&box, (kBoxHead + words) * sizeof(uint64_t) + words,
-                                     hipHostMallocCoherent);
-        if (e != hipSuccess) return e;
+        box = p;
         box_words = words;
         act_h = reinterpret_cast<uint8_t *>(box + kBoxHead + words);
         sc.box = box;
