@@ -206,6 +206,7 @@ struct gsp_ctx {
     gsp_status fail_hip(hipError_t e, const char *what) {
         // nothing of the failed call may post into the box of the next
         if (stream) (void)hipStreamSynchronize(stream);
+        (void)hipGetLastError();   // reported here: the next call is not to report it again
         err = std::string(what) + ": " + hipGetErrorString(e);
         return e == hipErrorOutOfMemory ? GSP_ENOMEM : GSP_EHIP;
     }

@@ -47,16 +47,17 @@ int hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t sh
 int hipGetDeviceCount(int *n) { *n = 1; return 0; }
 int hipGetDevice(int *d) { *d = 0; return 0; }
 int hipSetDevice(int d) { (void)d; return 0; }
-int hipGetLastError(void) { return 0; }
+static int last_error;   /* kept until it is asked for */
+int hipGetLastError(void) { int e = last_error; last_error = 0; return e; }
 const char *hipGetErrorString(int e) { (void)e; return "a fake error"; }
 int hipStreamCreateWithFlags(void **s, unsigned f) { (void)f; *s = malloc(1); return 0; }
 int hipStreamDestroy(void *s) { free(s); return 0; }
 int hipStreamSynchronize(void *s) { (void)s; return 0; }
-int hipMalloc(void **p, size_t n) { *p = calloc(n ? n : 1, 1); return *p ? 0 : 2; }
+int hipMalloc(void **p, size_t n) { *p = calloc(n ? n : 1, 1); return *p ? 0 : (last_error = 2); }
 int hipFree(void *p) { free(p); return 0; }
 int hipHostMalloc(void **p, size_t n, unsigned f) {
     (void)f;
-    if (n > fake_pinned_limit) return 2;   /* out of memory; *p stays as it is */
+    if (n > fake_pinned_limit) return last_error = 2;   /* out of memory; *p stays as it is */
     *p = calloc(n, 1);
     fake_pinned_alive++;
     return 0;
