@@ -252,6 +252,36 @@ struct gsp_ctx {
         mem_used += bytes;
         return (T *)p;
     }
+    // Buffers that are used only together: all of them, or on a failure none
+    // (a later call finds the group missing and asks for it again).
+    struct Want {
+        void *slot = nullptr;   // the pointer to fill (none: nothing to allocate)
+        size_t bytes = 0;
+        const char *what = "";
+    };
+    template <class T>
+    static Want want(T *&p, int64_t count, const char *what) {
+        return {&p, (size_t)std::max<int64_t>(count, 1) * sizeof(T), what};
+    }
+    gsp_status dalloc_all(std::initializer_list<Want> list) {
+        const size_t had = allocs.size();
+        const uint64_t used = mem_used;
+        for (const Want &w : list) {
+            if (!w.slot) continue;
+            hipError_t e = hipSuccess;
+            void *p = dalloc<uint8_t>(w.bytes, &e);
+            memcpy(w.slot, &p, sizeof(p));
+            if (e == hipSuccess) continue;
+            p = nullptr;
+            for (const Want &v : list)
+                if (v.slot) memcpy(v.slot, &p, sizeof(p));
+            for (size_t k = had; k < allocs.size(); k++) (void)hipFree(allocs[k]);
+            allocs.resize(had);
+            mem_used = used;
+            return fail_hip(e, w.what);
+        }
+        return GSP_OK;
+    }
     void free_graph() {
         if (stream) (void)hipStreamSynchronize(stream);
         drop_sweep_graphs();
@@ -478,20 +508,13 @@ struct PhaseCfg {
 
 gsp_status ensure_gate_state(gsp_ctx *ctx) {
     if (ctx->hbits) return GSP_OK;
-    hipError_t e = hipSuccess;
-    ctx->hfrac = ctx->dalloc<float>(ctx->n, &e);
-    if (e != hipSuccess) return ctx->fail_hip(e, "hipMalloc(gate history)");
-    ctx->hgain = ctx->dalloc<float>(ctx->n, &e);
-    if (e != hipSuccess) return ctx->fail_hip(e, "hipMalloc(gate history)");
-    ctx->hbits = ctx->dalloc<uint8_t>(ctx->n, &e);
-    if (e != hipSuccess) return ctx->fail_hip(e, "hipMalloc(gate history)");
-    ctx->dmoved = ctx->dalloc<double>(ctx->n, &e);
-    if (e != hipSuccess) return ctx->fail_hip(e, "hipMalloc(gate history)");
-    ctx->dsnap = ctx->dalloc<double>(ctx->n, &e);
-    if (e != hipSuccess) return ctx->fail_hip(e, "hipMalloc(gate history)");
-    ctx->cand = ctx->dalloc<int32_t>(ctx->n, &e);
-    if (e != hipSuccess) return ctx->fail_hip(e, "hipMalloc(gate candidates)");
-    return GSP_OK;
+    const int64_t n = ctx->n;
+    return ctx->dalloc_all({ctx->want(ctx->hfrac, n, "hipMalloc(gate history)"),
+                            ctx->want(ctx->hgain, n, "hipMalloc(gate history)"),
+                            ctx->want(ctx->hbits, n, "hipMalloc(gate history)"),
+                            ctx->want(ctx->dmoved, n, "hipMalloc(gate history)"),
+                            ctx->want(ctx->dsnap, n, "hipMalloc(gate history)"),
+                            ctx->want(ctx->cand, n, "hipMalloc(gate candidates)")});
 }
 
 GateNet net_of(const gsp_ctx *ctx) {
@@ -918,40 +941,29 @@ gsp_status ensure_levels(gsp_ctx *ctx) {
         if (ctx->mem_used + need > ctx->mem_limit)
             return ctx->fail(GSP_ENOMEM, "device memory limit (mem_limit_bytes) reached");
     }
-    hipError_t e = hipSuccess;
-    for (int k = 0; k < 2; k++) {
-        ctx->offL[k] = ctx->dalloc<int64_t>(ctx->n + 1, &e);
-        if (e != hipSuccess) return ctx->fail_hip(e, "hipMalloc(level offsets)");
-        ctx->colL[k] = ctx->dalloc<int32_t>(ctx->nnz, &e);
-        if (e != hipSuccess) return ctx->fail_hip(e, "hipMalloc(level columns)");
-        ctx->wL[k] = ctx->dalloc<double>(ctx->nnz, &e);
-        if (e != hipSuccess) return ctx->fail_hip(e, "hipMalloc(level weights)");
-        ctx->degL[k] = ctx->dalloc<int32_t>(ctx->n, &e);
-        if (e != hipSuccess) return ctx->fail_hip(e, "hipMalloc(level degrees)");
-        ctx->KL[k] = ctx->dalloc<double>(ctx->n, &e);
-        if (e != hipSuccess) return ctx->fail_hip(e, "hipMalloc(level weights K)");
-    }
-    ctx->gap_col = ctx->dalloc<int32_t>(ctx->nnz, &e);
-    if (e != hipSuccess) return ctx->fail_hip(e, "hipMalloc(gap columns)");
-    ctx->gap_w = ctx->dalloc<double>(ctx->nnz, &e);
-    if (e != hipSuccess) return ctx->fail_hip(e, "hipMalloc(gap weights)");
-    ctx->mhist = ctx->dalloc<int64_t>(ctx->n, &e);
-    if (e != hipSuccess) return ctx->fail_hip(e, "hipMalloc(move records)");
-    ctx->iter_dev = ctx->dalloc<int64_t>(2, &e);
-    if (e != hipSuccess) return ctx->fail_hip(e, "hipMalloc(sweep index)");
-    return GSP_OK;
+    const int64_t n = ctx->n, nnz = ctx->nnz;
+    return ctx->dalloc_all({ctx->want(ctx->offL[0], n + 1, "hipMalloc(level offsets)"),
+                            ctx->want(ctx->colL[0], nnz, "hipMalloc(level columns)"),
+                            ctx->want(ctx->wL[0], nnz, "hipMalloc(level weights)"),
+                            ctx->want(ctx->degL[0], n, "hipMalloc(level degrees)"),
+                            ctx->want(ctx->KL[0], n, "hipMalloc(level weights K)"),
+                            ctx->want(ctx->offL[1], n + 1, "hipMalloc(level offsets)"),
+                            ctx->want(ctx->colL[1], nnz, "hipMalloc(level columns)"),
+                            ctx->want(ctx->wL[1], nnz, "hipMalloc(level weights)"),
+                            ctx->want(ctx->degL[1], n, "hipMalloc(level degrees)"),
+                            ctx->want(ctx->KL[1], n, "hipMalloc(level weights K)"),
+                            ctx->want(ctx->gap_col, nnz, "hipMalloc(gap columns)"),
+                            ctx->want(ctx->gap_w, nnz, "hipMalloc(gap weights)"),
+                            ctx->want(ctx->mhist, n, "hipMalloc(move records)"),
+                            ctx->want(ctx->iter_dev, 2, "hipMalloc(sweep index)")});
 }
 
 gsp_status ensure_leiden(gsp_ctx *ctx) {
     if (ctx->bnd) return GSP_OK;
     if (ctx->mem_limit && ctx->mem_used + 8 * (uint64_t)ctx->n + 16 > ctx->mem_limit)
         return ctx->fail(GSP_ENOMEM, "device memory limit (mem_limit_bytes) reached (refinement)");
-    hipError_t e = hipSuccess;
-    ctx->bnd = ctx->dalloc<int32_t>(ctx->n, &e);
-    if (e != hipSuccess) return ctx->fail_hip(e, "hipMalloc(bound communities)");
-    ctx->bstart = ctx->dalloc<int32_t>(ctx->n, &e);
-    if (e != hipSuccess) return ctx->fail_hip(e, "hipMalloc(starting communities)");
-    return GSP_OK;
+    return ctx->dalloc_all({ctx->want(ctx->bnd, ctx->n, "hipMalloc(bound communities)"),
+                            ctx->want(ctx->bstart, ctx->n, "hipMalloc(starting communities)")});
 }
 
 // GSP-Leiden's refinement of level g (Section 3.5, read greedily) within the
@@ -1019,19 +1031,19 @@ gsp_status ensure_order(gsp_ctx *ctx, int rounds) {
         if (ctx->mem_used + order_bytes(ctx) > ctx->mem_limit)
             return ctx->fail(GSP_ENOMEM, "device memory limit (mem_limit_bytes) reached (degree order)");
     }
-    hipError_t e = hipSuccess;
     DegreeOrder o;
-    auto fail = [&](const char *what) { return ctx->fail_hip(e, what); };
-    if (!(o.orig = ctx->dalloc<int32_t>(n, &e))) return fail("hipMalloc(order)");
-    if (!(o.rank = ctx->dalloc<int32_t>(n, &e))) return fail("hipMalloc(order rank)");
-    if (!(o.deg = ctx->dalloc<int32_t>(n, &e))) return fail("hipMalloc(order degrees)");
-    if (!(o.off = ctx->dalloc<int64_t>(n + 1, &e))) return fail("hipMalloc(order offsets)");
-    if (!(o.col = ctx->dalloc<int32_t>(nnz, &e))) return fail("hipMalloc(order columns)");
-    if (wb == 4 && !(o.w = ctx->dalloc<float>(nnz, &e))) return fail("hipMalloc(order weights)");
-    if (wb == 8 && !(o.w = ctx->dalloc<double>(nnz, &e))) return fail("hipMalloc(order weights)");
-    if (!(o.hist = ctx->dalloc<unsigned long long>(2 * kOrderBucketsMax, &e))) return fail("hipMalloc(order counters)");
-    double *K = ctx->dalloc<double>(n, &e);
-    if (!K) return fail("hipMalloc(order K)");
+    double *K = nullptr;
+    uint8_t *w = nullptr;
+    gsp_status st = ctx->dalloc_all({ctx->want(o.orig, n, "hipMalloc(order)"),
+                                     ctx->want(o.rank, n, "hipMalloc(order rank)"),
+                                     ctx->want(o.deg, n, "hipMalloc(order degrees)"),
+                                     ctx->want(o.off, n + 1, "hipMalloc(order offsets)"),
+                                     ctx->want(o.col, nnz, "hipMalloc(order columns)"),
+                                     wb ? ctx->want(w, nnz * wb, "hipMalloc(order weights)") : gsp_ctx::Want(),
+                                     ctx->want(o.hist, 2 * kOrderBucketsMax, "hipMalloc(order counters)"),
+                                     ctx->want(K, n, "hipMalloc(order K)")});
+    if (st != GSP_OK) return st;
+    o.w = w;
     HIP_TRY(order_by_degree(level0(ctx), ctx->sc, o, rounds, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
     ctx->ord = o;
