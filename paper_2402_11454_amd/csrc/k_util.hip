@@ -287,6 +287,13 @@ __global__ void __launch_bounds__(kBlock) k_vertex_weights_rows(Level g, double 
 // 2.29 -> 1.34 ms, a road-like graph of 31 M entries 3.07 -> 0.63 ms.
 constexpr int kInPer = 16;
 constexpr int kInTile = kBlock * kInPer;
+// A tile's rows are walked by its workgroup, empty ones among them; between
+// two ranges of ids there may be any number of those, and beyond this many
+// rows each entry searches the offsets for its own.  Measured on one tile of
+// a path, microseconds of the whole call, walked / searched: 16,384 empty
+// rows 109 / 124, 32,768 127 / 130, 65,536 160 / 127, 1M 1,170 / 144, 67M
+// 110,500 / 996.
+constexpr int64_t kInWalk = 8 * kInTile;
 
 // Largest r in [0, n) with off[r] <= e (off[0] = 0 <= e); by a whole wavefront.
 __device__ __forceinline__ int64_t wave_row_of(const int64_t *off, int64_t n, int64_t e) {
@@ -339,7 +346,22 @@ __global__ void __launch_bounds__(kBlock) k_inside_weight(Level g, const int32_t
         for (int k = 0; k < kInPer; k++) srow[k * kBlock + tid] = 0;
         __syncthreads();
         const int64_t r0 = sr[0], r1 = sr[1];
-        for (int64_t r = r0 + 1 + tid; r <= r1; r += kBlock) atomicMax(&srow[g.off[r] - e0], (int)(r - r0));
+        if (r1 - r0 <= kInWalk) {
+            for (int64_t r = r0 + 1 + tid; r <= r1; r += kBlock) atomicMax(&srow[g.off[r] - e0], (int)(r - r0));
+        } else {
+            int64_t top = 1;
+            while (2 * top <= r1 - r0) top *= 2;
+#pragma unroll 1
+            for (int k = 0; k < kInPer; k += 4) {   // four searches in step
+                int64_t lo[4] = {r0, r0, r0, r0};
+                for (int64_t step = top; step > 0; step >>= 1)
+#pragma unroll
+                    for (int q = 0; q < 4; q++)
+                        if (lo[q] + step <= r1 && g.off[lo[q] + step] <= e0 + (k + q) * kBlock + tid) lo[q] += step;
+#pragma unroll
+                for (int q = 0; q < 4; q++) srow[(k + q) * kBlock + tid] = (int)(lo[q] - r0);
+            }
+        }
         int cj[kInPer];
 #pragma unroll
         for (int k = 0; k < kInPer; k++) cj[k] = j[k] >= 0 ? memb[j[k]] : -1;

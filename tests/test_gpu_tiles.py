@@ -90,6 +90,34 @@ def test_modularity_at_the_tiles_edges(ctx, name, weighted, order):
         assert ctx.count_disconnected(m) == oracle.disconnected(g, m)[0]
 
 
+WALK = 8 * TILE   # rows between a tile's first and last entry that are walked
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("rows", [WALK - 1, WALK, WALK + 1, 3000000])
+def test_inside_weight_across_empty_rows(ctx, rows, weighted):
+    """A path whose ids leave empty rows in the middle of its second tile, so
+    that the tile spans `rows` rows, and of its last, which is not full; of a
+    single graph and, beside others, of a batch."""
+    a, b = TILE // 2, TILE   # the path's vertices that hold the second tile's first and last entry
+    ids = np.arange(2 * TILE - 300, dtype=np.int64)
+    ids[a + 700:] += rows - (b - a)
+    ids[-500:] += rows
+    n = int(ids[-1]) + 40
+    g = _csr(n, ids[:-1], ids[1:], weighted, 3)
+    row_of = np.repeat(np.arange(n), np.diff(g.offsets))
+    assert row_of[2 * TILE - 1] - row_of[TILE] == rows
+    ctx.load_graph(g)
+    for m in (np.zeros(n, np.int32), (np.arange(n) // 3).astype(np.int32), gi.random_membership(n, 7, 5)):
+        assert abs(ctx.modularity(m) - _modularity(g, m)) <= 1e-12
+    gs = [g, _path(40, 300, weighted), g]
+    ctx.load_batch(gs)
+    ctx.run_batch(1e-2, 10)
+    q = ctx.batch_modularity()
+    for k, h in enumerate(gs):
+        assert abs(q[k] - _modularity(h, ctx.batch_membership(k))) <= 1e-12
+
+
 @pytest.mark.parametrize("weighted", [False, True])
 def test_batch_modularity_with_many_graphs_in_a_tile(ctx, weighted):
     """Graphs of 2 to 4,098 entries side by side: several per tile, a tile
