@@ -1570,7 +1570,7 @@ gsp_status run_passes(gsp_ctx *ctx, double tolerance, int32_t max_passes, const 
                       !opt.return_moves && opt.split_mode == GSP_SPLIT_PASS && opt.split_algo == GSP_SPLIT_UF &&
                       opt.hub_global == 0 && opt.hub_max_parts == 0 && ctx->nnz < (int64_t(1) << 32);
     for (int lp = 0; lp < max_passes; lp++) {
-        if (rest && !g.orig && g.n <= kRestVertices && g.nnz <= rest_entries(g.n)) {
+        if (rest && !g.orig && g.n <= kRestVertices && g.nnz <= rest_entries(g.n, opt.sub_rounds)) {
             int taken = 0;
             st = run_rest(ctx, g, K, opt, tau, lp, max_passes - lp, next, &taken);
             if (st != GSP_OK) return st;

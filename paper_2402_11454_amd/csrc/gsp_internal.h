@@ -348,14 +348,21 @@ void launch_move_apply_compact(const MoveArgs &a, const MoveArgs &next, const Wo
 // fit (vertices, entries, a row beyond kBlockMaxDeg entries) or takes
 // more than kRestPasses passes; nothing of the graph has changed then.
 constexpr int kRestVertices = 1536;
-// Entries a level of n vertices may have: four times as many where every
-// wavefront has a dense table over the communities.  Measured on a run over
-// 100k vertices whose levels have 1,058, 404 and 316 of them with 455k, 150k
-// and 98k entries: 5.49 ms with this rule, 5.72 ms with 65,536 throughout (the
-// last two passes in level-wide kernels), 6.97 ms with 524,288 throughout (the
-// first level's rows, too long for seven dense tables to keep up with).
 constexpr int kRestDense = 512;
-__host__ __device__ inline int64_t rest_entries(int64_t n) { return n <= kRestDense ? 262144 : 65536; }
+// Entries a level of n vertices may have in a run with so many sub-rounds: in
+// all, four times as many where every wavefront has a dense table over the
+// communities, and 16,384 for each sub-round, as the one compute unit reads a
+// sweep's entries at its own rate while the level-wide kernels pay per
+// sub-round.  Random and block graphs of 64 to 1,536 vertices, the
+// level-wide kernels' time over this one's: 8 sub-rounds, 65,536 entries
+// 0.99 to 2; 98,304 up to 512 vertices 0.93 to 1.4 and beyond 0.75 to 1.15;
+// 131,072 up to 512 0.78 to 1.3; 261,632 0.44 to 0.63; 1 sub-round, 16,384 entries
+// 0.72 to 1.6, 32,768 0.67 to 1.2, 65,536 0.48 to 0.96; 64 sub-rounds, 262,144
+// 1.2 up to 512.
+__host__ __device__ inline int64_t rest_entries(int64_t n, int rounds) {
+    const int64_t all = n <= kRestDense ? 262144 : 65536, each = (int64_t)16384 * rounds;
+    return all < each ? all : each;
+}
 constexpr int kRestPasses = 64;
 struct RestOut {
     int status, passes, ncomm, sweeps;

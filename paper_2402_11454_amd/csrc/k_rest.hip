@@ -554,7 +554,7 @@ __global__ void __launch_bounds__(kT) k_rest_of_run(RestArgs a) {
         }
     if (ent) atomicAdd(&s.gain, ent);
     __syncthreads();
-    if (s.bad || s.gain > (unsigned long long)rest_entries(nv)) {
+    if (s.bad || s.gain > (unsigned long long)rest_entries(nv, 1 << a.shift)) {
         if (tid == 0) out->status = 1;
         return;
     }

@@ -276,6 +276,21 @@ def test_small_levels_in_one_launch(ctx, name, sub_rounds):
     _same_run(ctx, g, sub_rounds=sub_rounds)
 
 
+@pytest.mark.parametrize("over", [0, 1])
+@pytest.mark.parametrize("n, sub_rounds, entries", [(700, 1, 16384), (700, 2, 32768), (700, 8, 65536),
+                                                    (512, 1, 16384), (512, 8, 131072), (511, 16, 260610)])
+def test_small_levels_at_the_entries_limit(ctx, n, sub_rounds, entries, over):
+    """Exactly as many entries as one workgroup takes in a run with so many
+    sub-rounds, and two more (the last pair: a complete graph, and one edge
+    short of it)."""
+    u, v = np.triu_indices(n, 1)
+    m = min(entries // 2 + over, u.shape[0] - (1 - over))
+    k = np.random.default_rng(n + entries).permutation(u.shape[0])[:m]
+    g = _csr(n, u[k].astype(np.int64), v[k].astype(np.int64), True, entries)
+    ctx.load_graph(g)
+    _same_run(ctx, g, sub_rounds=sub_rounds)
+
+
 @pytest.mark.parametrize("kw", [dict(max_iterations=0), dict(max_iterations=1), dict(aggregation_tolerance=0.3),
                                 dict(aggregation_tolerance=1.0), dict(tolerance_drop=2.0)])
 @pytest.mark.parametrize("max_passes", [1, 2, 10])
