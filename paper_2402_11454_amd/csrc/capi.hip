@@ -1434,7 +1434,7 @@ gsp_status run_split(gsp_ctx *ctx, const Level &g, const WorkLists &wl, const in
         return GSP_OK;
     }
     launch_split(g, wl, cm, labels, ctx->sc.i32c, reinterpret_cast<uint32_t *>(ctx->sc.i32a),
-                 reinterpret_cast<unsigned long long *>(ctx->sc.i64a), s);
+                 reinterpret_cast<unsigned long long *>(ctx->sc.i64a), false, s);
     return GSP_OK;
 }
 
@@ -2063,7 +2063,7 @@ gsp_status gsp_count_disconnected(gsp_ctx *ctx, const int32_t *membership, int w
     WorkLists wl = make_lists(ctx);
     HIP_TRY(build_work_lists(g, 1, wl, ctx->sc, s));
     launch_split(g, wl, ctx->cm, ctx->lab, ctx->sc.i32c, reinterpret_cast<uint32_t *>(ctx->sc.i32a),
-                 reinterpret_cast<unsigned long long *>(ctx->sc.i64a), s);
+                 reinterpret_cast<unsigned long long *>(ctx->sc.i64a), true, s);
     HIP_TRY(hipMemsetAsync(ctx->sc.u64, 0, sizeof(unsigned long long), s));
     launch_count_disconnected(ctx->lab, ctx->cm, ctx->n, ctx->sc.i32a, ctx->sc.u64, s);
     HIP_TRY(hipMemcpyAsync(ctx->i64_h, ctx->sc.u64, sizeof(int64_t), hipMemcpyDeviceToHost, s));
@@ -2639,7 +2639,7 @@ gsp_status gsp_step_split(gsp_ctx *ctx, const int32_t *membership, int where, in
     WorkLists wl = make_lists(ctx);
     HIP_TRY(build_work_lists(g, 1, wl, ctx->sc, s));
     launch_split(g, wl, ctx->cm, ctx->lab, ctx->sc.i32c, reinterpret_cast<uint32_t *>(ctx->sc.i32a),
-                 reinterpret_cast<unsigned long long *>(ctx->sc.i64a), s);
+                 reinterpret_cast<unsigned long long *>(ctx->sc.i64a), true, s);
     HIP_TRY(hipGetLastError());
     st = copy_out(ctx, labels_out, ctx->lab, g.n, where);
     if (st != GSP_OK) return st;

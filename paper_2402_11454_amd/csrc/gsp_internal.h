@@ -447,9 +447,9 @@ void launch_batch_flag_confirm(const int32_t *gid, const uint8_t *gconfirm, int6
 // ---- k_split.hip ----
 // labels[i] = smallest vertex of i's component among same-community edges.
 // dom, vote_cnt, vote_best: scratch of n entries each (the picked root per
-// community and its vote)
+// community and its vote); given: cm is the caller's, not a run's
 void launch_split(const Level &g, const WorkLists &wl, const int32_t *cm, int32_t *labels, int32_t *dom,
-                  uint32_t *vote_cnt, unsigned long long *vote_best, hipStream_t s);
+                  uint32_t *vote_cnt, unsigned long long *vote_best, bool given, hipStream_t s);
 // The same labels by minimum-label propagation with pruning (Algorithm
 // splitDisconnectedLp with its pruning) and pointer jumping: next (n flags,
 // zero on return), q_small / q_large (n each) the rounds' queues, counts (4

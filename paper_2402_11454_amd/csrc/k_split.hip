@@ -50,21 +50,32 @@ __device__ __forceinline__ int ld_cached(const int32_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+template <bool FRESH = false>
 __device__ int find_root(int32_t *parent, int x) {
     while (true) {
-        int p = ld_cached(parent + x);
+        int p = FRESH ? ld(parent + x) : ld_cached(parent + x);
         if (p == x) return x;
-        int gp = ld_cached(parent + p);
+        int gp = FRESH ? ld(parent + p) : ld_cached(parent + p);
         if (gp != p) st(parent + x, gp);
         x = gp;
     }
 }
 
+// GIVEN: the communities are the caller's, one for the whole graph perhaps.
+// In a tree of that size the cached parents lag behind, and the hooks follow
+// them one failure after another; from the second on the walks go past the
+// caches.  One community, reads past the caches throughout / caches alone /
+// this: 300,000 vertices, 2.4M random edges 0.75 / 0.80 to 1.3 / 0.66 ms; 60,000
+// with a thousand each 3.0 / 1.6 / 2.4; a grid of 1M 2.0 / 1.2 / 1.6.  A run's
+// communities stay small until its levels are: there caches alone are the
+// faster (learned run on 1M vertices 15.7 ms, with this 16.1), and in the
+// allocation-free count, which hooks every entry (1.3 to 1.8, 3.3 to 4.4 ms).
+template <bool GIVEN>
 __device__ void unite(int32_t *parent, int a, int b) {
-    while (true) {
-        a = find_root(parent, a);
-        b = find_root(parent, b);
-        if (a == b) return;
+    a = find_root(parent, a);
+    b = find_root(parent, b);
+    bool failed = false;
+    while (a != b) {
         if (a < b) {
             int t = a;
             a = b;
@@ -74,12 +85,20 @@ __device__ void unite(int32_t *parent, int a, int b) {
         // is smaller: the rounds end whatever the caches show
         const int p = atomicCAS(parent + a, a, b);
         if (p == a) return;
-        a = p;
+        if (GIVEN && failed) {
+            a = find_root<true>(parent, p);
+            b = find_root<true>(parent, b);
+        } else {
+            a = find_root(parent, p);
+            b = find_root(parent, b);
+        }
+        failed = true;
     }
 }
 
+template <bool GIVEN>
 __device__ __forceinline__ void hook_entry(int32_t *parent, const int32_t *cm, int i, int ci, int j) {
-    if (j != i && cm[j] == ci) unite(parent, i, j);
+    if (j != i && cm[j] == ci) unite<GIVEN>(parent, i, j);
 }
 
 // Sampling: every vertex links to those of its first kSample neighbours that
@@ -88,6 +107,7 @@ __device__ __forceinline__ void hook_entry(int32_t *parent, const int32_t *cm, i
 // of the vertices outside the picked trees.)
 constexpr int kSample = 8;
 
+template <bool GIVEN>
 __global__ void __launch_bounds__(kBlock) k_split_sample(Level g, const int32_t *cm, int32_t *parent) {
     // one thread per (vertex, sample): the unions of a vertex run side by side
     const int64_t total = g.n * kSample;
@@ -95,7 +115,7 @@ __global__ void __launch_bounds__(kBlock) k_split_sample(Level g, const int32_t 
         const int i = (int)(t / kSample), r = (int)(t % kSample);
         if (r >= g.deg[i]) continue;
         const int j = g.col[g.off[i] + r];
-        if (j != i && cm[j] == cm[i]) unite(parent, i, j);
+        if (j != i && cm[j] == cm[i]) unite<GIVEN>(parent, i, j);
     }
 }
 
@@ -195,6 +215,7 @@ struct BinRanges {
     int64_t beg[kNumBins], n[kNumBins];
 };
 
+template <bool GIVEN>
 __global__ void __launch_bounds__(kBlock) k_split_hook(Level g, const int32_t *bl, BinRanges br,
                                                       const int32_t *ch_vert,
                                                       const int64_t *ch_beg, int64_t nchunks, const int32_t *cm,
@@ -220,7 +241,7 @@ __global__ void __launch_bounds__(kBlock) k_split_hook(Level g, const int32_t *b
             if (qi < binn[b]) {
                 int i = bl[binb[b] + qi];
                 int ci = cm[i];
-                if (gl < g.deg[i] && !settled(parent, dom, i, ci)) hook_entry(parent, cm, i, ci, g.col[g.off[i] + gl]);
+                if (gl < g.deg[i] && !settled(parent, dom, i, ci)) hook_entry<GIVEN>(parent, cm, i, ci, g.col[g.off[i] + gl]);
             }
         } else if (u < pre[kNumSmallBins] + uw) {
             int64_t qi = (u - pre[kNumSmallBins]) * (kBlock / kWave) + threadIdx.x / kWave;
@@ -230,7 +251,7 @@ __global__ void __launch_bounds__(kBlock) k_split_hook(Level g, const int32_t *b
                 int ci = cm[i];
                 int64_t beg = g.off[i];
                 if (!settled(parent, dom, i, ci))
-                    for (int e = lane_id(); e < g.deg[i]; e += kWave) hook_entry(parent, cm, i, ci, g.col[beg + e]);
+                    for (int e = lane_id(); e < g.deg[i]; e += kWave) hook_entry<GIVEN>(parent, cm, i, ci, g.col[beg + e]);
             }
         } else {
             int64_t k = u - pre[kNumSmallBins] - uw;
@@ -240,7 +261,7 @@ __global__ void __launch_bounds__(kBlock) k_split_hook(Level g, const int32_t *b
             int64_t end = g.off[i] + g.deg[i];
             if (end > beg + kHubChunk) end = beg + kHubChunk;
             if (!settled(parent, dom, i, ci))
-                for (int64_t e = beg + threadIdx.x; e < end; e += kBlock) hook_entry(parent, cm, i, ci, g.col[e]);
+                for (int64_t e = beg + threadIdx.x; e < end; e += kBlock) hook_entry<GIVEN>(parent, cm, i, ci, g.col[e]);
         }
     }
 }
@@ -476,7 +497,7 @@ __global__ void __launch_bounds__(kBlock) k_na_hook(const int64_t *off, const in
                     bad = true;
                     continue;
                 }
-                if (j != (int)i && memb[j] == ci) unite(parent, (int)i, j);
+                if (j != (int)i && memb[j] == ci) unite<false>(parent, (int)i, j);
             }
         if (bad) atomicOr(&flags[1], 1ull);
     }
@@ -504,10 +525,12 @@ inline unsigned grid1(int64_t n) {
 }  // namespace
 
 void launch_split(const Level &g, const WorkLists &wl, const int32_t *cm, int32_t *labels, int32_t *dom,
-                  uint32_t *vote_cnt, unsigned long long *vote_best, hipStream_t s) {
+                  uint32_t *vote_cnt, unsigned long long *vote_best, bool given, hipStream_t s) {
     if (g.n == 0) return;
     launch_iota_i32(labels, g.n, s);
-    k_split_sample<<<grid1(g.n * kSample), kBlock, 0, s>>>(g, cm, labels);
+    const auto sample = given ? k_split_sample<true> : k_split_sample<false>;
+    const auto hook = given ? k_split_hook<true> : k_split_hook<false>;
+    sample<<<grid1(g.n * kSample), kBlock, 0, s>>>(g, cm, labels);
     k_split_compress<<<grid1(g.n), kBlock, 0, s>>>(labels, g.n);
     k_split_pick<<<grid1(g.n), kBlock, 0, s>>>(labels, cm, g.n, dom);
     const int64_t ns = (g.n + kVoteStride - 1) / kVoteStride;
@@ -531,7 +554,7 @@ void launch_split(const Level &g, const WorkLists &wl, const int32_t *cm, int32_
     units += (wl.bin_size(BIN_WAVE) + wl.bin_size(BIN_BLOCK) + 3) / 4 + wl.nchunks;
     if (units > 0) {
         unsigned gr = (unsigned)(units < 65536 ? units : 65536);
-        k_split_hook<<<gr, kBlock, 0, s>>>(g, wl.bl, br, wl.ch_vert, wl.ch_beg, wl.nchunks, cm, dom, labels);
+        hook<<<gr, kBlock, 0, s>>>(g, wl.bl, br, wl.ch_vert, wl.ch_beg, wl.nchunks, cm, dom, labels);
     }
     k_split_compress<<<grid1(g.n), kBlock, 0, s>>>(labels, g.n);
 }
