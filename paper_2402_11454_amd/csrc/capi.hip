@@ -1439,7 +1439,7 @@ gsp_status run_split(gsp_ctx *ctx, const Level &g, const WorkLists &wl, const in
 }
 
 // The rest of a run of at most `left` passes from level g (pass lp, tolerance
-// tau) in one launch, *taken passes; 0, and nothing changed, if g does not fit.
+// tau) in one launch, *taken passes; 0 if g does not fit (g is as it was).
 gsp_status run_rest(gsp_ctx *ctx, const Level &g, const double *K, const gsp_options &opt, double tau, int lp,
                     int left, int next, int *taken) {
     hipStream_t s = ctx->stream;
@@ -1462,7 +1462,7 @@ gsp_status run_rest(gsp_ctx *ctx, const Level &g, const double *K, const gsp_opt
     a.w[1] = ctx->gap_w;
     a.label = ctx->cm;
     a.out = reinterpret_cast<RestOut *>(ctx->sc.u64);
-    launch_rest_of_run(a, 1, s);
+    launch_rest_of_run(a, s);
     PostArgs pa;
     pa.src[0] = a.out;
     pa.n[0] = sizeof(RestOut) / sizeof(uint64_t);

@@ -16,8 +16,9 @@ constexpr int kIntMax = 0x7fffffff;     // "no community" in an argmax
 
 // Degree bins.  A vertex (or a community, for aggregation) with d entries is
 // processed by:
-//   d <= 4, 8, 16, 32, 64 : a group of 4/8/16/32/64 lanes, one entry per lane,
-//                           table of 2*group slots in LDS;
+//   d <= 4, 8, 16, 32, 64 : a group of 4/8/16/32/64 lanes, one entry per lane
+//                           (local moving: a quarter of the lanes with up to
+//                           four entries each), table of 2*group slots in LDS;
 //   d <= 512              : one wavefront, table in LDS (1024 slots on unit
 //                           weights, 768 otherwise);
 //   d <= 2048             : one 256-thread workgroup, table in LDS (4096 slots
@@ -25,8 +26,8 @@ constexpr int kIntMax = 0x7fffffff;     // "no community" in an argmax
 //   d > 2048              : several workgroups, table of nextpow2(2d) slots in
 //                           global memory ("hub").
 // Every table is at most half full (the local-moving scan's wave and
-// workgroup tables on weighted graphs two thirds), so linear probing always
-// terminates.
+// workgroup tables on weighted graphs two thirds), and every probe sequence
+// goes over all of its slots, so a probe always ends.
 constexpr int kNumBins = 8;
 enum { BIN_G4 = 0, BIN_G8, BIN_G16, BIN_G32, BIN_G64, BIN_WAVE, BIN_BLOCK, BIN_HUB };
 constexpr int kNumSmallBins = 5;

@@ -339,14 +339,14 @@ void launch_move_apply(const MoveArgs &a, int64_t cap, hipStream_t s);
 void launch_move_apply_compact(const MoveArgs &a, const MoveArgs &next, const WorkLists &wl, hipStream_t s);
 
 // ---- k_rest.hip ----
-// The rest of a run on a small level (at most kRestVertices vertices and
-// rest_entries of them), a workgroup per graph: every remaining
-// pass of the level (or, of a batch, of graphs which[0..graphs)) with plain
-// pruning, the split in every pass and no options beyond those below.
-// label[v] <- the number of v's final community (from 0 within its graph,
-// in ascending order of the smallest vertex).  status 1: the graph does not
-// fit (vertices, entries, a row beyond kBlockMaxDeg entries) or takes
-// more than kRestPasses passes; nothing of the graph has changed then.
+// The rest of a single graph's run on a small level (at most kRestVertices
+// vertices and rest_entries of them), by one workgroup: every remaining pass
+// of the level with plain pruning, the split in every pass and no options
+// beyond those below.  label[v] <- the number of v's final community (in
+// ascending order of the smallest vertex).  status 1: the level does not fit
+// (vertices, entries, a row beyond kBlockMaxDeg entries), or takes more than
+// kRestPasses passes; label and the two buffers may be written then, the
+// level itself is as it was.
 constexpr int kRestVertices = 1536;
 constexpr int kRestDense = 512;
 // Entries a level of n vertices may have in a run with so many sub-rounds: in
@@ -373,15 +373,14 @@ struct RestArgs {
     Level g;
     const double *K = nullptr;
     double M2 = 0.0;
-    const int32_t *which = nullptr;   // batch: the graphs to run
     double tau = 0.0, tol_drop = 10.0, agg_tol = 0.8;
     int max_iter = 20, shift = 3, passes = 1;   // passes left, at least 1
     int32_t *col[2] = {nullptr, nullptr};       // two buffers for the levels to come, indexed
     double *w[2] = {nullptr, nullptr};          // like g's entries
     int32_t *label = nullptr;
-    RestOut *out = nullptr;                     // one per graph
+    RestOut *out = nullptr;
 };
-void launch_rest_of_run(const RestArgs &a, int graphs, hipStream_t s);
+void launch_rest_of_run(const RestArgs &a, hipStream_t s);
 
 // ---- k_leiden.hip ----
 // The same-bound subgraph of a level for GSP-Leiden's refinement: row i

@@ -1492,7 +1492,7 @@ inline unsigned cap_grid(int64_t units, int64_t cap) {
 // A kernel's cap under the run's launch schedule.
 inline int64_t sched_cap(const MoveArgs &a, int64_t cap) { return a.grid_cap > 0 && a.grid_cap < cap ? a.grid_cap : cap; }
 
-// One workgroup; the stripes are 18 KB, so it is a chain of one read, the
+// One workgroup; the stripes are 6 KB, so it is a chain of one read, the
 // stores to the host's memory and the flag behind them.  Clearing here and not
 // before the sweep saves the fill's launch.
 __global__ void __launch_bounds__(kBlock) k_sweep_end(IterCounters *ctr, unsigned long long *ggain,

@@ -1,4 +1,4 @@
-// k_rest.hip - the rest of a run on small levels: once a graph's level has at
+// k_rest.hip - the rest of a run on small levels: once a run's level has at
 // most kRestVertices vertices and rest_entries entries, one workgroup takes
 // it through every remaining pass of Algorithm "louvain" (local moving, split,
 // renumbering, the pass tests, aggregation) with the level's state in LDS.
@@ -526,13 +526,10 @@ __device__ __noinline__ void aggregate_level(const int32_t *col, const double *w
 __global__ void __launch_bounds__(kT) k_rest_of_run(RestArgs a) {
     State &s = state();
     const int tid = threadIdx.x;
-    const int gk = a.which ? a.which[blockIdx.x] : 0;
-    const int64_t vb = a.g.vbase ? a.g.vbase[gk] : 0;
-    const int64_t nv = a.g.vbase ? a.g.vbase[gk + 1] - vb : a.g.n;
-    const double m2 = a.g.M2g ? a.g.M2g[gk] : a.M2;
-    RestOut *out = a.out + blockIdx.x;
+    const double m2 = a.M2;
+    RestOut *out = a.out;
+    const int64_t nv = a.g.n;
     int n = (int)nv;
-    const int64_t base = a.g.off[vb];   // of the level's rows, and of this graph's part of the buffers
     // the level, and whether it fits
     if (tid == 0) {
         s.bad = nv > kN;
@@ -544,12 +541,12 @@ __global__ void __launch_bounds__(kT) k_rest_of_run(RestArgs a) {
     unsigned long long ent = 0;
     if (nv <= kN)
         for (int i = tid; i < n; i += kT) {
-            const int64_t b = a.g.off[vb + i] - base;
-            const int d = a.g.deg[vb + i];
+            const int64_t b = a.g.off[i];
+            const int d = a.g.deg[i];
             if (d > kBlockMaxDeg || b > 0xffffffffll) s.bad = 1;
             s.rowb[i] = (uint32_t)b;
             s.deg[i] = (uint16_t)d;
-            s.K[i] = a.K[vb + i];
+            s.K[i] = a.K[i];
             ent += (unsigned)d;
         }
     if (ent) atomicAdd(&s.gain, ent);
@@ -558,20 +555,20 @@ __global__ void __launch_bounds__(kT) k_rest_of_run(RestArgs a) {
         if (tid == 0) out->status = 1;
         return;
     }
-    // its columns, from 0, and its weights in fp64, into the first buffer
-    int32_t *col = a.col[0] + base;
-    double *w = a.w[0] + base;
+    // its columns, and its weights in fp64, into the first buffer
+    int32_t *col = a.col[0];
+    double *w = a.w[0];
     for (int i = tid / kLanes; i < n; i += kT / kLanes) {
         const int64_t b = s.rowb[i];
         for (int e = tid % kLanes; e < (int)s.deg[i]; e += kLanes) {
-            col[b + e] = a.g.col[base + b + e] - (int32_t)vb;
-            w[b + e] = entry_weight(a.g.w, a.g.wt, base + b + e);
+            col[b + e] = a.g.col[b + e];
+            w[b + e] = entry_weight(a.g.w, a.g.wt, b + e);
         }
     }
     __syncthreads();
     double tau = a.tau;
     int sweeps = 0, next = 1, passes = 0;
-    int32_t *label = a.label + vb;
+    int32_t *label = a.label;
     while (true) {
         const int li = move_phase(a.shift, a.max_iter, col, w, n, m2, tau);
         sweeps += li;
@@ -601,9 +598,9 @@ __global__ void __launch_bounds__(kT) k_rest_of_run(RestArgs a) {
             }
             break;
         }
-        aggregate_level(col, w, n, n2, a.col[next] + base, a.w[next] + base);
-        col = a.col[next] + base;
-        w = a.w[next] + base;
+        aggregate_level(col, w, n, n2, a.col[next], a.w[next]);
+        col = a.col[next];
+        w = a.w[next];
         n = n2;
         next ^= 1;
         tau = tau / a.tol_drop;
@@ -612,8 +609,6 @@ __global__ void __launch_bounds__(kT) k_rest_of_run(RestArgs a) {
 
 }  // namespace
 
-void launch_rest_of_run(const RestArgs &a, int graphs, hipStream_t s) {
-    if (graphs > 0) k_rest_of_run<<<graphs, kT, 0, s>>>(a);
-}
+void launch_rest_of_run(const RestArgs &a, hipStream_t s) { k_rest_of_run<<<1, kT, 0, s>>>(a); }
 
 }  // namespace gsp
