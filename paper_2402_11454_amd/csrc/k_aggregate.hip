@@ -91,9 +91,12 @@ __global__ void __launch_bounds__(kBlock) k_agg_count(Level g, const int32_t *cm
 // vertices counted since then, each thread its own, add the places reserved
 // to their own.  A popular community then takes an atomic per table and not
 // per tile (atomics to one address follow each other: 4M vertices in 70k
-// communities 0.51 -> 0.09 ms).  With few members each, nothing is popular, and
-// the second look at the table is lost (15M in 6.5M 0.66 -> 0.71): it takes
-// eight members a community.
+// uneven communities 0.51 -> 0.09 ms).  With few members each, nothing is
+// popular, and the second look at the table is lost (15M in 6.5M 0.66 -> 0.71):
+// it takes eight members a community.  Even communities gain from some
+// hundreds of members on (8.4M vertices, kept / by tiles: 128 random ones 0.10 /
+// 1.41 ms, 8,192 0.29 / 0.35; 131,072 0.39 / 0.39; eight in a row each 0.14 /
+// 0.09).
 constexpr int kKeptThreads = 1024, kKeptTable = 8192, kKeptR = 2, kKeptGroups = 256;
 constexpr int kKeptTile = kKeptThreads * kKeptR;
 constexpr int64_t kKeptFrom = (int64_t)kKeptGroups * kKeptTile;   // a tile for every workgroup

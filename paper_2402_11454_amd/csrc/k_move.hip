@@ -1202,7 +1202,11 @@ __global__ void __launch_bounds__(kBlock) k_move_hub_final(MoveArgs a) {
 // 68,000 movers among 1,992 tiles of 256: 54 us, now 29; 4.3 -> 2.9 ms of its
 // run).  A shorter queue leaves the chip idle in such tiles and waits for four
 // rounds of table operations instead (139,000 entries with few movers: 26 us
-// with the next compaction, 40 in wide tiles).
+// with the next compaction, 40 in wide tiles).  Where no community is popular
+// wide tiles gain nothing: the moves of a run over a random graph whose whole
+// queue is one sub-round take 0.76 of their time in tiles of 256 at 160,000
+// vertices, 0.80 at 200,000, 0.90 at 500,000 and 0.94 at 1M (blocks of 200:
+// 0.79, 0.83, 0.94, 0.99); the line is where the DC-SBM's queues gain.
 constexpr int kApplyR = 4;                     // queue entries per thread and tile, of long queues
 constexpr int64_t kApplyWide = 163840;         // those above this many entries
 constexpr int kApplyTable = 2 * kApplyR * kBlock;   // slots
@@ -1416,7 +1420,12 @@ __global__ void __launch_bounds__(kBlock) k_community_totals(const double *K, co
 // tiles and empties it when half of the slots are taken, so that few
 // communities cost an atomic per workgroup instead of one per tile (4M
 // vertices in 606 communities, where each took one from nearly every tile:
-// 0.56 ms, now 0.06; 16.8M in 7.9M, some giant: 1.03, now 0.18).
+// 0.56 ms, now 0.06; 16.8M in 7.9M, some giant: 1.03, now 0.18).  It is the
+// few or uneven communities that gain; many even ones cost a little more here
+// (8.4M vertices, kept / by tiles: 128 random communities 0.08 / 1.38 ms, 8,192
+// 0.28 / 0.34, 131,072 0.37 / 0.36; eight in a row each 0.12 / 0.07), and below
+// a tile for every workgroup more of them do (131,072 vertices, 8 to 15 us / 5
+// to 10).
 constexpr int kKeptThreads = 1024;
 constexpr int kKeptTable = 8192;
 constexpr int kKeptR = 2;
