@@ -190,7 +190,7 @@ inline Pair swap(uint32_t x, int half, int line) {   // the lower rows' word, th
 #define __builtin_amdgcn_permlane16_swap(x, y, fi, bc) emu::swap((x), 16, __LINE__)
 #define __builtin_amdgcn_permlane32_swap(x, y, fi, bc) emu::swap((x), 32, __LINE__)
 #define __builtin_amdgcn_fence(...) ((void)0)
-#define __builtin_amdgcn_wave_barrier() ((void)0)
+#define __builtin_amdgcn_wave_barrier() emu::yield(emu::kWave, __LINE__)
 #define __builtin_amdgcn_s_waitcnt(x) ((void)0)
 #define __hip_atomic_load(p, order, scope) (*(p))
 #define __hip_atomic_store(p, v, order, scope) (*(p) = (v))
